@@ -10,9 +10,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpufe.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["capi.cpp", "plan.cpp", "kernels.hip", "backward.hip", "split.hip", "aq_error.hip", "nonlocal.hip",
+SOURCES = ["capi.cpp", "plan.cpp", "kernels.hip", "moments.hip", "expand.hip", "backward.hip", "split.hip", "aq_error.hip", "nonlocal.hip",
            "bloch.hip", "scf.hip"]
-HEADERS = ["tables.hpp", "plan.hpp", "kernels.hpp", "basis.hpp", "backward.hpp", "device_common.hpp", "enrich.hpp",
+HEADERS = ["tables.hpp", "plan.hpp", "kernels.hpp", "moments.hpp", "basis.hpp", "backward.hpp", "device_common.hpp", "enrich.hpp",
            "aq_error.hpp", "stage.hpp", "limbs.hpp", "nonlocal.hpp", "bloch.hpp", "scf.hpp"]
 
 FLAGS = [
@@ -21,6 +21,11 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
 ]
+
+
+# per source: the moment sums live through the evaluation of the enrichment
+# functions; constants hoisted out of the stage loop would spill them
+EXTRA = {"moments.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def _hipcc() -> str:
@@ -38,7 +43,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
 
     def compile_one(src):
         obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-        cmd = [_hipcc(), *FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [_hipcc(), *FLAGS, *EXTRA.get(src, []), *inc, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)

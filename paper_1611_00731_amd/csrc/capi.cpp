@@ -14,6 +14,7 @@
 #include "backward.hpp"
 #include "bloch.hpp"
 #include "kernels.hpp"
+#include "moments.hpp"
 #include "nonlocal.hpp"
 #include "plan.hpp"
 #include "scf.hpp"
@@ -87,7 +88,22 @@ struct pufe_ctx {
     DevBuf<int32_t> d_edof, d_leaf_elem, d_color_elems, d_brow, d_bcol;
     DevBuf<int2> d_scat;
     std::vector<int2> reduce;       // (element, tile pair) of every element with several K-chunks
-    DevBuf<int2> d_reduce;
+    std::vector<int2> reduce_f64;   // those of the elements on the direct FP64 kernels
+    DevBuf<int2> d_reduce, d_reduce_f64;
+    // moment form (FP64): items of the 4- and 8-wave work groups with their
+    // costs, the wave tasks they point into, chunk sums and expansion lists
+    // (index 2: the items of the classical part)
+    std::vector<MomItemDev> mom_items[3];
+    std::vector<double> mom_cost[3];
+    std::vector<int32_t> mom_tasks;
+    std::vector<int4> mom_reduce, mom_expand;
+    size_t mom_lds[3] = {0, 0, 0};
+    int64_t mom_doubles = 0;
+    DevBuf<MomItemDev> d_mom_items[3];
+    DevBuf<int32_t> d_mom_tasks;
+    DevBuf<int4> d_mom_reduce, d_mom_expand;
+    DevBuf<double> d_mom;
+    DevBuf<CtxDev> d_self;          // this problem's tables, for the kernels that take a list of problems
     DevBuf<double2> d_ztab;
     DevBuf<uint32_t> d_leaves;
     DevBuf<int64_t> d_leaf_count, d_leaf_off, d_bval_off, d_dof_off;
@@ -163,6 +179,21 @@ static int fail(pufe_ctx *c, int code, const std::string &msg) {
 static int hipfail(pufe_ctx *c, hipError_t e, const char *where) {
     int code = (e == hipErrorOutOfMemory) ? PUFE_ERR_OOM : PUFE_ERR_HIP;
     return fail(c, code, std::string(where) + ": " + hipGetErrorString(e));
+}
+
+// The problem's device tables, without the buffers of a call.
+static CtxDev tables_of(const pufe_ctx *c) {
+    CtxDev d{};
+    d.kp = c->plan.kp;
+    d.elems = c->d_elems.p;
+    d.groups = c->d_groups.p;
+    d.img = c->d_img.p;
+    d.edof = c->d_edof.p;
+    d.leaves = c->d_leaves.p;
+    d.partial = c->d_partial.p;
+    d.mom = c->d_mom.p;
+    d.nnz = c->plan.nnz;
+    return d;
 }
 
 #define CHECK_HIP(ctx, x, where)                          \
@@ -313,11 +344,214 @@ static void plan_chunks(pufe_ctx *c, double target_items) {
         if (el.nchunk > 1)
             for (int p = 0; p < T * (T + 1) / 2; ++p) c->reduce.push_back(make_int2((int)e, p));
     }
+    c->reduce_f64.clear();
+    for (const int2 &r : c->reduce)
+        if (pl.elems[r.x].mchunk == 0) c->reduce_f64.push_back(r);
 }
 
+// ---- moment form
+
+// SIMD cycles per quadrature point of the wave tasks of an element (MFMA 17,
+// FP64 VALU 6, as measured beside each other on two waves per SIMD): the x
+// sums per line of n points, the y and z sums per line and per plane; fill:
+// the enrichment functions, once per work group.
+struct MomCost {
+    double e, a, bxy, bz, f, ff, fill;
+};
+static MomCost mom_cost_of(const Plan &pl, const ElemDev &el) {
+    const int n = pl.kp.n;
+    const double k = std::ceil(n / 4.0) / n, line = 6.0 / n, plane = 6.0 / (n * n);
+    MomCost m;
+    m.e = k * (13 * 17 + 9 * 6) + 12 * line + 36 * plane;
+    m.a = k * (2 * 17 + 6) + 6 * line + 18 * plane;
+    m.bxy = k * (5 * 17 + 2 * 6) + 12 * line + 36 * plane;
+    m.bz = k * (3 * 17 + 2 * 6) + 9 * line + 18 * plane;
+    m.f = (10 * 17 + 4 * 6) / 4.0 + 40 * plane;
+    m.ff = (2 * 17 + 4 * 6) / 4.0;
+    m.fill = 0.0;
+    for (int g = 0; g < el.ngrp; ++g) m.fill += (70 + 14 * (2 * pl.groups[el.grp_off + g].l + 1)) * 6.0 / 64.0;
+    return m;
+}
+static double mom_cost_total(const MomCost &m, int nt, int items) {
+    return mom_quads_ae(nt) * (m.e + m.a) + mom_quads_b(nt) * (m.bxy + m.bz) + mom_groups_f(nt) * m.f + items * m.fill;
+}
+
+// Waves per work group of the enriched part: elements of up to 12 functions
+// take 4-wave groups, two per CU, the others 8-wave groups with twice the
+// tasks to each evaluation of the enrichment functions.
+static int mom_waves(int nt) { return nt <= 3 ? 4 : 8; }
+
+// Wave tasks of an element of nt row tiles in nw-wave work groups, appended to
+// `out`; returns the work groups per K-chunk.  The overlap moments of x^0
+// and x^1 and the B_z moments (18 sums each) share a wave.  Tasks go, longest first, to the
+// least loaded SIMD (waves w and w + 4 of a work group); 4-wave groups come in
+// four rotations (4 entries each), so that two groups on one CU put their
+// longest task on different SIMDs.
+static int mom_wave_tasks(int nt, int nw, const MomCost &m, std::vector<int32_t> &out) {
+    std::vector<std::pair<double, int32_t>> tasks;
+    const int qa = mom_quads_ae(nt), qb = mom_quads_b(nt);
+    for (int i = 0; i < qa; ++i) tasks.push_back({m.e, MOM_E | (i << 8)});
+    for (int i = 0; i < qb; ++i) tasks.push_back({m.bxy, MOM_BXY | (i << 8)});
+    for (int i = 0; i < mom_groups_f(nt); ++i) tasks.push_back({m.f, MOM_F | (i << 8)});
+    for (int i = 0; i < std::max(qa, qb); ++i)   // qa <= qb for every nt
+        tasks.push_back(i < qa ? std::make_pair(m.a + m.bz, (int32_t)(MOM_A_BZ | (i << 8) | (i << 20)))
+                               : std::make_pair(m.bz, (int32_t)(MOM_BZ | (i << 20))));
+    std::stable_sort(tasks.begin(), tasks.end(),
+                     [](const std::pair<double, int32_t> &a, const std::pair<double, int32_t> &b) { return a.first > b.first; });
+    const int items = ((int)tasks.size() + nw - 1) / nw, cap = nw / 4, bins = 4 * items;
+    std::vector<double> load(bins, 0.0);
+    std::vector<int> used(bins, 0);
+    std::vector<int32_t> t((size_t)nw * items, MOM_IDLE);
+    for (const auto &k : tasks) {
+        int best = -1;
+        for (int b = 0; b < bins; ++b)
+            if (used[b] < cap && (best < 0 || load[b] < load[best])) best = b;
+        t[(size_t)nw * (best / 4) + best % 4 + 4 * used[best]] = k.second;
+        load[best] += k.first;
+        ++used[best];
+    }
+    for (int i = 0; i < items; ++i)
+        for (int r = 0; r < (nw == 4 ? 4 : 1); ++r)
+            for (int w = 0; w < nw; ++w) out.push_back(t[(size_t)nw * i + (w + r) % nw]);
+    return items;
+}
+
+// Which elements run in moment form, their K-chunks, slots and work items.
+static void plan_moments(pufe_ctx *c) {
+    Plan &pl = c->plan;
+    const int n = pl.kp.n, p = pl.kp.p;
+    for (int k = 0; k < 3; ++k) {
+        c->mom_items[k].clear();
+        c->mom_cost[k].clear();
+        c->mom_lds[k] = 0;
+    }
+    c->mom_tasks.clear();
+    c->mom_reduce.clear();
+    c->mom_expand.clear();
+    c->mom_doubles = 0;
+    int nimg = 0;
+    for (const ElemDev &el : pl.elems)
+        if (el.ngrp > 0) {
+            const GroupDev &g = pl.groups[el.grp_off + el.ngrp - 1];
+            nimg = std::max(nimg, g.img_off + g.nimg - pl.groups[el.grp_off].img_off);
+        }
+    // per number of row tiles: first wave task, work groups per chunk, stage
+    struct Kind {
+        int tab = -1, items = 0;
+        MomStage st{0, 0, 0};
+    };
+    std::vector<Kind> kinds(kMaxFun / 4 + 1);
+    std::vector<double> cost(pl.nel, 0.0);
+    double total = 0.0, fe_cost = 0.0, saved = 0.0;
+    for (int64_t e = 0; e < pl.nel; ++e) {
+        ElemDev &el = pl.elems[e];
+        el.mchunk = 0;
+        el.mom_base = 0;
+        el.nt = (el.nfun + 3) / 4;
+        if (p > 2) continue;   // the serendipity functions are no tensor products
+        Kind &kd = kinds[el.nt];
+        const MomCost m = mom_cost_of(pl, el);
+        if (el.nt > 0) {
+            if (kd.tab < 0) {
+                kd.st = mom_stage(el.nt, nimg, n, p, mom_waves(el.nt));
+                kd.tab = (int)c->mom_tasks.size();
+                kd.items = mom_wave_tasks(el.nt, mom_waves(el.nt), m, c->mom_tasks);
+            }
+            if (kd.st.planes == 0) continue;
+        }
+        const double per_point = mom_cost_total(m, el.nt, kd.items);
+        // the direct kernels: five 16x16x4 MFMAs of 64 cycles per tile pair
+        // and 4 points, the rows' VALU work about once more on top.  Measured
+        // over issue-bound time: about 2.0 there, 1.7 here
+        const int T = (el.nloc + 15) / 16;
+        const double direct = 2.0 * (T * (T + 1) / 2 * 80.0 + 3.0 * el.nloc + m.fill), moment = 1.7 * (per_point + m.ff);
+        if (moment > direct) continue;
+        saved += (direct - moment) * pl.kp.n3 * (double)(el.leaf_end - el.leaf_off);
+        el.mchunk = 1;
+        fe_cost = m.ff;
+        cost[e] = per_point * pl.kp.n3 * (double)(el.leaf_end - el.leaf_off);
+        total += cost[e] + m.ff * pl.kp.n3 * (double)(el.leaf_end - el.leaf_off);
+    }
+    // the moment form takes two to four launches more; below about 60 us of work
+    // saved on the whole chip (1024 SIMDs) a problem stays with the direct kernels
+    if (saved < 60e-6 * 2.4e9 * 1024.0) {
+        for (ElemDev &el : pl.elems) el.mchunk = el.fchunk = 0;
+        return;
+    }
+    // chunks: about four rounds of work groups over the chip, none shorter
+    // than 40,000 cycles (the start of a work group and its moments' stores)
+    const double dur = std::max(total / (1024.0 * 4.0), 40000.0);
+    for (int64_t e = 0; e < pl.nel; ++e) {
+        ElemDev &el = pl.elems[e];
+        el.fchunk = 0;
+        el.ff_base = 0;
+        if (el.mchunk == 0) continue;
+        const Kind &kd = kinds[el.nt];
+        const int w = mom_waves(el.nt) == 4 ? 0 : 1, slots = mom_slots(el.nt), nw = w ? 8 : 4;
+        const int64_t nleaf = el.leaf_end - el.leaf_off;
+        auto chunks = [&](double co) {
+            return std::max<int64_t>(1, std::min<int64_t>(nleaf, (int64_t)std::ceil(co / dur)));
+        };
+        auto add = [&](int list, int64_t ch, int64_t nch, int tab, double co) {
+            MomItemDev it{};
+            it.elem = (int32_t)e;
+            it.chunk = (int32_t)ch;
+            it.leaf_b = el.leaf_off + ch * nleaf / nch;
+            it.leaf_e = el.leaf_off + (ch + 1) * nleaf / nch;
+            it.tab = tab;
+            c->mom_items[list].push_back(it);
+            c->mom_cost[list].push_back(co / nch);
+        };
+        if (el.nt > 0) {
+            const double item = cost[e] / kd.items / (w ? 4.0 : 2.0);
+            const int64_t nch = chunks(item);
+            el.mchunk = (int32_t)nch;
+            el.mom_base = c->mom_doubles;
+            c->mom_doubles += nch * slots * (int64_t)kMomSlot;
+            c->mom_lds[w] = std::max(c->mom_lds[w], kd.st.lds);
+            for (int64_t ch = 0; ch < nch; ++ch)
+                for (int i = 0; i < kd.items; ++i) {
+                    const int k = (int)c->mom_items[w].size();
+                    const int off = w ? nw * i : 4 * (4 * i + ((k ^ (k >> 3) ^ (k >> 5) ^ (k >> 8)) & 3));
+                    add(w, ch, nch, (kd.tab + off) | (kd.st.planes << 24) | (kd.st.buffers << 28), item);
+                }
+            if (nch > 1) {
+                const int qe = mom_quads_ae(el.nt) + mom_quads_b(el.nt);
+                for (int s = 0; s < slots; ++s) c->mom_reduce.push_back(make_int4((int)e, s, (s < qe ? 54 : 40) * 64, 0));
+            }
+        }
+        // the classical part: a few leaves per wave (each leaf is a chain of
+        // planes, bound by latency)
+        const double fe = fe_cost * pl.kp.n3 * (double)nleaf / 2.0;
+        el.fchunk = (int32_t)((nleaf + 15) / 16);
+        el.ff_base = c->mom_doubles;
+        c->mom_doubles += el.fchunk * (int64_t)kMomFFSlot;
+        for (int64_t ch = 0; ch < el.fchunk; ++ch) add(2, ch, el.fchunk, 0, fe);
+        for (int q = 0; q < mom_quads_ae(el.nt); ++q) c->mom_expand.push_back(make_int4((int)e, MOM_X_ENR, q, 0));
+        for (int q = 0; 2 * q < el.nfun; ++q) c->mom_expand.push_back(make_int4((int)e, MOM_X_MIXED, q, 0));
+        c->mom_expand.push_back(make_int4((int)e, MOM_X_FE, 0, 0));
+    }
+    for (int w = 0; w < 3; ++w) {   // longest first
+        std::vector<size_t> order(c->mom_items[w].size());
+        for (size_t i = 0; i < order.size(); ++i) order[i] = i;
+        std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return c->mom_cost[w][a] > c->mom_cost[w][b]; });
+        std::vector<MomItemDev> it;
+        std::vector<double> co;
+        for (size_t i : order) {
+            it.push_back(c->mom_items[w][i]);
+            co.push_back(c->mom_cost[w][i]);
+        }
+        c->mom_items[w].swap(it);
+        c->mom_cost[w].swap(co);
+    }
+}
+
+static int upload_moments(pufe_ctx *ctx, hipStream_t st);
+
 // Work items (row block x column block of 16x16 tiles x K-chunk), largest
-// MFMA work first.  sel: 0 every element, 1 the elements of at most
-// kWholeMaxTiles tiles, 2 the others.
+// MFMA work first.  sel: 0 every element (the split kernels); the elements on
+// the direct FP64 kernels: 1 those of at most kWholeMaxTiles tiles, 2 the
+// others, 3 all.
 static std::vector<ItemDev> make_items(const pufe_ctx *c, int block_tiles, int *max_rows, int *max_leaves,
                                        int sel = 0) {
     const Plan &pl = c->plan;
@@ -326,7 +560,7 @@ static std::vector<ItemDev> make_items(const pufe_ctx *c, int block_tiles, int *
     for (int64_t e = 0; e < pl.nel; ++e) {
         const ElemDev &el = pl.elems[e];
         const int T = (el.nloc + 15) / 16;
-        if ((sel == 1 && T > kWholeMaxTiles) || (sel == 2 && T <= kWholeMaxTiles)) continue;
+        if ((sel == 1 && T > kWholeMaxTiles) || (sel == 2 && T <= kWholeMaxTiles) || (sel > 0 && el.mchunk > 0)) continue;
         // up to 5 tiles fit one diagonal block (15 tile pairs over 4 waves)
         const int bt = (T <= 5 && block_tiles >= 4) ? T : block_tiles;
         const int nb = (T + bt - 1) / bt;
@@ -367,6 +601,7 @@ static std::vector<ItemDev> make_items(const pufe_ctx *c, int block_tiles, int *
 }
 
 static void plan_items(pufe_ctx *c, double target_items, int block_tiles) {
+    plan_moments(c);
     plan_chunks(c, target_items);
     const int nfun = std::max(c->plan.max_nfun, 1);
     const int n3 = c->plan.kp.n3;
@@ -386,7 +621,7 @@ static void plan_items(pufe_ctx *c, double target_items, int block_tiles) {
     // the FP64 stage double-buffers the rows of an item: use the largest
     // tile block (and stage length) whose buffers fit in LDS
     for (int b = block_tiles; b >= 1; --b) {
-        c->items = make_items(c, b, &c->max_rows, &c->max_item_leaves, wide ? 1 : 0);
+        c->items = make_items(c, b, &c->max_rows, &c->max_item_leaves, wide ? 1 : 3);
         c->lds = contract_lds_bytes(c->contract_q, c->max_rows, nfun, c->plan.max_img, c->max_item_leaves, n3);
         if (c->lds > kMaxDynLds && c->contract_q > 16) {   // shorter stages before smaller blocks
             c->contract_q = 16;
@@ -462,6 +697,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     {
         hipError_t ea = init_contract_attributes();
+        if (ea == hipSuccess) ea = init_moment_attributes();
         if (ea == hipSuccess) ea = init_split_attributes();
         if (ea == hipSuccess) ea = init_backward_attributes();
         if (ea == hipSuccess) ea = init_nonlocal_attributes();
@@ -564,12 +800,17 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     CHECK_HIP(ctx, ctx->d_color_elems.upload(pl.color_elems, st), "upload colours");
     CHECK_HIP(ctx, ctx->d_scat.upload(pl.scat, st), "upload scatter list");
     CHECK_HIP(ctx, ctx->d_reduce.upload(ctx->reduce, st), "upload chunk reduction list");
+    CHECK_HIP(ctx, ctx->d_reduce_f64.upload(ctx->reduce_f64, st), "upload chunk reduction list");
     CHECK_HIP(ctx, ctx->d_ztab.alloc(kMaxKPerLaunch * 27), "alloc phase table");
     CHECK_HIP(ctx, ctx->d_brow.upload(pl.brow, st), "upload layout");
     CHECK_HIP(ctx, ctx->d_bcol.upload(pl.bcol, st), "upload layout");
     CHECK_HIP(ctx, ctx->d_bval_off.upload(pl.bval_off, st), "upload layout");
     CHECK_HIP(ctx, ctx->d_dof_off.upload(pl.dof_off, st), "upload layout");
     CHECK_HIP(ctx, ctx->d_partial.alloc((size_t)ctx->part_slots * 512), "alloc partial tiles");
+    {
+        int rc = upload_moments(ctx, st);
+        if (rc != PUFE_OK) return rc;
+    }
     {
         // the allocation-free entry's workspace: its device address is looked
         // up once per device, here at set-up
@@ -747,8 +988,23 @@ static int run_contraction(pufe_ctx *ctx, const double *d_V, int precision, hipS
                                            ctx->d_elems.p, ctx->d_groups.p, ctx->d_img.p, ctx->d_edof.p,
                                            ctx->d_leaves.p, d_V, partial, ctx->lds, st),
                   "contraction");
+        CHECK_HIP(ctx, launch_classical_moments(ctx->d_self.p, ctx->d_mom_items[2].p, (int)ctx->mom_items[2].size(), d_V, st),
+                  "contraction (classical moments)");
+        for (int w = 1; w >= 0; --w)
+            CHECK_HIP(ctx, launch_moments(w ? 8 : 4, pl.kp.n, pl.max_l, general_variant(pl), pl.kp.skew != 0, ctx->d_self.p, ctx->d_mom_items[w].p,
+                                          (int)ctx->mom_items[w].size(), ctx->d_mom_tasks.p, d_V, wimg, ctx->mom_lds[w], st),
+                      "contraction (moments)");
     }
     TimedRegion tr(ctx, 3, st);
+    if (precision == PUFE_PREC_FP64) {
+        CHECK_HIP(ctx, launch_chunk_reduce(ctx->d_elems.p, ctx->d_reduce_f64.p, (int)ctx->reduce_f64.size(), partial, st),
+                  "K-chunk reduction");
+        CHECK_HIP(ctx, launch_moment_reduce(ctx->d_self.p, ctx->d_mom_reduce.p, (int)ctx->mom_reduce.size(), st),
+                  "K-chunk reduction (moments)");
+        CHECK_HIP(ctx, launch_moment_expand(ctx->d_self.p, ctx->d_mom_expand.p, (int)ctx->mom_expand.size(), partial, st),
+                  "element matrices from moments");
+        return PUFE_OK;
+    }
     CHECK_HIP(ctx, launch_chunk_reduce(ctx->d_elems.p, ctx->d_reduce.p, (int)ctx->reduce.size(), partial, st),
               "K-chunk reduction");
     return PUFE_OK;
@@ -1360,6 +1616,21 @@ int pufe_kernel_times(pufe_ctx *ctx, double *out_ms, int64_t *counts, int reset)
     return PUFE_OK;
 }
 
+// Device tables and slots of the moment form for the current plan, and the
+// problem's own entry of a list of problems (the other tables are in place).
+static int upload_moments(pufe_ctx *ctx, hipStream_t st) {
+    for (int w = 0; w < 3; ++w)
+        CHECK_HIP(ctx, ctx->d_mom_items[w].upload(ctx->mom_items[w], st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_mom_tasks.upload(ctx->mom_tasks, st), "upload wave tasks");
+    CHECK_HIP(ctx, ctx->d_mom_reduce.upload(ctx->mom_reduce, st), "upload chunk reduction list");
+    CHECK_HIP(ctx, ctx->d_mom_expand.upload(ctx->mom_expand, st), "upload expansion list");
+    CHECK_HIP(ctx, ctx->d_mom.alloc((size_t)ctx->mom_doubles), "alloc moments");
+    std::vector<CtxDev> self(1);
+    self[0] = tables_of(ctx);
+    CHECK_HIP(ctx, ctx->d_self.upload(self, st), "upload tables");
+    return PUFE_OK;
+}
+
 // Upload the element table, work items and partial buffer of the current plan.
 static int upload_items(pufe_ctx *ctx, hipStream_t st) {
     ++ctx->plan_gen;
@@ -1368,7 +1639,12 @@ static int upload_items(pufe_ctx *ctx, hipStream_t st) {
     CHECK_HIP(ctx, ctx->d_items_wide.upload(ctx->items_wide, st), "upload work items");
     CHECK_HIP(ctx, ctx->d_items_split.upload(ctx->items_split, st), "upload work items");
     CHECK_HIP(ctx, ctx->d_reduce.upload(ctx->reduce, st), "upload chunk reduction list");
+    CHECK_HIP(ctx, ctx->d_reduce_f64.upload(ctx->reduce_f64, st), "upload chunk reduction list");
     CHECK_HIP(ctx, ctx->d_partial.alloc((size_t)ctx->part_slots * 512), "alloc partial tiles");
+    {
+        int rc = upload_moments(ctx, st);
+        if (rc != PUFE_OK) return rc;
+    }
     ctx->have_bw = false;
     ctx->have_poisson = false;
     return upload_nonlocal(ctx, st);
@@ -1537,8 +1813,19 @@ struct pufe_batch {
     DevBuf<CtxDev> d_ctxs;
     DevBuf<ItemDev> d_items, d_items_split, d_items_wide;
     DevBuf<int4> d_lists;
-    std::vector<int4> reduce;               // (problem, element, tile pair) of multi-chunk elements
-    DevBuf<int4> d_reduce;
+    // (problem, element, tile pair) of multi-chunk elements: all, and those on the direct FP64 kernels
+    std::vector<int4> reduce, reduce_f64;
+    DevBuf<int4> d_reduce, d_reduce_f64;
+    // moment form: items of all problems by work group width (index / 3: 4 or 8
+    // waves) and x steps of the rule (index % 3: 1..3); index 6: classical part
+    std::vector<MomItemDev> mom_items[7];
+    bool skew = false;                      // some cell is skewed
+    std::vector<int32_t> mom_tasks;
+    std::vector<int4> mom_reduce, mom_expand;
+    size_t mom_lds[7] = {};
+    DevBuf<MomItemDev> d_mom_items[7];
+    DevBuf<int32_t> d_mom_tasks;
+    DevBuf<int4> d_mom_reduce, d_mom_expand;
     DevBuf<double2> d_ztab;
     std::vector<int64_t> list_off;
     DevBuf<int> d_counter;
@@ -1667,6 +1954,38 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
                 b->lists[c->plan.elems[e].color].push_back(make_int4(i, (int)e, pp, 0));
         }
         for (const int2 &r : c->reduce) b->reduce.push_back(make_int4(i, r.x, r.y, 0));
+        for (const int2 &r : c->reduce_f64) b->reduce_f64.push_back(make_int4(i, r.x, r.y, 0));
+        for (int4 r : c->mom_reduce) {
+            r.w = i;
+            b->mom_reduce.push_back(r);
+        }
+        for (int4 r : c->mom_expand) {
+            r.w = i;
+            b->mom_expand.push_back(r);
+        }
+    }
+    // moment items of all problems, longest first, over the joined wave tasks
+    for (int i = 0; i < n; ++i) b->skew = b->skew || ctxs[i]->plan.kp.skew != 0;
+    for (int w = 0; w < 7; ++w) {
+        std::vector<std::pair<double, MomItemDev>> all;
+        int base = 0;
+        for (int i = 0; i < n; ++i) {
+            pufe_ctx *c = ctxs[i];
+            if (w == 6 || (c->plan.kp.n + 3) / 4 == w % 3 + 1) {
+                for (size_t k = 0; k < c->mom_items[w / 3].size(); ++k) {
+                    MomItemDev it = c->mom_items[w / 3][k];
+                    it.ctx = i;
+                    it.tab += base;
+                    all.push_back({c->mom_cost[w / 3][k], it});
+                }
+                b->mom_lds[w] = std::max(b->mom_lds[w], c->mom_lds[w / 3]);
+            }
+            if (w == 0) b->mom_tasks.insert(b->mom_tasks.end(), c->mom_tasks.begin(), c->mom_tasks.end());
+            base += (int)c->mom_tasks.size();
+        }
+        std::stable_sort(all.begin(), all.end(),
+                         [](const std::pair<double, MomItemDev> &a, const std::pair<double, MomItemDev> &c) { return a.first > c.first; });
+        for (auto &a : all) b->mom_items[w].push_back(a.second);
     }
     std::vector<int4> flat;
     b->list_off.assign(1, 0);
@@ -1711,6 +2030,16 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
     if (b->d_items.upload(b->items, st) != hipSuccess || b->d_items_split.upload(b->items_split, st) != hipSuccess ||
         b->d_items_wide.upload(b->items_wide, st) != hipSuccess ||
         b->d_lists.upload(flat, st) != hipSuccess || b->d_reduce.upload(b->reduce, st) != hipSuccess ||
+        b->d_reduce_f64.upload(b->reduce_f64, st) != hipSuccess ||
+        b->d_mom_items[0].upload(b->mom_items[0], st) != hipSuccess ||
+        b->d_mom_items[1].upload(b->mom_items[1], st) != hipSuccess ||
+        b->d_mom_items[2].upload(b->mom_items[2], st) != hipSuccess ||
+        b->d_mom_items[3].upload(b->mom_items[3], st) != hipSuccess ||
+        b->d_mom_items[4].upload(b->mom_items[4], st) != hipSuccess ||
+        b->d_mom_items[5].upload(b->mom_items[5], st) != hipSuccess ||
+        b->d_mom_items[6].upload(b->mom_items[6], st) != hipSuccess ||
+        b->d_mom_tasks.upload(b->mom_tasks, st) != hipSuccess || b->d_mom_reduce.upload(b->mom_reduce, st) != hipSuccess ||
+        b->d_mom_expand.upload(b->mom_expand, st) != hipSuccess ||
         b->d_counter.alloc(1) != hipSuccess || b->d_ctxs.alloc(n) != hipSuccess ||
         b->d_ztab.alloc(kMaxKPerLaunch * 27) != hipSuccess ||
         hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess) {
@@ -1772,17 +2101,10 @@ int pufe_batch_assemble(pufe_batch *b, const double *const *d_V, const double *k
         std::vector<CtxDev> cd(n);
         for (int i = 0; i < n; ++i) {
             pufe_ctx *c = b->ctxs[i];
-            cd[i].kp = c->plan.kp;
-            cd[i].elems = c->d_elems.p;
-            cd[i].groups = c->d_groups.p;
-            cd[i].img = c->d_img.p;
-            cd[i].edof = c->d_edof.p;
-            cd[i].leaves = c->d_leaves.p;
+            cd[i] = tables_of(c);
             cd[i].V = d_V[i];
-            cd[i].partial = c->d_partial.p;
             cd[i].H = d_H[i];
             cd[i].S = d_S ? d_S[i] : nullptr;
-            cd[i].nnz = c->plan.nnz;
         }
         CHECK_HIP_B(b, hipMemcpy(b->d_ctxs.p, cd.data(), sizeof(CtxDev) * n, hipMemcpyHostToDevice), "upload tables");
         KPoints kps;
@@ -1811,6 +2133,16 @@ int pufe_batch_assemble(pufe_batch *b, const double *const *d_V, const double *k
                                                         (int)b->items_wide.size(), b->d_counter.p, b->grid_wide,
                                                         b->lds_wide, b->cap);
             }
+            if (e == hipSuccess)
+                e = launch_classical_moments(b->d_ctxs.p, b->d_mom_items[6].p, (int)b->mom_items[6].size(), nullptr, b->cap);
+            for (int w = 5; w >= 0 && e == hipSuccess; --w)
+                e = launch_moments(w / 3 ? 8 : 4, 4 * (w % 3 + 1), b->max_l, b->gen, b->skew, b->d_ctxs.p, b->d_mom_items[w].p, (int)b->mom_items[w].size(),
+                                   b->d_mom_tasks.p, nullptr, nullptr, b->mom_lds[w], b->cap);
+            if (e == hipSuccess)
+                e = launch_chunk_reduce_batch(b->d_ctxs.p, b->d_reduce_f64.p, (int)b->reduce_f64.size(), b->cap);
+            if (e == hipSuccess) e = launch_moment_reduce(b->d_ctxs.p, b->d_mom_reduce.p, (int)b->mom_reduce.size(), b->cap);
+            if (e == hipSuccess)
+                e = launch_moment_expand(b->d_ctxs.p, b->d_mom_expand.p, (int)b->mom_expand.size(), nullptr, b->cap);
         } else {
             const int k = precision == PUFE_PREC_BF16X3 ? 0 : 1;
             if (b->lds_split[k] > kMaxDynLds) e = hipErrorInvalidValue;
@@ -1818,7 +2150,8 @@ int pufe_batch_assemble(pufe_batch *b, const double *const *d_V, const double *k
                 e = launch_split_persistent(k + 2, b->max_l, b->gen, b->d_ctxs.p, b->d_items_split.p, (int)b->items_split.size(), b->d_counter.p,
                                             b->grid_split[k], b->lds_split[k], b->cap);
         }
-        if (e == hipSuccess) e = launch_chunk_reduce_batch(b->d_ctxs.p, b->d_reduce.p, (int)b->reduce.size(), b->cap);
+        if (e == hipSuccess && precision != PUFE_PREC_FP64)
+            e = launch_chunk_reduce_batch(b->d_ctxs.p, b->d_reduce.p, (int)b->reduce.size(), b->cap);
         const bool f32 = out_dtype == PUFE_OUT_C64;
         for (int i = 0; i < n && e == hipSuccess; ++i) {
             const int64_t per = (out_dtype == PUFE_OUT_F64_GAMMA ? 1 : 2) * b->ctxs[i]->plan.nnz * n_k;

@@ -573,6 +573,16 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
     for (int c = 0; c < 3; ++c)
         for (int d = 0; d < 3; ++d) kp.Jt[3 * c + d] = 2.0 * mesh[d] * pl.inv[3 * c + d];
     kp.jac = pl.vol / (8.0 * n1 * n2 * n3);
+    // reference metric: grad f . grad g = sum_de G[d][e] d_d f d_e g
+    for (int d = 0; d < 3; ++d)
+        for (int e = 0; e < 3; ++e) {
+            kp.G[3 * d + e] = 0.0;
+            for (int c = 0; c < 3; ++c) kp.G[3 * d + e] += kp.Jt[3 * c + d] * kp.Jt[3 * c + e];
+        }
+    inverse3(kp.G, kp.Gi);
+    kp.skew = !(kp.Jt[1] == 0.0 && kp.Jt[2] == 0.0 && kp.Jt[3] == 0.0 && kp.Jt[5] == 0.0 && kp.Jt[6] == 0.0 &&
+                kp.Jt[7] == 0.0);
+    for (int d = 0; d < 3; ++d) kp.sd[d] = kp.skew ? 1.0 : kp.Jt[4 * d];
     kp.n = q.n_gauss;
     kp.n3 = q.n_gauss * q.n_gauss * q.n_gauss;
     kp.p = pr.p;

@@ -36,6 +36,12 @@ struct ElemDev {
     int32_t ncol;        // projector columns (sum of 2l+1 over the groups)
     int32_t pf_nchunk;   // K-chunks of its projector coefficients (0: none)
     int64_t pf_base;     // first double of its projector-coefficient slots, F[chunk][col][npad]
+    // moment form (FP64 contraction): K-chunks (0: the element runs the direct
+    // kernels), 4-row tiles of its enrichment functions, first double of its
+    // moment slots [chunk][task][kMomSlot], K-chunks of its classical part and
+    // the first double of theirs [chunk][kMomFFSlot]
+    int32_t mchunk, nt, fchunk;
+    int64_t mom_base, ff_base;
 };
 
 // Projector descriptor of one atom image that reaches an element: the 2l+1
@@ -84,6 +90,35 @@ struct ItemDev {
     int32_t ctx;         // problem of a batched launch (0 otherwise)
 };
 
+// A work item of the moment form: one element, one range of octree leaves and
+// the wave tasks wave_task[tab & 0xffffff ..] (one per wave of the work group;
+// planes per stage at bits 24..27, stage buffers at 28..29).  Items of the
+// classical part have no tasks.
+struct MomItemDev {
+    int32_t elem, chunk, tab, ctx;
+    int64_t leaf_b, leaf_e;
+};
+
+// Wave tasks of the moment form: role | index << 8 | second index << 20.  An
+// element's moment slots are its energy quads, its gradient quads and its
+// mixed groups, in that order; the index is the quad of 4x4 tile pairs or the
+// group of 8 functions.
+enum {
+    MOM_IDLE = 0,
+    MOM_E = 1,      // E of every x power and A of x^2
+    MOM_BXY = 2,    // B_x and B_y
+    MOM_A = 3,      // A of x^0 and x^1 (energy quad: index)
+    MOM_BZ = 4,     // B_z (gradient quad: second index)
+    MOM_A_BZ = 5,   // both
+    MOM_F = 6       // mixed
+};
+constexpr int kMomSlot = 54 * 64;   // doubles of one task's moments
+constexpr int kMomFFSlot = 320;     // doubles of the classical moments of one leaf range
+static inline __host__ __device__ int mom_quads_ae(int nt) { return (nt * (nt + 1) / 2 + 3) / 4; }
+static inline __host__ __device__ int mom_quads_b(int nt) { return (nt * nt + 3) / 4; }
+static inline __host__ __device__ int mom_groups_f(int nt) { return (nt + 1) / 2; }
+static inline __host__ __device__ int mom_slots(int nt) { return mom_quads_ae(nt) + mom_quads_b(nt) + mom_groups_f(nt); }
+
 // Per-launch constants of the mesh and the rule.
 struct KParams {
     double E[9];      // row d: a_d / n_d (element edge vector)
@@ -93,6 +128,10 @@ struct KParams {
     double rx[kMaxGauss], rw[kMaxGauss];   // reference rule of the error mode (nref points)
     int32_t n, n3, p, nfe, nfs, nref;
     int32_t mesh[3];
+    // reference metric G = Jt^T Jt and its inverse, the scale of the stored
+    // gradients against reference derivatives, and whether the cell is skewed
+    double G[9], Gi[9], sd[3];
+    int32_t skew;
     const double *spl;   // coefficients of the tabulated radials (device)
     // Bloch-periodic enrichment: the weight of every image entry at the
     // k-point of the launch, cos or sin(2 pi kappa.n) (null: periodic, all 1)
@@ -110,6 +149,7 @@ struct CtxDev {
     const uint32_t *leaves;
     const double *V;
     double *partial;
+    double *mom;         // moment slots
     void *H, *S;
     int64_t nnz;
 };
