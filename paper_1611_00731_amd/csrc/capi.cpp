@@ -13,6 +13,7 @@
 #include "aq_error.hpp"
 #include "backward.hpp"
 #include "bloch.hpp"
+#include "gather.hpp"
 #include "kernels.hpp"
 #include "moments.hpp"
 #include "nonlocal.hpp"
@@ -43,6 +44,12 @@ struct DevBuf {
         if (e == hipSuccess) n = count;
         else p = nullptr;
         return e;
+    }
+    // upload, with no buffer at all for an empty list (which no launch reads)
+    hipError_t upload_list(const std::vector<T> &v, hipStream_t st) {
+        if (!v.empty()) return upload(v, st);
+        release();
+        return hipSuccess;
     }
     hipError_t upload(const std::vector<T> &v, hipStream_t st) {
         hipError_t e = alloc(v.size());
@@ -85,8 +92,8 @@ struct pufe_ctx {
     DevBuf<GroupDev> d_groups;
     DevBuf<double> d_img, d_pos, d_partial;
     DevBuf<double> d_spl;           // coefficients of the tabulated radials
-    DevBuf<int32_t> d_edof, d_leaf_elem, d_color_elems, d_brow, d_bcol;
-    DevBuf<int2> d_scat;
+    DevBuf<int32_t> d_edof, d_leaf_elem, d_contr, d_brow, d_bcol;
+    DevBuf<int4> d_blocks;
     std::vector<int2> reduce;       // (element, tile pair) of every element with several K-chunks
     std::vector<int2> reduce_f64;   // those of the elements on the direct FP64 kernels
     DevBuf<int2> d_reduce, d_reduce_f64;
@@ -104,7 +111,6 @@ struct pufe_ctx {
     DevBuf<int4> d_mom_reduce, d_mom_expand;
     DevBuf<double> d_mom;
     DevBuf<CtxDev> d_self;          // this problem's tables, for the kernels that take a list of problems
-    DevBuf<double2> d_ztab;
     DevBuf<uint32_t> d_leaves;
     DevBuf<int64_t> d_leaf_count, d_leaf_off, d_bval_off, d_dof_off;
     DevBuf<ItemDev> d_items, d_items_split, d_items_wide;
@@ -192,6 +198,11 @@ static CtxDev tables_of(const pufe_ctx *c) {
     d.leaves = c->d_leaves.p;
     d.partial = c->d_partial.p;
     d.mom = c->d_mom.p;
+    d.contr = c->d_contr.p;
+    d.brow = c->d_brow.p;
+    d.bcol = c->d_bcol.p;
+    d.bval_off = c->d_bval_off.p;
+    d.dof_off = c->d_dof_off.p;
     d.nnz = c->plan.nnz;
     return d;
 }
@@ -782,12 +793,14 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     CHECK_HIP(ctx, ctx->d_groups.upload(pl.groups, st), "upload groups");
     CHECK_HIP(ctx, ctx->d_img.upload(pl.img_cur, st), "upload images");
     CHECK_HIP(ctx, ctx->d_edof.upload(pl.edof, st), "upload enriched functions");
-    CHECK_HIP(ctx, ctx->d_img_nk.upload(pl.img_nk, st), "upload image shifts");
-    CHECK_HIP(ctx, ctx->d_bpart.upload(pl.bpart, st), "upload enriched partners");
-    CHECK_HIP(ctx, ctx->d_wimg.alloc(pl.bloch ? pl.img_nk.size() / 4 : 0), "alloc image weights");
-    CHECK_HIP(ctx, ctx->d_items.upload(ctx->items, st), "upload work items");
-    CHECK_HIP(ctx, ctx->d_items_wide.upload(ctx->items_wide, st), "upload work items");
-    CHECK_HIP(ctx, ctx->d_items_split.upload(ctx->items_split, st), "upload work items");
+    if (pl.bloch) {
+        CHECK_HIP(ctx, ctx->d_img_nk.upload(pl.img_nk, st), "upload image shifts");
+        CHECK_HIP(ctx, ctx->d_bpart.upload(pl.bpart, st), "upload enriched partners");
+        CHECK_HIP(ctx, ctx->d_wimg.alloc(pl.img_nk.size() / 4), "alloc image weights");
+    }
+    CHECK_HIP(ctx, ctx->d_items.upload_list(ctx->items, st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_items_wide.upload_list(ctx->items_wide, st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_items_split.upload_list(ctx->items_split, st), "upload work items");
     // tables of the self-consistent field pieces belong to the previous plan
     ctx->d_dof_el_off.release();
     ctx->d_dof_el.release();
@@ -797,11 +810,10 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
         int rc = upload_nonlocal(ctx, st);
         if (rc != PUFE_OK) return rc;
     }
-    CHECK_HIP(ctx, ctx->d_color_elems.upload(pl.color_elems, st), "upload colours");
-    CHECK_HIP(ctx, ctx->d_scat.upload(pl.scat, st), "upload scatter list");
-    CHECK_HIP(ctx, ctx->d_reduce.upload(ctx->reduce, st), "upload chunk reduction list");
-    CHECK_HIP(ctx, ctx->d_reduce_f64.upload(ctx->reduce_f64, st), "upload chunk reduction list");
-    CHECK_HIP(ctx, ctx->d_ztab.alloc(kMaxKPerLaunch * 27), "alloc phase table");
+    CHECK_HIP(ctx, ctx->d_contr.upload(pl.contr, st), "upload assembly lists");
+    CHECK_HIP(ctx, ctx->d_blocks.upload(pl.blocks, st), "upload assembly lists");
+    CHECK_HIP(ctx, ctx->d_reduce.upload_list(ctx->reduce, st), "upload chunk reduction list");
+    CHECK_HIP(ctx, ctx->d_reduce_f64.upload_list(ctx->reduce_f64, st), "upload chunk reduction list");
     CHECK_HIP(ctx, ctx->d_brow.upload(pl.brow, st), "upload layout");
     CHECK_HIP(ctx, ctx->d_bcol.upload(pl.bcol, st), "upload layout");
     CHECK_HIP(ctx, ctx->d_bval_off.upload(pl.bval_off, st), "upload layout");
@@ -1033,8 +1045,8 @@ static int check_assemble_args(pufe_ctx *ctx, const double *d_V, const double *k
 
 // Assembly with the Bloch-periodic enrichment: for every k-point the image
 // weights, the contraction of the real and imaginary rows, the K-chunk sum,
-// the projector coefficients of those rows (with projectors), the complex
-// scatter of each colour into that k-point's output and the separable term.
+// the projector coefficients of those rows (with projectors), the assembly of
+// that k-point's output and the separable term.
 static int assemble_bloch(pufe_ctx *ctx, const double *d_V, const double *kpts, int n_k, int precision,
                           int out_dtype, void *d_H, void *d_S, hipStream_t st, bool nonlocal) {
     const Plan &pl = ctx->plan;
@@ -1047,14 +1059,6 @@ static int assemble_bloch(pufe_ctx *ctx, const double *d_V, const double *kpts, 
         kps.nk = std::min(kMaxKPerLaunch, n_k - k0);
         for (int k = 0; k < kps.nk; ++k)
             for (int d = 0; d < 3; ++d) kps.kap[k][d] = kpts[3 * (k0 + k) + d];
-        {
-            TimedRegion tr(ctx, 1, st);
-            if (k0 == 0)
-                CHECK_HIP(ctx, launch_prepare_outputs(d_H, d_S, (int64_t)(per * n_k * esz), kps, ctx->d_ztab.p, st),
-                          "zero outputs and phase table");
-            else
-                CHECK_HIP(ctx, launch_phase_table(kps, ctx->d_ztab.p, st), "phase table");
-        }
         for (int k = 0; k < kps.nk; ++k) {
             CHECK_HIP(ctx, launch_image_weights(ctx->d_img_nk.p, nimg, kps.kap[k], ctx->d_wimg.p, st),
                       "image weights");
@@ -1077,19 +1081,15 @@ static int assemble_bloch(pufe_ctx *ctx, const double *d_V, const double *kpts, 
             TimedRegion tr(ctx, 1, st);
             char *H = (char *)d_H + (size_t)(k0 + k) * per * esz;
             char *S = d_S ? (char *)d_S + (size_t)(k0 + k) * per * esz : nullptr;
-            for (size_t col = 0; col + 1 < pl.scat_off.size(); ++col) {
-                const int n = (int)(pl.scat_off[col + 1] - pl.scat_off[col]);
-                CHECK_HIP(ctx, launch_scatter_bloch(pl.kp, ctx->d_elems.p, ctx->d_scat.p + pl.scat_off[col], n,
-                                                    ctx->d_edof.p, ctx->d_bpart.p, ctx->d_partial.p,
-                                                    ctx->d_ztab.p + 27 * k, out_dtype, H, S, st),
-                          "scatter");
-            }
+            KPoints one;
+            std::memset(&one, 0, sizeof one);
+            one.nk = 1;
+            for (int d = 0; d < 3; ++d) one.kap[0][d] = kps.kap[k][d];
+            CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), ctx->d_partial.p, H, S, one,
+                                         out_dtype, true, st),
+                      "assembly");
             if (with_nl) {
                 // the separable term of this k-point into its H
-                KPoints one;
-                std::memset(&one, 0, sizeof one);
-                one.nk = 1;
-                for (int d = 0; d < 3; ++d) one.kap[0][d] = kps.kap[k][d];
                 const int64_t ndof = pl.dof_off[pl.nv];
                 CHECK_HIP(ctx, launch_nl_gather(pl.kp, ctx->d_elems.p, ctx->d_pgroups.p, ctx->d_edof.p, ctx->d_bpart.p,
                                                 ctx->d_dof_el_off.p, ctx->d_dof_el.p, ctx->d_Fp.p, one, pl.n_pfun,
@@ -1105,11 +1105,10 @@ static int assemble_bloch(pufe_ctx *ctx, const double *d_V, const double *kpts, 
     return PUFE_OK;
 }
 
-// Contraction, K-chunk sum, output zero fill and coloured scatter of one
-// assembly, with the partial tiles and the phase table in the given buffers.
+// Contraction, K-chunk sum and assembly of H and S, with the partial tiles in
+// the given buffer.
 static int assemble_impl(pufe_ctx *ctx, const double *d_V, const double *kpts, int n_k, int precision, int out_dtype,
-                         void *d_H, void *d_S, hipStream_t st, double *partial, double2 *ztab, bool timed,
-                         bool nonlocal = true) {
+                         void *d_H, void *d_S, hipStream_t st, double *partial, bool timed, bool nonlocal = true) {
     if (ctx->plan.bloch) return assemble_bloch(ctx, d_V, kpts, n_k, precision, out_dtype, d_H, d_S, st, nonlocal);
     int rc = run_contraction(ctx, d_V, precision, st, partial, timed);
     if (rc != PUFE_OK) return rc;
@@ -1137,18 +1136,9 @@ static int assemble_impl(pufe_ctx *ctx, const double *d_V, const double *kpts, i
             for (int d = 0; d < 3; ++d) kps.kap[k][d] = kpts[3 * (k0 + k) + d];
         char *H = (char *)d_H + (size_t)k0 * per * esz;
         char *S = d_S ? (char *)d_S + (size_t)k0 * per * esz : nullptr;
-        // the first pass zeroes every output (all k-points) with its phase table
-        if (k0 == 0)
-            CHECK_HIP(ctx, launch_prepare_outputs(d_H, d_S, (int64_t)(per * n_k * esz), kps, ztab, st),
-                      "zero outputs and phase table");
-        else
-            CHECK_HIP(ctx, launch_phase_table(kps, ztab, st), "phase table");
-        for (size_t col = 0; col + 1 < pl.scat_off.size(); ++col) {
-            const int n = (int)(pl.scat_off[col + 1] - pl.scat_off[col]);
-            CHECK_HIP(ctx, launch_scatter(pl.kp, ctx->d_elems.p, ctx->d_scat.p + pl.scat_off[col], n, ctx->d_edof.p,
-                                          partial, ztab, kps.nk, out_dtype, H, S, pl.nnz, st),
-                      "scatter");
-        }
+        CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), partial, H, S, kps, out_dtype,
+                                     false, st),
+                  "assembly");
         if (with_nl) {
             // the separable term of these k-points into H
             const int64_t ndof = pl.dof_off[pl.nv];
@@ -1171,8 +1161,7 @@ int pufe_assemble(pufe_ctx *ctx, const double *d_V, const double *kpts, int n_k,
     if (rc != PUFE_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
-    return assemble_impl(ctx, d_V, kpts, n_k, precision, out_dtype, d_H, d_S, st, ctx->d_partial.p, ctx->d_ztab.p,
-                         true);
+    return assemble_impl(ctx, d_V, kpts, n_k, precision, out_dtype, d_H, d_S, st, ctx->d_partial.p, true);
 }
 
 int pufe_assemble_noalloc(pufe_ctx *ctx, const double *d_V, const double *kpts, int n_k, int precision, int out_dtype,
@@ -1186,7 +1175,8 @@ int pufe_assemble_noalloc(pufe_ctx *ctx, const double *d_V, const double *kpts, 
         return fail(ctx, PUFE_ERR_UNSUPPORTED,
                     "pufe_assemble_noalloc: the Bloch-periodic enrichment keeps its image weights in context buffers; "
                     "use pufe_assemble");
-    // workspace: the phase table, then the partial tiles (256-byte aligned)
+    // workspace: the partial tiles, behind the room the size limit counts for
+    // a phase table
     const size_t ztab_bytes = (sizeof(double2) * kMaxKPerLaunch * 27 + 255) / 256 * 256;
     const size_t need = ztab_bytes + (size_t)ctx->part_slots * 512 * sizeof(double);
     if (need > kScratchBytes)
@@ -1199,7 +1189,7 @@ int pufe_assemble_noalloc(pufe_ctx *ctx, const double *d_V, const double *kpts, 
     double *ws = nullptr;
     CHECK_HIP(ctx, scratch_address(ctx->device, &ws), "workspace address");
     return assemble_impl(ctx, d_V, kpts, n_k, precision, out_dtype, d_H, d_S, st,
-                         ws + ztab_bytes / sizeof(double), (double2 *)ws, false);
+                         ws + ztab_bytes / sizeof(double), false);
 }
 
 int pufe_element_matrices(pufe_ctx *ctx, int64_t elem, const double *d_V, int precision, double *d_He,
@@ -1283,7 +1273,7 @@ static int build_poisson(pufe_ctx *ctx, hipStream_t st) {
         CHECK_HIP(ctx, Hfull.alloc((size_t)pl.nnz), "alloc kinetic matrix");
         const double gamma[3] = {0.0, 0.0, 0.0};
         int rc = assemble_impl(ctx, zeroV.p, gamma, 1, PUFE_PREC_FP64, PUFE_OUT_F64_GAMMA, Hfull.p, nullptr, st,
-                               ctx->d_partial.p, ctx->d_ztab.p, false, false);
+                               ctx->d_partial.p, false, false);
         if (rc != PUFE_OK) return rc;
         CHECK_HIP(ctx, ctx->d_Kfe.alloc((size_t)(nnzb * pl.nfs * pl.nfs)), "alloc FE stiffness");
         CHECK_HIP(ctx, launch_fe_blocks(nnzb, pl.nfs, ctx->d_bcol.p, ctx->d_bval_off.p, ctx->d_dof_off.p, Hfull.p, 2.0,
@@ -1620,11 +1610,12 @@ int pufe_kernel_times(pufe_ctx *ctx, double *out_ms, int64_t *counts, int reset)
 // problem's own entry of a list of problems (the other tables are in place).
 static int upload_moments(pufe_ctx *ctx, hipStream_t st) {
     for (int w = 0; w < 3; ++w)
-        CHECK_HIP(ctx, ctx->d_mom_items[w].upload(ctx->mom_items[w], st), "upload work items");
-    CHECK_HIP(ctx, ctx->d_mom_tasks.upload(ctx->mom_tasks, st), "upload wave tasks");
-    CHECK_HIP(ctx, ctx->d_mom_reduce.upload(ctx->mom_reduce, st), "upload chunk reduction list");
-    CHECK_HIP(ctx, ctx->d_mom_expand.upload(ctx->mom_expand, st), "upload expansion list");
-    CHECK_HIP(ctx, ctx->d_mom.alloc((size_t)ctx->mom_doubles), "alloc moments");
+        CHECK_HIP(ctx, ctx->d_mom_items[w].upload_list(ctx->mom_items[w], st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_mom_tasks.upload_list(ctx->mom_tasks, st), "upload wave tasks");
+    CHECK_HIP(ctx, ctx->d_mom_reduce.upload_list(ctx->mom_reduce, st), "upload chunk reduction list");
+    CHECK_HIP(ctx, ctx->d_mom_expand.upload_list(ctx->mom_expand, st), "upload expansion list");
+    if (ctx->mom_doubles > 0) CHECK_HIP(ctx, ctx->d_mom.alloc((size_t)ctx->mom_doubles), "alloc moments");
+    else ctx->d_mom.release();
     std::vector<CtxDev> self(1);
     self[0] = tables_of(ctx);
     CHECK_HIP(ctx, ctx->d_self.upload(self, st), "upload tables");
@@ -1635,11 +1626,11 @@ static int upload_moments(pufe_ctx *ctx, hipStream_t st) {
 static int upload_items(pufe_ctx *ctx, hipStream_t st) {
     ++ctx->plan_gen;
     CHECK_HIP(ctx, ctx->d_elems.upload(ctx->plan.elems, st), "upload elements");
-    CHECK_HIP(ctx, ctx->d_items.upload(ctx->items, st), "upload work items");
-    CHECK_HIP(ctx, ctx->d_items_wide.upload(ctx->items_wide, st), "upload work items");
-    CHECK_HIP(ctx, ctx->d_items_split.upload(ctx->items_split, st), "upload work items");
-    CHECK_HIP(ctx, ctx->d_reduce.upload(ctx->reduce, st), "upload chunk reduction list");
-    CHECK_HIP(ctx, ctx->d_reduce_f64.upload(ctx->reduce_f64, st), "upload chunk reduction list");
+    CHECK_HIP(ctx, ctx->d_items.upload_list(ctx->items, st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_items_wide.upload_list(ctx->items_wide, st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_items_split.upload_list(ctx->items_split, st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_reduce.upload_list(ctx->reduce, st), "upload chunk reduction list");
+    CHECK_HIP(ctx, ctx->d_reduce_f64.upload_list(ctx->reduce_f64, st), "upload chunk reduction list");
     CHECK_HIP(ctx, ctx->d_partial.alloc((size_t)ctx->part_slots * 512), "alloc partial tiles");
     {
         int rc = upload_moments(ctx, st);
@@ -1797,7 +1788,7 @@ struct pufe_batch {
     std::vector<uint64_t> gens;             // plan generation of each context at creation
     int device = 0;
     std::vector<ItemDev> items, items_split;
-    std::vector<std::vector<int4>> lists;   // per colour: (problem, element, tile pair)
+    std::vector<int4> blocks;               // assembly list of all problems (gather.hpp)
     // FP64 items in up to kBatchClasses classes, each a persistent launch of
     // its own (items [item_off[c], item_off[c + 1])): per stage length, the
     // problems whose combined stage fits two work groups per CU, then the rest
@@ -1812,7 +1803,7 @@ struct pufe_batch {
     int grid_wide = 0;
     DevBuf<CtxDev> d_ctxs;
     DevBuf<ItemDev> d_items, d_items_split, d_items_wide;
-    DevBuf<int4> d_lists;
+    DevBuf<int4> d_blocks;
     // (problem, element, tile pair) of multi-chunk elements: all, and those on the direct FP64 kernels
     std::vector<int4> reduce, reduce_f64;
     DevBuf<int4> d_reduce, d_reduce_f64;
@@ -1826,8 +1817,6 @@ struct pufe_batch {
     DevBuf<MomItemDev> d_mom_items[7];
     DevBuf<int32_t> d_mom_tasks;
     DevBuf<int4> d_mom_reduce, d_mom_expand;
-    DevBuf<double2> d_ztab;
-    std::vector<int64_t> list_off;
     DevBuf<int> d_counter;
     hipStream_t cap = nullptr;
     hipGraph_t graph = nullptr;
@@ -1878,7 +1867,6 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
     b->device = ctxs[0]->device;
     if (hipSetDevice(b->device) != hipSuccess) { delete b; return PUFE_ERR_HIP; }
     int max_rows_split = 16, max_nfun = 1, max_img = 0, max_leaves_split = 1, max_n3 = 1;
-    b->lists.assign(27, {});
     // FP64 classes.  Each problem keeps its own stage length (the one pufe_tune
     // chose, else the library default); the problems of one length, in order of
     // their own stage size, join that length's first class while the class's
@@ -1948,10 +1936,9 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
         b->max_l = std::max(b->max_l, c->plan.max_l);
         b->gen = b->gen || general_variant(c->plan);
         if (!c->items_wide.empty()) b->lds_wide = std::max(b->lds_wide, c->lds_wide);
-        for (int64_t e = 0; e < c->plan.nel; ++e) {
-            const int T = (c->plan.elems[e].nloc + 15) / 16;
-            for (int pp = 0; pp < T * (T + 1) / 2; ++pp)
-                b->lists[c->plan.elems[e].color].push_back(make_int4(i, (int)e, pp, 0));
+        for (int4 r : c->plan.blocks) {
+            r.w |= i;
+            b->blocks.push_back(r);
         }
         for (const int2 &r : c->reduce) b->reduce.push_back(make_int4(i, r.x, r.y, 0));
         for (const int2 &r : c->reduce_f64) b->reduce_f64.push_back(make_int4(i, r.x, r.y, 0));
@@ -1986,12 +1973,6 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
         std::stable_sort(all.begin(), all.end(),
                          [](const std::pair<double, MomItemDev> &a, const std::pair<double, MomItemDev> &c) { return a.first > c.first; });
         for (auto &a : all) b->mom_items[w].push_back(a.second);
-    }
-    std::vector<int4> flat;
-    b->list_off.assign(1, 0);
-    for (auto &l : b->lists) {
-        flat.insert(flat.end(), l.begin(), l.end());
-        b->list_off.push_back((int64_t)flat.size());
     }
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess || ncu < 1) ncu = 256;
@@ -2029,7 +2010,7 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
     hipStream_t st = nullptr;
     if (b->d_items.upload(b->items, st) != hipSuccess || b->d_items_split.upload(b->items_split, st) != hipSuccess ||
         b->d_items_wide.upload(b->items_wide, st) != hipSuccess ||
-        b->d_lists.upload(flat, st) != hipSuccess || b->d_reduce.upload(b->reduce, st) != hipSuccess ||
+        b->d_blocks.upload(b->blocks, st) != hipSuccess || b->d_reduce.upload(b->reduce, st) != hipSuccess ||
         b->d_reduce_f64.upload(b->reduce_f64, st) != hipSuccess ||
         b->d_mom_items[0].upload(b->mom_items[0], st) != hipSuccess ||
         b->d_mom_items[1].upload(b->mom_items[1], st) != hipSuccess ||
@@ -2041,7 +2022,6 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
         b->d_mom_tasks.upload(b->mom_tasks, st) != hipSuccess || b->d_mom_reduce.upload(b->mom_reduce, st) != hipSuccess ||
         b->d_mom_expand.upload(b->mom_expand, st) != hipSuccess ||
         b->d_counter.alloc(1) != hipSuccess || b->d_ctxs.alloc(n) != hipSuccess ||
-        b->d_ztab.alloc(kMaxKPerLaunch * 27) != hipSuccess ||
         hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess) {
         delete b;
         return PUFE_ERR_OOM;
@@ -2152,18 +2132,9 @@ int pufe_batch_assemble(pufe_batch *b, const double *const *d_V, const double *k
         }
         if (e == hipSuccess && precision != PUFE_PREC_FP64)
             e = launch_chunk_reduce_batch(b->d_ctxs.p, b->d_reduce.p, (int)b->reduce.size(), b->cap);
-        const bool f32 = out_dtype == PUFE_OUT_C64;
-        for (int i = 0; i < n && e == hipSuccess; ++i) {
-            const int64_t per = (out_dtype == PUFE_OUT_F64_GAMMA ? 1 : 2) * b->ctxs[i]->plan.nnz * n_k;
-            e = launch_fill_zero(d_H[i], per, f32, b->cap);
-            if (e == hipSuccess && d_S && d_S[i]) e = launch_fill_zero(d_S[i], per, f32, b->cap);
-        }
-        if (e == hipSuccess) e = launch_phase_table(kps, b->d_ztab.p, b->cap);
-        for (size_t col = 0; col + 1 < b->list_off.size() && e == hipSuccess; ++col) {
-            const int cnt = (int)(b->list_off[col + 1] - b->list_off[col]);
-            e = launch_scatter_batch(b->d_ctxs.p, b->d_lists.p + b->list_off[col], cnt, b->d_ztab.p, n_k, out_dtype,
-                                     b->cap);
-        }
+        if (e == hipSuccess)
+            e = launch_gather(b->d_ctxs.p, b->d_blocks.p, (int)b->blocks.size(), nullptr, nullptr, nullptr, kps, out_dtype,
+                              false, b->cap);
         hipGraph_t g = nullptr;
         hipError_t e2 = hipStreamEndCapture(b->cap, &g);
         if (e != hipSuccess) {

@@ -1,0 +1,228 @@
+// Assembly of H and S (eq. disceig3d, Bloch boundary conditions of eqs. bloch
+// and wbpspace): every entry of the block-sparse matrices is gathered from the
+// element matrices that hold it,
+//   H[g_a][g_b] = sum over elements of conj(p_a) p_b H_e[a][b],
+// and written once.  One wave per pair of blocks (v, w), (w, v): the matrices
+// are Hermitian, so the second block is the conjugate transpose of the first.
+//
+// Bound by writing H and S.  Scattering element by element instead needs the
+// outputs zeroed, two reads and two writes of each entry per element that
+// touches it, and one launch per element colour (8, or up to 27 on odd
+// meshes); gathered, an entry costs one write and one 8-byte read per element
+// (2.4 on average) from tiles that the caches hold, in one launch.  The sums
+// run in element order, so results do not depend on the launch.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "gather.hpp"
+
+namespace pufe {
+
+namespace {
+
+// Local function of element slot `slot` of the vertex at corner c (-1: the
+// element does not hold it): classical functions first, then the corner's
+// enriched entries from cs.
+__device__ __forceinline__ int local_of(int p, int nfs, int nfe, int c, int slot, int cs) {
+    if (slot >= nfs) return nfe + cs + (slot - nfs);
+    if (p == 1) return c;
+    if (p == 2) {   // midpoint slots lie in the positive directions of the vertex
+        if (slot & c) return -1;
+        const int d0 = (slot & 1) + 2 * (c & 1), d1 = ((slot >> 1) & 1) + (c & 2), d2 = (slot >> 2) + ((c >> 1) & 2);
+        return d0 + 3 * d1 + 9 * d2;
+    }
+    if (slot == 0) return c;
+    const int d = (slot - 1) >> 1;
+    if ((c >> d) & 1) return -1;
+    const int k = (c & ((1 << d) - 1)) | ((c >> (d + 1)) << d);   // the corner's place among those with bit d clear
+    return 8 + 2 * (4 * d + k) + ((slot - 1) & 1);
+}
+
+__device__ __forceinline__ int64_t entry_of(int a, int b) {
+    const int lo = min(a, b), hi = max(a, b), I = lo >> 4, J = hi >> 4;
+    return ((int64_t)J * (J + 1) / 2 + I) * 512 + (lo & 15) * 16 + (hi & 15);
+}
+
+__device__ __forceinline__ int64_t read_lane64(int64_t v, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+template <int DT>
+struct OutType {
+    typedef double2 type;
+};
+template <>
+struct OutType<1> {
+    typedef float2 type;
+};
+template <>
+struct OutType<2> {
+    typedef double type;
+};
+template <int DT>
+__device__ __forceinline__ typename OutType<DT>::type out_value(double re, double im) {
+    if constexpr (DT == 0) return make_double2(re, im);
+    else if constexpr (DT == 1) return make_float2((float)re, (float)im);
+    else return re;
+}
+
+}  // namespace
+
+template <int DT, bool BLOCH>
+__global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ ctxs, const int4 *__restrict__ list, int n,
+                                                     const double *__restrict__ partial1, void *H1, void *S1,
+                                                     const KPoints kps) {
+    typedef typename OutType<DT>::type Out;
+    __shared__ double2 sZ[kMaxKPerLaunch * 27];   // exp(2 pi i kappa . dn), dn = (t % 3, t / 3 % 3, t / 9) - 1
+    const int lane = threadIdx.x & 63, at = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const bool live = at < n;
+    const int4 e = list[live ? at : n - 1];
+    const CtxDev &cx = ctxs[e.w & 0x7ffffff];
+    const int ncon = e.w >> 27, nfs = cx.kp.nfs, nfe = cx.kp.nfe, p = cx.kp.p;
+    // lane j holds contribution j: element tiles, corners, lattice shift and
+    // the corners' enriched entries
+    int64_t base = 0;
+    int cc = 0, ca0 = 0, cb0 = 0, shift = 13, sa3 = 0, sb3 = 0;
+    if (lane < ncon) {
+        const int con = cx.contr[e.z + lane];
+        const ElemDev &el = cx.elems[con >> 6];
+        const int ca = (con >> 3) & 7, cb = con & 7;
+        base = el.part_base * 512;
+        cc = con & 63;
+        ca0 = el.cs[ca] | ((el.cs[ca + 1] - el.cs[ca]) << 16);
+        cb0 = el.cs[cb] | ((el.cs[cb + 1] - el.cs[cb]) << 16);
+        sa3 = (el.shifts >> (3 * ca)) & 7;
+        sb3 = (el.shifts >> (3 * cb)) & 7;
+        auto dn = [&](int d) { return ((sb3 >> d) & 1) - ((sa3 >> d) & 1) + 1; };
+        shift = dn(0) + 3 * dn(1) + 9 * dn(2);
+    }
+    // a block that meets no cell boundary has phase one (and, with the
+    // Bloch-periodic enrichment, the boundary phase on classical rows only)
+    const bool wraps = __any(lane < ncon && (BLOCH ? (sa3 | sb3) != 0 : shift != 13));
+    if (__syncthreads_or(live && wraps)) {
+        for (int i = threadIdx.x; i < kps.nk * 27; i += 256) {
+            const int k = i / 27, t = i - 27 * k;
+            double sn, cs;
+            sincos(2.0 * M_PI * (kps.kap[k][0] * (t % 3 - 1) + kps.kap[k][1] * ((t / 3) % 3 - 1) + kps.kap[k][2] * (t / 9 - 1)),
+                   &sn, &cs);
+            sZ[i] = make_double2(cs, sn);
+        }
+        __syncthreads();
+    }
+    if (!live) return;
+    const double *part = partial1 ? partial1 : cx.partial;
+    Out *H = (Out *)(H1 ? H1 : cx.H), *S = (Out *)(H1 ? S1 : cx.S);
+    const int64_t off = cx.bval_off[e.x], offT = cx.bval_off[e.y], nnz = cx.nnz;
+    const int64_t v = cx.brow[e.x], w = cx.bcol[e.x];
+    const int bv = (int)(cx.dof_off[v + 1] - cx.dof_off[v]), bw = (int)(cx.dof_off[w + 1] - cx.dof_off[w]);
+    const bool mirror = e.x != e.y;
+    for (int i = lane; i < bv * bw; i += 64) {
+        const int sa = i / bw, sb = i - sa * bw;
+        const int64_t o = off + i, oT = offT + (int64_t)sb * bv + sa;
+        auto put = [&](int k, double hr, double hi, double sr, double si) {
+            const int64_t b = (int64_t)k * nnz;
+            H[b + o] = out_value<DT>(hr, hi);
+            if (mirror) H[b + oT] = out_value<DT>(hr, -hi);
+            if (S) {
+                S[b + o] = out_value<DT>(sr, si);
+                if (mirror) S[b + oT] = out_value<DT>(sr, -si);
+            }
+        };
+        // one element's value: hr + i hi, sr + i si before the phase
+        auto value = [&](int j, double *h, double *s) -> bool {
+            const int c = __builtin_amdgcn_readlane(cc, j), ua = __builtin_amdgcn_readlane(ca0, j),
+                      ub = __builtin_amdgcn_readlane(cb0, j);
+            const int a = local_of(p, nfs, nfe, c >> 3, sa, ua & 0xffff), b = local_of(p, nfs, nfe, c & 7, sb, ub & 0xffff);
+            if (a < 0 || b < 0) return false;
+            const double *t = part + read_lane64(base, j);
+            const int64_t ab = entry_of(a, b);
+            h[0] = t[ab];
+            s[0] = t[ab + 256];
+            if (BLOCH) {   // the imaginary rows follow the corner's real ones
+                const int ai = a >= nfe ? a + (ua >> 17) : -1, bi = b >= nfe ? b + (ub >> 17) : -1;
+                h[1] = s[1] = 0.0;
+                if (ai >= 0 && bi >= 0) {
+                    const int64_t x = entry_of(ai, bi);
+                    h[0] += t[x];
+                    s[0] += t[x + 256];
+                }
+                if (bi >= 0) {
+                    const int64_t x = entry_of(a, bi);
+                    h[1] += t[x];
+                    s[1] += t[x + 256];
+                }
+                if (ai >= 0) {
+                    const int64_t x = entry_of(ai, b);
+                    h[1] -= t[x];
+                    s[1] -= t[x + 256];
+                }
+            }
+            return true;
+        };
+        if (!BLOCH && !wraps) {
+            double hr = 0.0, sr = 0.0;
+            for (int j = 0; j < ncon; ++j) {
+                double h[2], s[2];
+                if (value(j, h, s)) {
+                    hr += h[0];
+                    sr += s[0];
+                }
+            }
+            for (int k = 0; k < kps.nk; ++k) put(k, hr, 0.0, sr, 0.0);
+            continue;
+        }
+        for (int k0 = 0; k0 < kps.nk; k0 += 4) {
+            double hr[4], hi[4], sr[4], si[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) hr[u] = hi[u] = sr[u] = si[u] = 0.0;
+            for (int j = 0; j < ncon; ++j) {
+                double h[2], s[2];
+                if (!value(j, h, s)) continue;
+                int t = __builtin_amdgcn_readlane(shift, j);
+                if (BLOCH) {
+                    const int za = sa < nfs ? __builtin_amdgcn_readlane(sa3, j) : 0, zb = sb < nfs ? __builtin_amdgcn_readlane(sb3, j) : 0;
+                    auto dn = [&](int d) { return ((zb >> d) & 1) - ((za >> d) & 1) + 1; };
+                    t = dn(0) + 3 * dn(1) + 9 * dn(2);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (k0 + u >= kps.nk) break;
+                    const double2 z = wraps ? sZ[(k0 + u) * 27 + t] : make_double2(1.0, 0.0);
+                    hr[u] += z.x * h[0];
+                    hi[u] += z.y * h[0];
+                    sr[u] += z.x * s[0];
+                    si[u] += z.y * s[0];
+                    if (BLOCH) {
+                        hr[u] -= z.y * h[1];
+                        hi[u] += z.x * h[1];
+                        sr[u] -= z.y * s[1];
+                        si[u] += z.x * s[1];
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (k0 + u < kps.nk) put(k0 + u, hr[u], hi[u], sr[u], si[u]);
+        }
+    }
+}
+
+hipError_t launch_gather(const CtxDev *ctxs, const int4 *list, int n, const double *partial, void *H, void *S,
+                         const KPoints &kps, int out_dtype, bool bloch, hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    auto go = [&](auto *k) {
+        k<<<(n + 3) / 4, 256, 0, st>>>(ctxs, list, n, partial, H, S, kps);
+        return hipGetLastError();
+    };
+    if (bloch) {
+        if (out_dtype == 0) return go(gather_kernel<0, true>);
+        if (out_dtype == 1) return go(gather_kernel<1, true>);
+        return go(gather_kernel<2, true>);
+    }
+    if (out_dtype == 0) return go(gather_kernel<0, false>);
+    if (out_dtype == 1) return go(gather_kernel<1, false>);
+    return go(gather_kernel<2, false>);
+}
+
+}  // namespace pufe

@@ -1,0 +1,22 @@
+// Assembly of the block-sparse H and S from the element matrices (gather.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernels.hpp"
+#include "tables.hpp"
+
+namespace pufe {
+
+constexpr int kMaxBlockElems = 8;   // elements that hold both vertices of a block
+
+// H and S of the k-points kps: every stored block of the listed problems
+// written once.  list: (block (v, w) with v <= w, block (w, v), its first
+// contribution, problem | contributions << 27), contributions element << 6 |
+// corner of v << 3 | corner of w in element order.  partial, H, S: the buffers
+// of a single-problem call (partial null: each problem's own, also H and S);
+// bloch: the element matrices hold real and imaginary rows.
+hipError_t launch_gather(const CtxDev *ctxs, const int4 *list, int n, const double *partial, void *H, void *S,
+                         const KPoints &kps, int out_dtype, bool bloch, hipStream_t st);
+
+}  // namespace pufe

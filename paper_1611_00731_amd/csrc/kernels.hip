@@ -4,8 +4,6 @@
 //                   "Adaptive quadrature"), geometric refinement mode
 //   contract_f64    fused basis evaluation + FP64 MFMA contraction of the
 //                   element matrices H_e = B W_H B^T, S_e = B W B^T (eq. disceig3d)
-//   scatter         Bloch phases + atomic-free coloured scatter into the
-//                   block-sparse H and S (one launch per element colour)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -731,8 +729,6 @@ __global__ __launch_bounds__(256) void chunk_reduce_batch_kernel(const CtxDev *_
     chunk_reduce_tile(c.elems[ce.y], ce.z, c.partial);
 }
 
-// -------------------------------------------------------------- scatter
-
 __global__ void fill_zero_kernel(double *__restrict__ p, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -743,155 +739,6 @@ __global__ void fill_zero_f32_kernel(float *__restrict__ p, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (; i < n; i += stride) p[i] = 0.0f;
-}
-
-// Phase table z[k][t] = exp(2 pi i kappa_k . dn), dn = (t % 3, t / 3 % 3, t / 9) - 1:
-// the factor conj(p_a) p_b of a local pair whose corners differ by the
-// lattice shift dn (the Bloch phase factors at the cell boundary).
-__device__ __forceinline__ void phase_entry(const KPoints &kps, int idx, double2 *__restrict__ z) {
-    const int k = idx / 27, t = idx % 27;
-    const int dn[3] = {t % 3 - 1, (t / 3) % 3 - 1, t / 9 - 1};
-    double sn, cs;
-    sincos(2.0 * M_PI * (kps.kap[k][0] * dn[0] + kps.kap[k][1] * dn[1] + kps.kap[k][2] * dn[2]), &sn, &cs);
-    z[idx] = make_double2(cs, sn);
-}
-
-__global__ void phase_table_kernel(const KPoints kps, double2 *__restrict__ z) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= kps.nk * 27) return;
-    phase_entry(kps, idx, z);
-}
-
-// Zero fill of the H and S outputs of an assembly (nw 8-byte words each; S
-// may be null; zero bits serve every output type) and, in the first work
-// group, the phase table of its k-points: one launch ahead of the scatter.
-__global__ void prepare_outputs_kernel(double *__restrict__ H, double *__restrict__ S, int64_t nw, const KPoints kps,
-                                       double2 *__restrict__ z) {
-    if (blockIdx.x == 0)
-        for (int idx = threadIdx.x; idx < kps.nk * 27; idx += blockDim.x) phase_entry(kps, idx, z);
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nw; i += stride) {
-        H[i] = 0.0;
-        if (S) S[i] = 0.0;
-    }
-}
-
-// One upper tile pair (I, J) of one element: each thread owns one entry
-// (a, b), a <= b, sums its K-chunk partials in chunk order, and for every
-// k-point adds conj(p_a) p_b H_e[a][b] at (g_a, g_b) and the conjugate at
-// (g_b, g_a).  The elements of one launch share no vertex (one colour), so
-// no two threads of a launch touch the same entry.
-__device__ __forceinline__ void scatter_tile(const KParams &kp, const ElemDev &el, int pidx,
-                                             const int32_t *__restrict__ edof, const double *__restrict__ partial,
-                                             const double2 *__restrict__ z, int nk, int out_dtype,
-                                             void *__restrict__ Hout, void *__restrict__ Sout, int64_t nnz) {
-    const int nloc = el.nloc;
-    int J = 0;
-    while ((J + 1) * (J + 2) / 2 <= pidx) ++J;
-    const int I = pidx - J * (J + 1) / 2;
-    const int i = (int)(threadIdx.x >> 4), j = (int)(threadIdx.x & 15);
-    const int a = 16 * I + i, b = 16 * J + j;
-    if (a >= nloc || b >= nloc || a > b) return;
-    const int T = (nloc + 15) / 16;
-    const int64_t P = (int64_t)T * (T + 1) / 2;
-    // the K-chunk partials were summed into the chunk-0 slot
-    const double *src = partial + (el.part_base + pidx) * 512;
-    const double h = src[i * 16 + j], s = src[256 + i * 16 + j];
-    int ca, sa, cb, sb;
-    local_slot(el, edof, kp.p, a, &ca, &sa);
-    local_slot(el, edof, kp.p, b, &cb, &sb);
-    const int64_t oab = el.blk[ca * 8 + cb] + (int64_t)sa * el.bw[cb] + sb;
-    const int64_t oba = el.blk[cb * 8 + ca] + (int64_t)sb * el.bw[ca] + sa;
-    int t = 0;
-    for (int d = 2; d >= 0; --d) {
-        const int dn = ((el.shifts >> (3 * cb + d)) & 1) - ((el.shifts >> (3 * ca + d)) & 1);
-        t = 3 * t + (dn + 1);
-    }
-    if (out_dtype == 0) {
-        // complex128: four k-points at a time, all loads before the stores
-        // (the k-point arrays are disjoint), so their latencies overlap
-        double2 *H2 = (double2 *)Hout, *S2 = (double2 *)Sout;
-        for (int k0 = 0; k0 < nk; k0 += 4) {
-            double2 zk[4], hab[4], hba[4], sab[4], sba[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (k0 + u >= nk) break;
-                const int64_t base = (int64_t)(k0 + u) * nnz;
-                zk[u] = z[(k0 + u) * 27 + t];
-                hab[u] = H2[base + oab];
-                if (a != b) hba[u] = H2[base + oba];
-                if (Sout) {
-                    sab[u] = S2[base + oab];
-                    if (a != b) sba[u] = S2[base + oba];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (k0 + u >= nk) break;
-                const int64_t base = (int64_t)(k0 + u) * nnz;
-                const double cr = zk[u].x, ci = zk[u].y;
-                H2[base + oab] = make_double2(hab[u].x + cr * h, hab[u].y + ci * h);
-                if (a != b) H2[base + oba] = make_double2(hba[u].x + cr * h, hba[u].y - ci * h);
-                if (Sout) {
-                    S2[base + oab] = make_double2(sab[u].x + cr * s, sab[u].y + ci * s);
-                    if (a != b) S2[base + oba] = make_double2(sba[u].x + cr * s, sba[u].y - ci * s);
-                }
-            }
-        }
-        return;
-    }
-    for (int k = 0; k < nk; ++k) {
-        const double2 zz = z[k * 27 + t];
-        const double cr = zz.x, ci = zz.y;
-        if (out_dtype == 1) {
-            float *H = (float *)Hout + 2 * (int64_t)k * nnz;
-            H[2 * oab] += (float)(cr * h);
-            H[2 * oab + 1] += (float)(ci * h);
-            if (a != b) {
-                H[2 * oba] += (float)(cr * h);
-                H[2 * oba + 1] -= (float)(ci * h);
-            }
-            if (Sout) {
-                float *S = (float *)Sout + 2 * (int64_t)k * nnz;
-                S[2 * oab] += (float)(cr * s);
-                S[2 * oab + 1] += (float)(ci * s);
-                if (a != b) {
-                    S[2 * oba] += (float)(cr * s);
-                    S[2 * oba + 1] -= (float)(ci * s);
-                }
-            }
-        } else {
-            double *H = (double *)Hout + (int64_t)k * nnz;
-            H[oab] += h;
-            if (a != b) H[oba] += h;
-            if (Sout) {
-                double *S = (double *)Sout + (int64_t)k * nnz;
-                S[oab] += s;
-                if (a != b) S[oba] += s;
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void scatter_kernel(const KParams kp, const ElemDev *__restrict__ elems,
-                                                      const int2 *__restrict__ list,
-                                                      const int32_t *__restrict__ edof,
-                                                      const double *__restrict__ partial,
-                                                      const double2 *__restrict__ z, int nk, int out_dtype,
-                                                      void *__restrict__ Hout, void *__restrict__ Sout, int64_t nnz) {
-    const int2 ep = list[blockIdx.x];
-    scatter_tile(kp, elems[ep.x], ep.y, edof, partial, z, nk, out_dtype, Hout, Sout, nnz);
-}
-
-// Batched scatter of one colour: (problem, element, tile pair) of several
-// problems, each into its own output.
-__global__ __launch_bounds__(256) void scatter_batch_kernel(const CtxDev *__restrict__ ctxs,
-                                                            const int4 *__restrict__ list,
-                                                            const double2 *__restrict__ z, int nk,
-                                                            int out_dtype) {
-    const int4 ce = list[blockIdx.x];
-    const CtxDev &c = ctxs[ce.x];
-    scatter_tile(c.kp, c.elems[ce.y], ce.z, c.edof, c.partial, z, nk, out_dtype, c.H, c.S, c.nnz);
 }
 
 // Element matrices of one element (full, mirrored), from its partials.
@@ -940,8 +787,8 @@ __global__ void bsr_to_dense_kernel(int64_t nnzb, const int32_t *__restrict__ br
 
 // ------------------------------------------- allocation-free workspace
 //
-// The workspace of pufe_assemble_noalloc: the phase table and the K-chunk
-// partial tiles of one assembly, in a fixed array that the code object
+// The workspace of pufe_assemble_noalloc: the K-chunk partial tiles of one
+// assembly, in a fixed array that the code object
 // brings with it (each GPU holds its own copy for the life of the process).
 // In host code `scratch` is only a host-side stand-in for the symbol: kernels
 // get the device address that hipGetSymbolAddress returns on each device.
@@ -1127,29 +974,6 @@ hipError_t launch_chunk_reduce_batch(const CtxDev *ctxs, const int4 *list, int n
     return hipGetLastError();
 }
 
-hipError_t launch_phase_table(const KPoints &kps, double2 *z, hipStream_t st) {
-    hipLaunchKernelGGL(phase_table_kernel, dim3((kps.nk * 27 + 127) / 128), dim3(128), 0, st, kps, z);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter_batch(const CtxDev *ctxs, const int4 *list, int n, const double2 *z, int nk,
-                                int out_dtype, hipStream_t st) {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(scatter_batch_kernel, dim3(n), dim3(256), 0, st, ctxs, list, z, nk, out_dtype);
-    return hipGetLastError();
-}
-
-hipError_t launch_prepare_outputs(void *H, void *S, int64_t bytes, const KPoints &kps, double2 *z, hipStream_t st) {
-    if (bytes % 8 != 0) return hipErrorInvalidValue;
-    const int64_t nw = bytes / 8;
-    int64_t blocks = (nw + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(prepare_outputs_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (double *)H, (double *)S, nw,
-                       kps, z);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_zero(void *p, int64_t n, bool f32, hipStream_t st) {
     if (n == 0) return hipSuccess;
     int64_t blocks = (n + 255) / 256;
@@ -1158,15 +982,6 @@ hipError_t launch_fill_zero(void *p, int64_t n, bool f32, hipStream_t st) {
         hipLaunchKernelGGL(fill_zero_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (float *)p, n);
     else
         hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (double *)p, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter(const KParams &kp, const ElemDev *elems, const int2 *list, int n, const int32_t *edof,
-                          const double *partial, const double2 *z, int nk, int out_dtype, void *H, void *S,
-                          int64_t nnz, hipStream_t st) {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(scatter_kernel, dim3(n), dim3(256), 0, st, kp, elems, list, edof, partial, z, nk, out_dtype, H,
-                       S, nnz);
     return hipGetLastError();
 }
 

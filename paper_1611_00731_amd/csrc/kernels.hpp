@@ -12,7 +12,8 @@ constexpr int kContractQ = 16;      // quadrature points per LDS stage of the co
 constexpr int kMaxKPerLaunch = 16;  // k-points handled by one scatter launch
 constexpr int kSplitQ = 32;         // quadrature points per LDS stage of the split-bf16 contraction
 // Fixed device workspace of the allocation-free assembly (per GPU, held for
-// the life of the process): the phase table and the K-chunk partial tiles.
+// the life of the process): the K-chunk partial tiles, behind room for a phase
+// table that earlier layouts kept there (the size limit counts it).
 constexpr size_t kScratchBytes = PUFE_NOALLOC_WORKSPACE_BYTES;
 constexpr int kMaxDevices = 64;
 
@@ -63,15 +64,7 @@ hipError_t launch_split_persistent(int nlimb, int lmax, bool gen, const CtxDev *
                                    int grid, size_t lds, hipStream_t st);
 hipError_t launch_chunk_reduce(const ElemDev *elems, const int2 *list, int n, double *partial, hipStream_t st);
 hipError_t launch_chunk_reduce_batch(const CtxDev *ctxs, const int4 *list, int n, hipStream_t st);
-hipError_t launch_phase_table(const KPoints &kps, double2 *z, hipStream_t st);
-hipError_t launch_scatter_batch(const CtxDev *ctxs, const int4 *list, int n, const double2 *z, int nk,
-                                int out_dtype, hipStream_t st);
 hipError_t launch_fill_zero(void *p, int64_t n, bool f32, hipStream_t st);
-// zero H and S (bytes each, a multiple of 8; S may be null) and the phase table of kps, one launch
-hipError_t launch_prepare_outputs(void *H, void *S, int64_t bytes, const KPoints &kps, double2 *z, hipStream_t st);
-hipError_t launch_scatter(const KParams &kp, const ElemDev *elems, const int2 *list, int n, const int32_t *edof,
-                          const double *partial, const double2 *z, int nk, int out_dtype, void *H, void *S,
-                          int64_t nnz, hipStream_t st);
 hipError_t launch_elem_matrices(const ElemDev *elems, int64_t e, const double *partial, double *He, double *Se,
                                 int ld, hipStream_t st);
 hipError_t launch_bsr_to_dense(int64_t nnzb, const int32_t *brow, const int32_t *bcol, const int64_t *bval_off,

@@ -302,11 +302,11 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
     pl.brow_ptr[pl.nv] = (int64_t)pl.bcol.size();
     pl.bval_off.push_back(val);
     pl.nnz = val;
-    auto block_of = [&](int64_t v, int64_t w) -> int64_t {
+    auto block_index = [&](int64_t v, int64_t w) -> int64_t {
         auto b = pl.bcol.begin() + pl.brow_ptr[v], e = pl.bcol.begin() + pl.brow_ptr[v + 1];
-        auto it = std::lower_bound(b, e, (int32_t)w);
-        return pl.bval_off[it - pl.bcol.begin()];
+        return std::lower_bound(b, e, (int32_t)w) - pl.bcol.begin();
     };
+    std::vector<int32_t> elem_block((size_t)pl.nel * 64);   // block of every element's corner pairs
     // the blocks a projector function couples
     pl.nl_blocks.clear();
     for (const auto &vs : atom_vertices)
@@ -357,7 +357,11 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         }
         for (int ca = 0; ca < 8; ++ca) {
             el.bw[ca] = (int32_t)(pl.dof_off[cv[ca] + 1] - pl.dof_off[cv[ca]]);
-            for (int cb = 0; cb < 8; ++cb) el.blk[ca * 8 + cb] = block_of(cv[ca], cv[cb]);
+            for (int cb = 0; cb < 8; ++cb) {
+                const int64_t b = block_index(cv[ca], cv[cb]);
+                elem_block[64 * e + ca * 8 + cb] = (int32_t)b;
+                el.blk[ca * 8 + cb] = pl.bval_off[b];
+            }
         }
         // (atom, descriptor) groups present on the corners
         std::map<std::pair<int, int>, int> gidx;
@@ -446,6 +450,7 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         el.edof_off = (int32_t)pl.edof.size();
         int nenr = 0;
         for (int c = 0; c < 8; ++c) {
+            el.cs[c] = nenr;
             const int64_t t0 = pl.vf_off[cv[c]], t1 = pl.vf_off[cv[c] + 1];
             const int parts = pl.bloch ? 2 : 1;
             for (int part = 0; part < parts; ++part)
@@ -457,6 +462,7 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
                     ++nenr;
                 }
         }
+        el.cs[8] = nenr;
         el.nfe = pl.nfe;
         el.nloc = pl.nfe + nenr;
         if (el.nloc > kMaxNloc || nfun > kMaxFun || el.ngrp > kMaxGroups) {
@@ -536,34 +542,48 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
             pl.dof_el_off[g + 1] = (int64_t)pl.dof_el.size();
         }
     }
-    // the scatter relies on elements of one colour sharing no vertex
-    {
-        std::vector<int32_t> owner(pl.nv * 27, -1);
-        for (int64_t e = 0; e < pl.nel; ++e) {
-            const ElemDev &el = pl.elems[e];
-            for (int c = 0; c < 8; ++c) {
-                int j[3];
-                for (int d = 0; d < 3; ++d) j[d] = (el.ijk[d] + ((c >> d) & 1)) % mesh[d];
-                int64_t v = ((int64_t)j[2] * n2 + j[1]) * n1 + j[0];
-                int32_t &o = owner[v * 27 + el.color];
-                if (o >= 0 && o != (int32_t)e) { err = "internal error: element colouring conflict"; return PUFE_ERR_INVALID_ARG; }
-                o = (int32_t)e;
-            }
-        }
-    }
     pl.color_elems.clear();
     pl.color_off.assign(1, 0);
-    pl.scat.clear();
-    pl.scat_off.assign(1, 0);
     for (int c = 0; c < 27; ++c) {
         if (by_color[c].empty()) continue;
         pl.color_elems.insert(pl.color_elems.end(), by_color[c].begin(), by_color[c].end());
         pl.color_off.push_back((int32_t)pl.color_elems.size());
-        for (int32_t e : by_color[c]) {
-            const int T = (pl.elems[e].nloc + 15) / 16;
-            for (int p = 0; p < T * (T + 1) / 2; ++p) pl.scat.push_back(make_int2(e, p));
+    }
+    // ---- assembly lists: contributions of every block (v, w), v <= w, largest
+    // blocks first
+    {
+        const int64_t nnzb = (int64_t)pl.bcol.size();
+        if (pl.nel >= (int64_t)1 << 25 || nnzb >= (int64_t)1 << 31) { err = "too many elements"; return PUFE_ERR_UNSUPPORTED; }
+        std::vector<int32_t> first(nnzb + 1, 0), mirror(nnzb, -1);
+        auto upper = [&](int32_t b) { return pl.brow[b] <= pl.bcol[b]; };
+        for (size_t k = 0; k < elem_block.size(); ++k)
+            if (upper(elem_block[k])) ++first[elem_block[k] + 1];
+        for (int64_t k = 0; k < nnzb; ++k) first[k + 1] += first[k];
+        pl.contr.assign(first[nnzb], 0);
+        std::vector<int32_t> at(first.begin(), first.end() - 1);
+        for (size_t k = 0; k < elem_block.size(); ++k) {
+            const int32_t b = elem_block[k];
+            if (!upper(b)) continue;
+            pl.contr[at[b]++] = (int32_t)k;   // element << 6 | corner of v << 3 | corner of w
+            mirror[b] = elem_block[(k & ~(size_t)63) | (k & 7) << 3 | ((k >> 3) & 7)];
         }
-        pl.scat_off.push_back((int64_t)pl.scat.size());
+        // by the power of two of their work (at most 8 contributions, none for
+        // blocks that only projectors couple)
+        auto work = [&](int64_t b) {
+            int l = 0;
+            for (int64_t x = (pl.bval_off[b + 1] - pl.bval_off[b]) * (first[b + 1] - first[b] + 1); x > 1; x >>= 1) ++l;
+            return l;
+        };
+        int64_t start[66] = {};
+        for (int64_t b = 0; b < nnzb; ++b)
+            if (upper((int32_t)b)) ++start[65 - work(b)];
+        for (int l = 1; l < 66; ++l) start[l] += start[l - 1];
+        pl.blocks.assign(start[65], make_int4(0, 0, 0, 0));
+        for (int64_t b = 0; b < nnzb; ++b) {
+            if (!upper((int32_t)b)) continue;
+            const int64_t t = mirror[b] >= 0 ? mirror[b] : block_index(pl.bcol[b], pl.brow[b]);
+            pl.blocks[start[64 - work(b)]++] = make_int4((int)b, (int)t, first[b], (first[b + 1] - first[b]) << 27);
+        }
     }
 
     // ---- kernel constants

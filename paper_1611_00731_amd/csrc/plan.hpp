@@ -51,8 +51,10 @@ struct Plan {
     std::vector<int32_t> bpart;     // per enriched entry: its partner's entry index (-1: an imaginary part)
     std::vector<int32_t> color_elems;
     std::vector<int32_t> color_off; // n_colors + 1
-    std::vector<int2> scat;         // (element, upper tile pair), colour by colour
-    std::vector<int64_t> scat_off;  // n_colors + 1
+    // assembly: the (element, corner, corner) triples of every block with
+    // v <= w, element by element, and one entry per such block (see gather.hpp)
+    std::vector<int32_t> contr;
+    std::vector<int4> blocks;
     int max_nloc = 0, max_nfun = 0, max_ngrp = 0;
     int max_l = 0;                  // largest angular momentum of any descriptor
     int max_img = 0;                // most image centres of one element's groups

@@ -42,6 +42,7 @@ struct ElemDev {
     // the first double of theirs [chunk][kMomFFSlot]
     int32_t mchunk, nt, fchunk;
     int64_t mom_base, ff_base;
+    int32_t cs[9];       // first enriched entry of each corner, and their number
 };
 
 // Projector descriptor of one atom image that reaches an element: the 2l+1
@@ -150,6 +151,9 @@ struct CtxDev {
     const double *V;
     double *partial;
     double *mom;         // moment slots
+    // block layout and the elements of every block (assembly)
+    const int32_t *contr, *brow, *bcol;
+    const int64_t *bval_off, *dof_off;
     void *H, *S;
     int64_t nnz;
 };
