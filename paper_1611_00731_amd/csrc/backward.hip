@@ -765,23 +765,33 @@ __global__ __launch_bounds__(256) void backward_wide_kernel(
     }
 }
 
-// dL/dR of atom A: its partial slots summed in the order the host listed them
-// (P pass first, then Q pass).
-__global__ void force_reduce_kernel(int n_atoms, const int64_t *__restrict__ atom_ptr,
-                                    const int64_t *__restrict__ atom_slots, const double *__restrict__ fpartP,
-                                    const double *__restrict__ fpartQ, double *__restrict__ dLdR) {
-    const int A = blockIdx.x * blockDim.x + threadIdx.x;
-    if (A >= n_atoms) return;
+// dL/dR of atom A, one work group per atom: each thread sums a strided share
+// of the atom's partial slots (P pass, then Q pass) in list order, then a
+// fixed tree over the threads.  (One thread per atom was a chain of dependent
+// loads: 1.9 of the LiH-like cell's 8.1 ms.)
+__global__ __launch_bounds__(256) void force_reduce_kernel(const int64_t *__restrict__ atom_ptr,
+                                                           const int64_t *__restrict__ atom_slots,
+                                                           const double *__restrict__ fpartP,
+                                                           const double *__restrict__ fpartQ, double *__restrict__ dLdR) {
+    __shared__ double s[3][256];
+    const int A = blockIdx.x;
     double f[3] = {0.0, 0.0, 0.0};
     for (int pass = 0; pass < 2; ++pass) {
         const double *fp = pass == 0 ? fpartP : fpartQ;
         if (!fp) continue;
-        for (int64_t k = atom_ptr[A]; k < atom_ptr[A + 1]; ++k) {
+        for (int64_t k = atom_ptr[A] + threadIdx.x; k < atom_ptr[A + 1]; k += 256) {
             const int64_t sl = atom_slots[k];
             for (int c = 0; c < 3; ++c) f[c] += fp[3 * sl + c];
         }
     }
-    for (int c = 0; c < 3; ++c) dLdR[3 * A + c] = f[c];
+    for (int c = 0; c < 3; ++c) s[c][threadIdx.x] = f[c];
+    __syncthreads();
+    for (int st = 128; st > 0; st >>= 1) {
+        if ((int)threadIdx.x < st)
+            for (int c = 0; c < 3; ++c) s[c][threadIdx.x] += s[c][threadIdx.x + st];
+        __syncthreads();
+    }
+    if (threadIdx.x < 3) dLdR[3 * A + threadIdx.x] = s[threadIdx.x][0];
 }
 
 hipError_t init_backward_attributes() {
@@ -858,8 +868,7 @@ hipError_t launch_backward(const KParams &kp, bool qmode, int nl, int n_items, c
 hipError_t launch_force_reduce(int n_atoms, const int64_t *atom_ptr, const int64_t *atom_slots, const double *fP,
                                const double *fQ, double *dLdR, hipStream_t st) {
     if (n_atoms == 0) return hipSuccess;
-    hipLaunchKernelGGL(force_reduce_kernel, dim3((n_atoms + 63) / 64), dim3(64), 0, st, n_atoms, atom_ptr,
-                       atom_slots, fP, fQ, dLdR);
+    hipLaunchKernelGGL(force_reduce_kernel, dim3(n_atoms), dim3(256), 0, st, atom_ptr, atom_slots, fP, fQ, dLdR);
     return hipGetLastError();
 }
 
