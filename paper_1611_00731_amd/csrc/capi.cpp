@@ -140,6 +140,7 @@ struct pufe_ctx {
     // self-consistent field pieces: per-element load sums, the classical FE
     // blocks of the stiffness matrix, the FE integrals m_i, CG workspace
     DevBuf<double> d_fe_be, d_Kfe, d_mfe, d_fe_ones, d_cg, d_dot;
+    DevBuf<CgState> d_cg_state;
     DevBuf<int64_t> d_brow_ptr;
     bool have_poisson = false;
     double m_sum = 0.0;
@@ -1290,8 +1291,9 @@ static int build_poisson(pufe_ctx *ctx, hipStream_t st) {
     }
     int rc = fe_load_impl(ctx, ctx->d_fe_ones.p, ctx->d_mfe.p, st);
     if (rc != PUFE_OK) return rc;
-    CHECK_HIP(ctx, ctx->d_cg.alloc((size_t)(5 * nfe)), "alloc CG workspace");
-    CHECK_HIP(ctx, ctx->d_dot.alloc((size_t)(dot_partial_slots() + 1)), "alloc dot workspace");
+    CHECK_HIP(ctx, ctx->d_cg.alloc((size_t)(6 * nfe)), "alloc CG workspace");
+    CHECK_HIP(ctx, ctx->d_dot.alloc((size_t)(dot_partial_slots() + 1 + cg_partial_slots(pl.nv))), "alloc dot workspace");
+    CHECK_HIP(ctx, ctx->d_cg_state.alloc(1), "alloc CG state");
     double *out = ctx->d_dot.p + dot_partial_slots();
     CHECK_HIP(ctx, launch_dot(nfe, ctx->d_mfe.p, ctx->d_fe_ones.p, ctx->d_dot.p, out, st), "dot");
     if (!dev_scalar(ctx, out, &ctx->m_sum, st)) return fail(ctx, PUFE_ERR_HIP, "read FE integral sum");
@@ -1315,55 +1317,34 @@ int pufe_hartree(pufe_ctx *ctx, const double *d_n, double *d_vh, double *d_v, do
     }
     const Plan &pl = ctx->plan;
     const int64_t n = pl.nv * pl.nfs;
-    double *b = ctx->d_cg.p, *r = b + n, *p = r + n, *Ap = p + n, *x = Ap + n;
-    double *part = ctx->d_dot.p, *out = part + dot_partial_slots();
-    auto dot = [&](const double *a, const double *c, double *h) -> int {
-        CHECK_HIP(ctx, launch_dot(n, a, c, part, out, st), "dot");
-        if (!dev_scalar(ctx, out, h, st)) return fail(ctx, PUFE_ERR_HIP, "read dot product");
-        return PUFE_OK;
-    };
-    // right-hand side 4 pi (b - nbar m), nbar = int n / int 1 (the neutralising background)
+    double *b = ctx->d_cg.p, *x = b + 5 * n;
+    double *dots = ctx->d_dot.p;   // block partials of sum b and sum m x
+    CgSolve cg{pl.nv, pl.nfs, ctx->d_brow_ptr.p, ctx->d_bcol.p, ctx->d_Kfe.p, b + n, b + 2 * n, b + 3 * n, b + 4 * n, x,
+               dots + dot_partial_slots() + 1, ctx->d_cg_state.p};
+    // right-hand side 4 pi (b - nbar m), nbar = int n / int 1 (the neutralising
+    // background); conjugate gradients on K x = r from x = 0 (K is singular
+    // with the constants as its kernel; r is orthogonal to them)
     rc = fe_load_impl(ctx, d_n, b, st);
     if (rc != PUFE_OK) return rc;
-    double bsum = 0.0;
-    if ((rc = dot(b, ctx->d_fe_ones.p, &bsum)) != PUFE_OK) return rc;
-    const double nbar = bsum / ctx->m_sum;
-    CHECK_HIP(ctx, launch_scaled_diff(n, 4.0 * M_PI, b, nbar, ctx->d_mfe.p, r, st), "right-hand side");
-    // conjugate gradients on K x = r from x = 0 (K is singular with the
-    // constants as its kernel; r is orthogonal to them)
-    CHECK_HIP(ctx, launch_fill_zero(x, n, false, st), "zero solution");
-    CHECK_HIP(ctx, hipMemcpyAsync(p, r, sizeof(double) * n, hipMemcpyDeviceToDevice, st), "copy residual");
-    double rr = 0.0;
-    if ((rc = dot(r, r, &rr)) != PUFE_OK) return rc;
-    const double r0 = std::sqrt(rr);
-    int it = 0;
-    double rel = 0.0;
-    if (r0 > 0.0) {
-        for (; it < max_iter; ++it) {
-            CHECK_HIP(ctx, launch_fe_spmv(pl.nv, pl.nfs, ctx->d_brow_ptr.p, ctx->d_bcol.p, ctx->d_Kfe.p, p, Ap, st),
-                      "FE stiffness product");
-            double pAp = 0.0;
-            if ((rc = dot(p, Ap, &pAp)) != PUFE_OK) return rc;
-            if (!(pAp > 0.0)) break;
-            const double alpha = rr / pAp;
-            CHECK_HIP(ctx, launch_axpby(n, alpha, p, 1.0, x, st), "CG update");
-            CHECK_HIP(ctx, launch_axpby(n, -alpha, Ap, 1.0, r, st), "CG update");
-            double rn = 0.0;
-            if ((rc = dot(r, r, &rn)) != PUFE_OK) return rc;
-            rel = std::sqrt(rn) / r0;
-            if (rel <= tol) {
-                ++it;
-                break;
-            }
-            CHECK_HIP(ctx, launch_axpby(n, 1.0, r, rn / rr, p, st), "CG direction");
-            rr = rn;
-        }
+    CHECK_HIP(ctx, launch_dot_partials(n, b, ctx->d_fe_ones.p, dots, st), "dot");
+    CHECK_HIP(ctx, launch_cg_start(cg, b, ctx->d_mfe.p, dots, ctx->m_sum, st), "right-hand side");
+    CgState state{};
+    for (int it = 0; it <= max_iter;) {
+        // launches past the end of the solve do nothing: a batch is long
+        // enough to hide the look at its outcome, short enough to waste little
+        const int end = std::min(it + 16, max_iter);
+        for (; it < end; ++it) CHECK_HIP(ctx, launch_cg_iteration(cg, it, tol, false, st), "CG iteration");
+        CHECK_HIP(ctx, launch_cg_iteration(cg, it, tol, it == max_iter, st), "CG iteration");
+        ++it;
+        CHECK_HIP(ctx, hipMemcpyAsync(&state, ctx->d_cg_state.p, sizeof state, hipMemcpyDeviceToHost, st), "CG state");
+        CHECK_HIP(ctx, hipStreamSynchronize(st), "CG state");
+        if (state.done || state.broken) break;
     }
+    const int it = state.it;
+    const double rel = state.rel;
     // zero mean: int V_H = sum_i x_i m_i = 0
-    double mx = 0.0;
-    if ((rc = dot(ctx->d_mfe.p, x, &mx)) != PUFE_OK) return rc;
-    CHECK_HIP(ctx, launch_axpby(n, -mx / ctx->m_sum, ctx->d_fe_ones.p, 1.0, x, st), "zero mean");
-    if (d_v) CHECK_HIP(ctx, hipMemcpyAsync(d_v, x, sizeof(double) * n, hipMemcpyDeviceToDevice, st), "copy solution");
+    CHECK_HIP(ctx, launch_dot_partials(n, ctx->d_mfe.p, x, dots, st), "dot");
+    CHECK_HIP(ctx, launch_cg_mean(cg, dots, ctx->m_sum, d_v, st), "zero mean");
     CHECK_HIP(ctx, launch_fe_eval(pl.kp, ctx->d_elems.p, ctx->d_edof.p, ctx->d_leaves.p, ctx->d_leaf_elem.p,
                                   ctx->n_qp, x, d_vh, st),
               "Hartree potential at the points");

@@ -146,23 +146,6 @@ __global__ void fe_blocks_kernel(int64_t nnzb, int nfs, const int32_t *__restric
     K[i] = scale * A[bval_off[blk] + s * bw + t];
 }
 
-// y = K x over the classical FE space (block rows per vertex).
-__global__ void fe_spmv_kernel(int64_t nv, int nfs, const int64_t *__restrict__ brow_ptr,
-                               const int32_t *__restrict__ bcol, const double *__restrict__ K,
-                               const double *__restrict__ x, double *__restrict__ y) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nv * nfs) return;
-    const int64_t v = i / nfs;
-    const int s = (int)(i - v * nfs);
-    double acc = 0.0;
-    for (int64_t k = brow_ptr[v]; k < brow_ptr[v + 1]; ++k) {
-        const double *Kb = K + k * nfs * nfs + (int64_t)s * nfs;
-        const double *xb = x + (int64_t)bcol[k] * nfs;
-        for (int t = 0; t < nfs; ++t) acc += Kb[t] * xb[t];
-    }
-    y[i] = acc;
-}
-
 // Dot product in a fixed order: kDotBlocks partial sums (grid-strided, tree
 // per block), then one block sums them.
 __global__ __launch_bounds__(256) void dot_partial_kernel(int64_t n, const double *__restrict__ a,
@@ -192,17 +175,154 @@ __global__ __launch_bounds__(256) void dot_final_kernel(int n, const double *__r
     if (threadIdx.x == 0) *out = s[0];
 }
 
-// y = a x + b y
-__global__ void axpby_kernel(int64_t n, double a, const double *__restrict__ x, double b, double *__restrict__ y) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = a * x[i] + b * y[i];
+// ------------------------------------------------- conjugate gradients
+//
+// K x = r on the classical FE space, every scalar on the device: an iteration
+// is two launches, each of which sums the block partials of the one before it
+// in a fixed order, and the host only looks at `done` once per batch of
+// iterations.  (Read back to the host, the three scalars of an iteration cost
+// more than its arithmetic: 5.2 ms for 59 iterations on 4096 unknowns.)
+//
+// Launch A(i): rr = |r_i|^2; stop if it meets the tolerance, else beta,
+// p_i = r_i + beta p_{i-1} (kept in the buffer of parity i), Ap = K p_i and
+// the partials of p_i . Ap.  Launch B(i): alpha, x += alpha p_i,
+// r -= alpha Ap and the partials of |r|^2.
+
+// Sum of n partials by a work group of 256, the same in every group.
+__device__ __forceinline__ double sum_partials(const double *__restrict__ part, int n, double *__restrict__ s) {
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) acc += part[i];
+    s[threadIdx.x] = acc;
+    __syncthreads();
+    for (int st = 128; st > 0; st >>= 1) {
+        if ((int)threadIdx.x < st) s[threadIdx.x] += s[threadIdx.x + st];
+        __syncthreads();
+    }
+    const double v = s[0];
+    __syncthreads();
+    return v;
 }
 
-// y = a (x - c z)
-__global__ void scaled_diff_kernel(int64_t n, double a, const double *__restrict__ x, double c,
-                                   const double *__restrict__ z, double *__restrict__ y) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = a * (x[i] - c * z[i]);
+__device__ __forceinline__ void put_partial(double v, double *__restrict__ part, double *__restrict__ s) {
+    s[threadIdx.x] = v;
+    __syncthreads();
+    for (int st = 128; st > 0; st >>= 1) {
+        if ((int)threadIdx.x < st) s[threadIdx.x] += s[threadIdx.x + st];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+}
+
+// r = 4 pi (b - nbar m), nbar = (sum of b) / msum, x = 0, partials of |r|^2.
+__global__ __launch_bounds__(256) void cg_start_kernel(int64_t n, const double *__restrict__ b, const double *__restrict__ m,
+                                                       const double *__restrict__ bpart, int nbpart, double msum,
+                                                       double *__restrict__ r, double *__restrict__ x,
+                                                       double *__restrict__ part, CgState *__restrict__ st) {
+    __shared__ double s[256];
+    const double nbar = sum_partials(bpart, nbpart, s) / msum;
+    double rr = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const double v = 4.0 * M_PI * (b[i] - nbar * m[i]);
+        r[i] = v;
+        x[i] = 0.0;
+        rr += v * v;
+    }
+    put_partial(rr, part, s);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *st = CgState{{0.0, 0.0}, 0.0, 0.0, 0, 0, 0};
+}
+
+// A(i), one wave per vertex: lane l of a group of nfs^2 holds entry (s, t) of
+// a block, groups of lanes take the row's blocks in turn.  check: only the
+// test of the tolerance (after the last iteration allowed).
+__global__ __launch_bounds__(256) void cg_spmv_kernel(int64_t nv, int nfs, int it, double tol, int check,
+                                                      const int64_t *__restrict__ brow_ptr,
+                                                      const int32_t *__restrict__ bcol, const double *__restrict__ K,
+                                                      const double *__restrict__ r, const double *__restrict__ p0,
+                                                      double *__restrict__ p1, double *__restrict__ Ap,
+                                                      const double *__restrict__ rpart, int nrpart,
+                                                      double *__restrict__ part, CgState *__restrict__ st) {
+    __shared__ double s[256];
+    if (st->done || st->broken) return;
+    const double rr = sum_partials(rpart, nrpart, s);
+    const double old = st->rr[(it + 1) & 1], r0 = it == 0 ? sqrt(rr) : st->r0, rel = it == 0 ? 0.0 : sqrt(rr) / r0;
+    const bool stop = it == 0 ? !(r0 > 0.0) : rel <= tol;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->rr[it & 1] = rr;
+        st->r0 = r0;
+        st->rel = rel;
+        if (stop || check) {
+            st->it = it;
+            st->done = 1;
+        }
+    }
+    if (stop || check) return;
+    const double beta = it == 0 ? 0.0 : rr / old;
+    const int per = nfs * nfs, G = 64 / per, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = (int64_t)blockIdx.x * 4 + wave;
+    const int g = lane / per, e = lane - g * per, row = e / nfs, col = e - row * nfs;
+    // p_i at index j; p0 is not read in the first iteration
+    auto dir = [&](int64_t j) { return beta == 0.0 ? r[j] : r[j] + beta * p0[j]; };
+    double acc = 0.0;
+    if (v < nv && g < G) {
+        const int64_t k1 = brow_ptr[v + 1];
+#pragma unroll 4
+        for (int64_t k = brow_ptr[v] + g; k < k1; k += G) acc += K[k * per + e] * dir((int64_t)bcol[k] * nfs + col);
+    }
+    s[threadIdx.x] = acc;
+    __syncthreads();
+    double pAp = 0.0;
+    if (v < nv && lane < nfs) {
+        double y = 0.0;
+        for (int h = 0; h < G; ++h)
+            for (int t = 0; t < nfs; ++t) y += s[64 * wave + h * per + lane * nfs + t];
+        const int64_t i = v * nfs + lane;
+        const double pi = dir(i);
+        p1[i] = pi;
+        Ap[i] = y;
+        pAp = pi * y;
+    }
+    __syncthreads();
+    put_partial(pAp, part, s);
+}
+
+// B(i)
+__global__ __launch_bounds__(256) void cg_update_kernel(int64_t n, int it, const double *__restrict__ p,
+                                                        const double *__restrict__ Ap, double *__restrict__ x,
+                                                        double *__restrict__ r, const double *__restrict__ apart,
+                                                        int napart, double *__restrict__ part, CgState *__restrict__ st) {
+    __shared__ double s[256];
+    // `broken` of an earlier launch only: a group of this one that finds
+    // p.Ap <= 0 before another has started leads it to the same decision
+    if (st->done || st->broken) return;
+    const double pAp = sum_partials(apart, napart, s);
+    if (!(pAp > 0.0)) {
+        if (threadIdx.x == 0) {
+            st->it = it;
+            st->broken = 1;
+        }
+        return;
+    }
+    const double alpha = st->rr[it & 1] / pAp;
+    double rr = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        x[i] += alpha * p[i];
+        const double v = r[i] - alpha * Ap[i];
+        r[i] = v;
+        rr += v * v;
+    }
+    put_partial(rr, part, s);
+}
+
+// x -= (sum of m x) / msum, also into out (may be null)
+__global__ __launch_bounds__(256) void cg_mean_kernel(int64_t n, const double *__restrict__ mpart, int nmpart, double msum,
+                                                      double *__restrict__ x, double *__restrict__ out) {
+    __shared__ double s[256];
+    const double c = -sum_partials(mpart, nmpart, s) / msum;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const double v = x[i] + c;
+        x[i] = v;
+        if (out) out[i] = v;
+    }
 }
 
 // Local-density exchange-correlation of the unpolarised electron gas at
@@ -271,31 +391,39 @@ hipError_t launch_fe_blocks(int64_t nnzb, int nfs, const int32_t *bcol, const in
     return hipGetLastError();
 }
 
-hipError_t launch_fe_spmv(int64_t nv, int nfs, const int64_t *brow_ptr, const int32_t *bcol, const double *K,
-                          const double *x, double *y, hipStream_t st) {
-    if (nv * nfs <= 0) return hipSuccess;
-    fe_spmv_kernel<<<blocks_for(nv * nfs), 256, 0, st>>>(nv, nfs, brow_ptr, bcol, K, x, y);
-    return hipGetLastError();
-}
-
 hipError_t launch_dot(int64_t n, const double *a, const double *b, double *part, double *out, hipStream_t st) {
     dot_partial_kernel<<<kDotBlocks, 256, 0, st>>>(n, a, b, part);
     dot_final_kernel<<<1, 256, 0, st>>>(kDotBlocks, part, out);
     return hipGetLastError();
 }
 
-int dot_partial_slots() { return kDotBlocks; }
-
-hipError_t launch_axpby(int64_t n, double a, const double *x, double b, double *y, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    axpby_kernel<<<blocks_for(n), 256, 0, st>>>(n, a, x, b, y);
+hipError_t launch_dot_partials(int64_t n, const double *a, const double *b, double *part, hipStream_t st) {
+    dot_partial_kernel<<<kDotBlocks, 256, 0, st>>>(n, a, b, part);
     return hipGetLastError();
 }
 
-hipError_t launch_scaled_diff(int64_t n, double a, const double *x, double c, const double *z, double *y,
-                              hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    scaled_diff_kernel<<<blocks_for(n), 256, 0, st>>>(n, a, x, c, z, y);
+int dot_partial_slots() { return kDotBlocks; }
+
+int64_t cg_partial_slots(int64_t nv) { return (nv + 3) / 4 + kDotBlocks; }
+
+hipError_t launch_cg_start(const CgSolve &c, const double *b, const double *m, const double *bpart, double msum,
+                           hipStream_t st) {
+    cg_start_kernel<<<kDotBlocks, 256, 0, st>>>(c.nv * c.nfs, b, m, bpart, kDotBlocks, msum, c.r, c.x, c.part, c.state);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_iteration(const CgSolve &c, int it, double tol, bool check, hipStream_t st) {
+    const int nb = (int)((c.nv + 3) / 4);
+    double *apart = c.part + kDotBlocks, *p0 = it & 1 ? c.p0 : c.p1, *p1 = it & 1 ? c.p1 : c.p0;
+    cg_spmv_kernel<<<nb, 256, 0, st>>>(c.nv, c.nfs, it, tol, check, c.brow_ptr, c.bcol, c.K, c.r, p0, p1, c.Ap, c.part,
+                                       kDotBlocks, apart, c.state);
+    if (!check)
+        cg_update_kernel<<<kDotBlocks, 256, 0, st>>>(c.nv * c.nfs, it, p1, c.Ap, c.x, c.r, apart, nb, c.part, c.state);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_mean(const CgSolve &c, const double *mpart, double msum, double *out, hipStream_t st) {
+    cg_mean_kernel<<<kDotBlocks, 256, 0, st>>>(c.nv * c.nfs, mpart, kDotBlocks, msum, c.x, out);
     return hipGetLastError();
 }
 
