@@ -10,9 +10,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpufe.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["capi.cpp", "plan.cpp", "kernels.hip", "moments.hip", "expand.hip", "gather.hip", "backward.hip", "split.hip", "aq_error.hip", "nonlocal.hip",
+SOURCES = ["capi.cpp", "plan.cpp", "kernels.hip", "moments.hip", "expand.hip", "gather.hip", "adjoint.hip", "backward.hip", "split.hip", "aq_error.hip", "nonlocal.hip",
            "bloch.hip", "scf.hip"]
-HEADERS = ["tables.hpp", "plan.hpp", "kernels.hpp", "moments.hpp", "gather.hpp", "basis.hpp", "backward.hpp", "device_common.hpp", "enrich.hpp",
+HEADERS = ["tables.hpp", "plan.hpp", "kernels.hpp", "moments.hpp", "gather.hpp", "basis.hpp", "adjoint.hpp", "backward.hpp", "device_common.hpp", "enrich.hpp",
            "aq_error.hpp", "stage.hpp", "limbs.hpp", "nonlocal.hpp", "bloch.hpp", "scf.hpp"]
 
 FLAGS = [
@@ -23,9 +23,9 @@ FLAGS = [
 ]
 
 
-# per source: the moment sums live through the evaluation of the enrichment
-# functions; constants hoisted out of the stage loop would spill them
-EXTRA = {"moments.hip": ["-mllvm", "-disable-machine-licm"]}
+# per source: the moment sums and the adjoint coefficients live through long
+# loops; constants hoisted out of these would spill them
+EXTRA = {s: ["-mllvm", "-disable-machine-licm"] for s in ("moments.hip", "adjoint.hip")}
 
 
 def _hipcc() -> str:

@@ -14,9 +14,10 @@ constexpr int kBackwardWideMaxEnr = 256;   // enriched functions of one element 
 
 hipError_t init_backward_attributes();
 size_t backward_lds_bytes(int npad, int nenr, int nfun, int nimg);
-hipError_t launch_gather_adjoint(const KParams &kp, int64_t nel, const ElemDev *elems, const int32_t *edof,
-                                 const int64_t *pt_off, const double *P, const double *kpt, double *Pt,
-                                 hipStream_t st);
+// Ps at Pt and Qs at Qt; either matrix may be null.
+hipError_t launch_gather_adjoint(const KParams &kp, int64_t nel, int max_nloc, const ElemDev *elems, const int32_t *edof,
+                                 const int64_t *pt_off, const double *P, const double *Q, const double *kpt, double *Pt,
+                                 double *Qt, hipStream_t st);
 // nl = 0: FP64 MFMA form; nl = 2 or 3: split-precision form (bf16 limbs per operand)
 hipError_t launch_backward(const KParams &kp, bool qmode, int nl, int n_items, const ItemDev *items,
                            const ElemDev *elems, const GroupDev *groups, const double *img, const int32_t *edof,

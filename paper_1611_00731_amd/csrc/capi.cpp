@@ -11,6 +11,7 @@
 
 #include "../../include/pufe.h"
 #include "aq_error.hpp"
+#include "adjoint.hpp"
 #include "backward.hpp"
 #include "bloch.hpp"
 #include "gather.hpp"
@@ -115,9 +116,17 @@ struct pufe_ctx {
     DevBuf<int64_t> d_leaf_count, d_leaf_off, d_bval_off, d_dof_off;
     DevBuf<ItemDev> d_items, d_items_split, d_items_wide;
     // adjoint
-    bool have_bw = false;
+    bool have_bw = false, have_bw_direct = false;   // the adjoint's plan; its direct kernels' items
     std::vector<ItemDev> bw_items, bw_items_wide;   // elements of <= 80 functions, and the rest
     size_t bw_lds = 0, bw_lds_wide = 0;
+    // FP64 adjoint in moment form: items by 4 and 8 waves, or none
+    std::vector<MomItemDev> adj_items[2];
+    size_t adj_lds[2] = {0, 0};
+    DevBuf<MomItemDev> d_adj_items[2];
+    std::vector<int4> adj_fold;
+    DevBuf<int4> d_adj_fold;
+    DevBuf<int64_t> d_adj_base, d_adj_ptr, d_adj_slots;
+    DevBuf<double> d_adj_lam, d_adj_Qt, d_adj_f;
     DevBuf<ItemDev> d_bw_items, d_bw_items_wide;
     DevBuf<int64_t> d_pt_off, d_atom_ptr, d_atom_slots;
     DevBuf<double> d_Pt, d_fP, d_fQ;
@@ -285,7 +294,7 @@ int pufe_set_problem(pufe_ctx *ctx, const double lattice[9], const int mesh[3], 
     ctx->plan = std::move(pl);
     ctx->have_problem = true;
     ctx->have_setup = false;
-    ctx->have_bw = false;
+    ctx->have_bw = ctx->have_bw_direct = false;
     ctx->n_leaves = ctx->n_qp = 0;
     ++ctx->plan_gen;
     return PUFE_OK;
@@ -712,6 +721,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
         if (ea == hipSuccess) ea = init_moment_attributes();
         if (ea == hipSuccess) ea = init_split_attributes();
         if (ea == hipSuccess) ea = init_backward_attributes();
+        if (ea == hipSuccess) ea = init_adjoint_attributes();
         if (ea == hipSuccess) ea = init_nonlocal_attributes();
         if (ea != hipSuccess) {
             (void)hipGetLastError();   // do not leave the error for the caller's next HIP call
@@ -1362,7 +1372,9 @@ int pufe_lda_xc(int64_t n, const double *d_rho, double *d_vxc, double *d_exc, vo
 // Plan the adjoint: one work item per (element, K-chunk of the forward
 // partition), the padded Ps blocks, and for each atom the list of per-item
 // group partial forces in a fixed order.
-static int plan_backward(pufe_ctx *c, hipStream_t st) {
+static int plan_adjoint_moments(pufe_ctx *c, int64_t pt_doubles, hipStream_t st);
+
+static int plan_backward(pufe_ctx *c, bool split, hipStream_t st) {
     Plan &pl = c->plan;
     int max_npad = 16, max_nfun = 1, max_nenr = 1, max_nfun_wide = 1;
     std::vector<int64_t> pt_off(pl.nel + 1, 0);
@@ -1432,6 +1444,15 @@ static int plan_backward(pufe_ctx *c, hipStream_t st) {
                 (pass == 0 ? c->bw_items : c->bw_items_wide).push_back(it);
             }
         }
+    if (!c->have_bw) {
+        CHECK_HIP(c, c->d_pt_off.upload(pt_off, st), "upload adjoint offsets");
+        CHECK_HIP(c, c->d_Pt.alloc((size_t)pt_off[pl.nel]), "alloc adjoint blocks");
+        const int rc = plan_adjoint_moments(c, pt_off[pl.nel], st);
+        if (rc != PUFE_OK) return rc;
+        c->have_bw = true;
+    }
+    // with the moment form, the direct kernels serve the split precisions only
+    if (!split && !c->adj_fold.empty()) return PUFE_OK;
     std::vector<std::vector<int64_t>> slots(c->prob.species.size());
     const int64_t nn = (int64_t)c->bw_items.size(), ntot = nn + (int64_t)c->bw_items_wide.size();
     for (int64_t idx = 0; idx < ntot; ++idx) {
@@ -1444,15 +1465,112 @@ static int plan_backward(pufe_ctx *c, hipStream_t st) {
         aslots.insert(aslots.end(), slots[A].begin(), slots[A].end());
         aptr[A + 1] = (int64_t)aslots.size();
     }
-    CHECK_HIP(c, c->d_bw_items.upload(c->bw_items, st), "upload adjoint items");
-    CHECK_HIP(c, c->d_bw_items_wide.upload(c->bw_items_wide, st), "upload adjoint items");
-    CHECK_HIP(c, c->d_pt_off.upload(pt_off, st), "upload adjoint offsets");
+    CHECK_HIP(c, c->d_bw_items.upload_list(c->bw_items, st), "upload adjoint items");
+    CHECK_HIP(c, c->d_bw_items_wide.upload_list(c->bw_items_wide, st), "upload adjoint items");
     CHECK_HIP(c, c->d_atom_ptr.upload(aptr, st), "upload atom lists");
     CHECK_HIP(c, c->d_atom_slots.upload(aslots, st), "upload atom lists");
-    CHECK_HIP(c, c->d_Pt.alloc((size_t)pt_off[pl.nel]), "alloc adjoint blocks");
     CHECK_HIP(c, c->d_fP.alloc((size_t)ntot * mg * 3), "alloc partial forces");
     CHECK_HIP(c, c->d_fQ.alloc((size_t)ntot * mg * 3), "alloc partial forces");
-    c->have_bw = true;
+    c->have_bw_direct = true;
+    return PUFE_OK;
+}
+
+// Moment form of the FP64 adjoint: all elements or none.
+static int plan_adjoint_moments(pufe_ctx *c, int64_t pt_doubles, hipStream_t st) {
+    Plan &pl = c->plan;
+    const int n = pl.kp.n, p = pl.kp.p, mg = std::max(pl.max_ngrp, 1);
+    for (int w = 0; w < 2; ++w) {
+        c->adj_items[w].clear();
+        c->adj_lds[w] = 0;
+    }
+    c->adj_fold.clear();
+    // the serendipity functions are no tensor products; on sheared cells the
+    // sums take the metric's mixed terms too
+    if (p > 2 || pl.kp.skew) return PUFE_OK;
+    std::vector<AdjStage> stages(pl.nel);
+    std::vector<double> cost(pl.nel);
+    double total = 0.0;
+    for (int64_t e = 0; e < pl.nel; ++e) {
+        const ElemDev &el = pl.elems[e];
+        int nimg = 0;
+        if (el.ngrp > 0) {
+            const GroupDev &g = pl.groups[el.grp_off + el.ngrp - 1];
+            nimg = g.img_off + g.nimg - pl.groups[el.grp_off].img_off;
+        }
+        stages[e] = adj_stage((el.nfun + 3) / 4, nimg, n, p);
+        if (stages[e].waves == 0) return PUFE_OK;
+        cost[e] = (double)(el.leaf_end - el.leaf_off) * (adj_tasks((el.nfun + 3) / 4) + 0.5 * el.ngrp + 1.0);
+        total += cost[e];
+    }
+    // four items per resident group of four waves (512), six per group of eight
+    // (256): the shortest of 2, 3, 4, 6 and 8 on elements of one and two row tiles
+    // and of eight and eleven, by 7 % and 10 % over the next coarser cut
+    const double dur[2] = {total / 2048.0, total / 1536.0};
+    std::vector<int64_t> order(pl.nel), base(pl.nel + 1, 0);
+    for (int64_t e = 0; e < pl.nel; ++e) {
+        order[e] = e;
+        const int nt = (pl.elems[e].nfun + 3) / 4;
+        base[e + 1] = base[e] + adj_doubles(nt, p);
+        for (int q = 0; 4 * q < mom_quads_b(nt); ++q) c->adj_fold.push_back(make_int4((int)e, ADJ_PAIRS, q, 0));
+        for (int t = 0; t < ((nt + 3) & ~3); ++t) c->adj_fold.push_back(make_int4((int)e, ADJ_MIXED, t, 0));
+        c->adj_fold.push_back(make_int4((int)e, ADJ_CLASSICAL, 0, 0));
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return cost[a] > cost[b]; });
+    // an element's items go to one XCD (work groups are dealt round the eight),
+    // next to each other: they read the same coefficients
+    std::vector<MomItemDev> queue[2][8];
+    double load[2][8] = {};
+    for (int64_t e : order) {
+        const ElemDev &el = pl.elems[e];
+        const AdjStage &s = stages[e];
+        const int w = s.waves == 4 ? 0 : 1;
+        c->adj_lds[w] = std::max(c->adj_lds[w], s.lds);
+        int x = 0;
+        for (int k = 1; k < 8; ++k)
+            if (load[w][k] < load[w][x]) x = k;
+        load[w][x] += cost[e];
+        const int64_t nst = (el.leaf_end - el.leaf_off) * (s.planes > 0 ? (n + s.planes - 1) / s.planes
+                                                                        : n * ((n + s.lines - 1) / s.lines));
+        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(nst, (int64_t)std::ceil(cost[e] / dur[w])));
+        for (int64_t ch = 0; ch < nch; ++ch) {
+            MomItemDev it{};
+            it.elem = (int32_t)e;
+            it.leaf_b = ch * nst / nch;
+            it.leaf_e = (ch + 1) * nst / nch;
+            it.tab = s.planes | (s.lines << 8);
+            queue[w][x].push_back(it);
+        }
+    }
+    std::vector<std::vector<int64_t>> slots(c->prob.species.size());
+    int32_t slot = 0;
+    for (int w = 0; w < 2; ++w) {
+        size_t longest = 0;
+        for (int x = 0; x < 8; ++x) longest = std::max(longest, queue[w][x].size());
+        for (size_t k = 0; k < longest; ++k)
+            for (int x = 0; x < 8; ++x)
+                if (k < queue[w][x].size()) {
+                    MomItemDev it = queue[w][x][k];
+                    it.chunk = slot;
+                    c->adj_items[w].push_back(it);
+                    const ElemDev &el = pl.elems[it.elem];
+                    for (int g = 0; g < el.ngrp; ++g)
+                        slots[pl.groups[el.grp_off + g].atom].push_back((int64_t)slot * mg + g);
+                    ++slot;
+                }
+    }
+    std::vector<int64_t> aptr(slots.size() + 1, 0), aslots;
+    for (size_t A = 0; A < slots.size(); ++A) {
+        aslots.insert(aslots.end(), slots[A].begin(), slots[A].end());
+        aptr[A + 1] = (int64_t)aslots.size();
+    }
+    for (int w = 0; w < 2; ++w) CHECK_HIP(c, c->d_adj_items[w].upload_list(c->adj_items[w], st), "upload adjoint items");
+    CHECK_HIP(c, c->d_adj_fold.upload(c->adj_fold, st), "upload adjoint list");
+    CHECK_HIP(c, c->d_adj_base.upload(base, st), "upload adjoint offsets");
+    CHECK_HIP(c, c->d_adj_ptr.upload(aptr, st), "upload atom lists");
+    CHECK_HIP(c, c->d_adj_slots.upload(aslots, st), "upload atom lists");
+    CHECK_HIP(c, c->d_adj_lam.alloc((size_t)base[pl.nel]), "alloc adjoint coefficients");
+    CHECK_HIP(c, c->d_adj_Qt.alloc((size_t)pt_doubles), "alloc adjoint blocks");
+    CHECK_HIP(c, c->d_adj_f.alloc((size_t)slot * mg * 3), "alloc partial forces");
     return PUFE_OK;
 }
 
@@ -1470,8 +1588,8 @@ int pufe_assemble_backward(pufe_ctx *ctx, const double *d_V, const double kpt[3]
         return fail(ctx, PUFE_ERR_UNSUPPORTED, "the adjoint of the Bloch-periodic enrichment is not supported");
     hipStream_t st = (hipStream_t)stream;
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
-    if (!ctx->have_bw) {
-        int rc = plan_backward(ctx, st);
+    if (!ctx->have_bw || ((nl != 0 || ctx->adj_fold.empty()) && !ctx->have_bw_direct)) {
+        int rc = plan_backward(ctx, nl != 0, st);
         if (rc != PUFE_OK) return rc;
     }
     const Plan &pl = ctx->plan;
@@ -1483,10 +1601,32 @@ int pufe_assemble_backward(pufe_ctx *ctx, const double *d_V, const double kpt[3]
     TimedRegion tr(ctx, 2, st);
     const int mg = std::max(pl.max_ngrp, 1);
     const int nit = (int)ctx->bw_items.size();
+    if (nl == 0 && !ctx->adj_fold.empty()) {   // P and Q in one pass
+        if (d_P || d_Q) {
+            CHECK_HIP(ctx, launch_gather_adjoint(pl.kp, pl.nel, pl.max_nloc, ctx->d_elems.p, ctx->d_edof.p,
+                                                 ctx->d_pt_off.p, (const double *)d_P, (const double *)d_Q, kpt,
+                                                 ctx->d_Pt.p, ctx->d_adj_Qt.p, st), "gather P and Q");
+            CHECK_HIP(ctx, launch_adjoint_fold(ctx->d_self.p, ctx->d_adj_fold.p, (int)ctx->adj_fold.size(),
+                                               ctx->d_pt_off.p, d_P ? ctx->d_Pt.p : nullptr,
+                                               d_Q ? ctx->d_adj_Qt.p : nullptr, ctx->d_adj_base.p, ctx->d_adj_lam.p, st),
+                      "adjoint coefficients");
+            for (int w = 1; w >= 0; --w)
+                CHECK_HIP(ctx, launch_adjoint_moments(w ? 8 : 4, ctx->d_self.p, ctx->d_adj_items[w].p,
+                                                      (int)ctx->adj_items[w].size(), ctx->d_adj_base.p,
+                                                      ctx->d_adj_lam.p, d_V, d_P ? d_dLdV : nullptr, ctx->d_adj_f.p, mg,
+                                                      ctx->adj_lds[w], st), "adjoint");
+        }
+        if (!d_P && d_dLdV) CHECK_HIP(ctx, launch_fill_zero(d_dLdV, ctx->n_qp, false, st), "zero dLdV");
+        if (d_dLdR)
+            CHECK_HIP(ctx, launch_force_reduce((int)ctx->prob.species.size(), ctx->d_adj_ptr.p, ctx->d_adj_slots.p,
+                                               d_P || d_Q ? ctx->d_adj_f.p : nullptr, nullptr, d_dLdR, st),
+                      "force reduction");
+        return PUFE_OK;
+    }
     const size_t wide_slots = (size_t)nit * mg * 3;   // the wide items' partial forces follow the others
     if (d_P) {
-        CHECK_HIP(ctx, launch_gather_adjoint(pl.kp, pl.nel, ctx->d_elems.p, ctx->d_edof.p, ctx->d_pt_off.p,
-                                             (const double *)d_P, kpt, ctx->d_Pt.p, st), "gather P");
+        CHECK_HIP(ctx, launch_gather_adjoint(pl.kp, pl.nel, pl.max_nloc, ctx->d_elems.p, ctx->d_edof.p, ctx->d_pt_off.p,
+                                             (const double *)d_P, nullptr, kpt, ctx->d_Pt.p, nullptr, st), "gather P");
         CHECK_HIP(ctx, launch_backward(pl.kp, false, nl, nit, ctx->d_bw_items.p, ctx->d_elems.p, ctx->d_groups.p,
                                        ctx->d_img.p, ctx->d_edof.p, ctx->d_leaves.p, d_V, ctx->d_pt_off.p,
                                        ctx->d_Pt.p, d_dLdV, ctx->d_fP.p, mg, ctx->bw_lds, st), "adjoint (P)");
@@ -1498,8 +1638,8 @@ int pufe_assemble_backward(pufe_ctx *ctx, const double *d_V, const double kpt[3]
         CHECK_HIP(ctx, launch_fill_zero(d_dLdV, ctx->n_qp, false, st), "zero dLdV");
     }
     if (d_Q) {
-        CHECK_HIP(ctx, launch_gather_adjoint(pl.kp, pl.nel, ctx->d_elems.p, ctx->d_edof.p, ctx->d_pt_off.p,
-                                             (const double *)d_Q, kpt, ctx->d_Pt.p, st), "gather Q");
+        CHECK_HIP(ctx, launch_gather_adjoint(pl.kp, pl.nel, pl.max_nloc, ctx->d_elems.p, ctx->d_edof.p, ctx->d_pt_off.p,
+                                             nullptr, (const double *)d_Q, kpt, nullptr, ctx->d_Pt.p, st), "gather Q");
         CHECK_HIP(ctx, launch_backward(pl.kp, true, nl, nit, ctx->d_bw_items.p, ctx->d_elems.p, ctx->d_groups.p,
                                        ctx->d_img.p, ctx->d_edof.p, ctx->d_leaves.p, d_V, ctx->d_pt_off.p,
                                        ctx->d_Pt.p, nullptr, ctx->d_fQ.p, mg, ctx->bw_lds, st), "adjoint (Q)");
@@ -1617,7 +1757,7 @@ static int upload_items(pufe_ctx *ctx, hipStream_t st) {
         int rc = upload_moments(ctx, st);
         if (rc != PUFE_OK) return rc;
     }
-    ctx->have_bw = false;
+    ctx->have_bw = ctx->have_bw_direct = false;
     ctx->have_poisson = false;
     return upload_nonlocal(ctx, st);
 }
