@@ -135,12 +135,13 @@ struct pufe_ctx {
     std::vector<int32_t> nl_elems;
     int64_t nl_doubles = 0;
     size_t nl_lds = 0;
+    int nl_planes = 0;              // planes per stage of the projectors' moment form, 0: direct
     DevBuf<NlItemDev> d_nl_items;
     DevBuf<PGroupDev> d_pgroups;
     DevBuf<double> d_Fp, d_pfun_h;
     DevBuf<int64_t> d_dof_el_off;
     DevBuf<int2> d_dof_el;
-    DevBuf<int32_t> d_nl_elems, d_nl_blocks;
+    DevBuf<int32_t> d_nl_elems;
     DevBuf<double2> d_nlf;
     // Bloch-periodic enrichment: image shifts and kinds, the per-k image
     // weights, the partner table of the enriched entries
@@ -664,12 +665,23 @@ static void plan_items(pufe_ctx *c, double target_items, int block_tiles) {
     c->nl_elems.clear();
     c->nl_doubles = 0;
     int max_npad = 16, max_leaves = 1;
+    // moment form on tensor-product elements whose rows all fit in LDS
+    size_t mom_lds = 0;
+    c->nl_planes = c->plan.kp.p <= 2 ? nl_moment_planes(c->plan.kp.n) : 0;
+    if (c->nl_planes > 0) {
+        for (const ElemDev &el : c->plan.elems)
+            if (el.npg > 0)
+                mom_lds = std::max(mom_lds, nl_moment_lds(el.nfun, el.ncol, c->plan.max_img, c->plan.kp.n, c->nl_planes));
+        if (mom_lds > kMaxDynLds) c->nl_planes = 0;
+    }
     for (int64_t e = 0; e < c->plan.nel; ++e) {
         ElemDev &el = c->plan.elems[e];
         el.pf_nchunk = 0;
         el.pf_base = 0;
         if (el.npg == 0) continue;
-        const int T = (el.nloc + 15) / 16, TC = (el.ncol + 15) / 16, RB = std::max(1, 16 / TC);
+        const int T = (el.nloc + 15) / 16, TC = (el.ncol + 15) / 16;
+        const int rows = c->nl_planes > 0 ? nl_moment_tasks(el.nfun, el.ncol) : T;
+        const int RB = c->nl_planes > 0 ? kNlMomentTasks : std::max(1, 16 / TC);
         const int64_t nleaf = el.leaf_end - el.leaf_off, nch = el.nchunk;
         el.pf_nchunk = (int32_t)nch;
         el.pf_base = c->nl_doubles;
@@ -677,12 +689,12 @@ static void plan_items(pufe_ctx *c, double target_items, int block_tiles) {
         c->nl_elems.push_back((int32_t)e);
         max_npad = std::max(max_npad, 16 * T);
         for (int64_t ch = 0; ch < nch; ++ch)
-            for (int R0 = 0; R0 < T; R0 += RB) {
+            for (int R0 = 0; R0 < rows; R0 += RB) {
                 NlItemDev it{};
                 it.elem = (int32_t)e;
                 it.chunk = (int32_t)ch;
                 it.R0 = R0;
-                it.nR = std::min(RB, T - R0);
+                it.nR = std::min(RB, rows - R0);
                 it.leaf_b = el.leaf_off + ch * nleaf / nch;
                 it.leaf_e = el.leaf_off + (ch + 1) * nleaf / nch;
                 max_leaves = std::max(max_leaves, (int)(it.leaf_e - it.leaf_b));
@@ -690,6 +702,22 @@ static void plan_items(pufe_ctx *c, double target_items, int block_tiles) {
             }
     }
     c->nl_lds = nl_lds_bytes(max_npad, std::max(c->plan.max_ncol, 1), nfun, c->plan.max_img, max_leaves, n3);
+    // what the direct form could not hold stays refused
+    if (c->nl_planes > 0 && c->nl_lds <= kMaxDynLds) c->nl_lds = mom_lds;
+}
+
+// Projector coefficients of every element a projector reaches.
+static hipError_t run_projectors(pufe_ctx *c, const KParams &kp, hipStream_t st) {
+    const int n = (int)c->nl_items.size();
+    hipError_t e;
+    if (c->nl_planes > 0)
+        e = launch_nl_moments(kp, n, c->d_nl_items.p, c->d_elems.p, c->d_groups.p, c->d_img.p, c->d_edof.p, c->d_leaves.p,
+                              c->d_pgroups.p, c->nl_planes, c->d_Fp.p, c->nl_lds, st);
+    else
+        e = launch_nl_f(c->plan.max_l, kp, n, c->d_nl_items.p, c->d_elems.p, c->d_groups.p, c->d_img.p, c->d_edof.p,
+                        c->d_leaves.p, c->d_pgroups.p, c->d_Fp.p, c->nl_lds, st);
+    if (e != hipSuccess) return e;
+    return launch_nl_reduce(c->d_elems.p, c->d_nl_elems.p, (int)c->nl_elems.size(), c->d_Fp.p, st);
 }
 
 static int upload_items(pufe_ctx *ctx, hipStream_t st);
@@ -705,7 +733,6 @@ static int upload_nonlocal(pufe_ctx *ctx, hipStream_t st) {
     CHECK_HIP(ctx, ctx->d_pfun_h.upload(pl.pfun_h, st), "upload projector weights");
     CHECK_HIP(ctx, ctx->d_dof_el_off.upload(pl.dof_el_off, st), "upload DOF map");
     CHECK_HIP(ctx, ctx->d_dof_el.upload(pl.dof_el, st), "upload DOF map");
-    CHECK_HIP(ctx, ctx->d_nl_blocks.upload(pl.nl_blocks, st), "upload nonlocal blocks");
     CHECK_HIP(ctx, ctx->d_Fp.alloc((size_t)std::max<int64_t>(ctx->nl_doubles, 1)), "alloc projector coefficients");
     CHECK_HIP(ctx, ctx->d_nlf.alloc((size_t)kMaxKPerLaunch * pl.n_pfun * pl.dof_off[pl.nv]), "alloc projector sums");
     return PUFE_OK;
@@ -1081,13 +1108,7 @@ static int assemble_bloch(pufe_ctx *ctx, const double *d_V, const double *kpts, 
                 TimedRegion tn(ctx, 4, st);
                 KParams kp = pl.kp;
                 kp.wimg = ctx->d_wimg.p;
-                CHECK_HIP(ctx, launch_nl_f(pl.max_l, kp, (int)ctx->nl_items.size(), ctx->d_nl_items.p, ctx->d_elems.p,
-                                           ctx->d_groups.p, ctx->d_img.p, ctx->d_edof.p, ctx->d_leaves.p,
-                                           ctx->d_pgroups.p, ctx->d_Fp.p, ctx->nl_lds, st),
-                          "projector coefficients");
-                CHECK_HIP(ctx, launch_nl_reduce(ctx->d_elems.p, ctx->d_nl_elems.p, (int)ctx->nl_elems.size(),
-                                                ctx->d_Fp.p, st),
-                          "projector coefficient sum");
+                CHECK_HIP(ctx, run_projectors(ctx, kp, st), "projector coefficients");
             }
             TimedRegion tr(ctx, 1, st);
             char *H = (char *)d_H + (size_t)(k0 + k) * per * esz;
@@ -1096,21 +1117,16 @@ static int assemble_bloch(pufe_ctx *ctx, const double *d_V, const double *kpts, 
             std::memset(&one, 0, sizeof one);
             one.nk = 1;
             for (int d = 0; d < 3; ++d) one.kap[0][d] = kps.kap[k][d];
-            CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), ctx->d_partial.p, H, S, one,
-                                         out_dtype, true, st),
-                      "assembly");
-            if (with_nl) {
-                // the separable term of this k-point into its H
-                const int64_t ndof = pl.dof_off[pl.nv];
+            const int64_t ndof = pl.dof_off[pl.nv];
+            if (with_nl)
                 CHECK_HIP(ctx, launch_nl_gather(pl.kp, ctx->d_elems.p, ctx->d_pgroups.p, ctx->d_edof.p, ctx->d_bpart.p,
                                                 ctx->d_dof_el_off.p, ctx->d_dof_el.p, ctx->d_Fp.p, one, pl.n_pfun,
                                                 ndof, ctx->d_nlf.p, st),
                           "projector sums");
-                CHECK_HIP(ctx, launch_nl_update((int)pl.nl_blocks.size(), ctx->d_nl_blocks.p, ctx->d_brow.p,
-                                                ctx->d_bcol.p, ctx->d_bval_off.p, ctx->d_dof_off.p, ctx->d_nlf.p,
-                                                ctx->d_pfun_h.p, pl.n_pfun, ndof, 1, out_dtype, H, pl.nnz, st),
-                          "nonlocal update");
-            }
+            CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), ctx->d_partial.p, H, S, one,
+                                         out_dtype, true, with_nl ? ctx->d_nlf.p : nullptr, ctx->d_pfun_h.p, pl.n_pfun,
+                                         ndof, st),
+                      "assembly");
         }
     }
     return PUFE_OK;
@@ -1128,12 +1144,7 @@ static int assemble_impl(pufe_ctx *ctx, const double *d_V, const double *kpts, i
     if (with_nl) {
         // projector coefficients of every element a projector image reaches
         TimedRegion tn(ctx, timed ? 4 : -1, st);
-        CHECK_HIP(ctx, launch_nl_f(pl.max_l, pl.kp, (int)ctx->nl_items.size(), ctx->d_nl_items.p, ctx->d_elems.p,
-                                   ctx->d_groups.p, ctx->d_img.p, ctx->d_edof.p, ctx->d_leaves.p, ctx->d_pgroups.p,
-                                   ctx->d_Fp.p, ctx->nl_lds, st),
-                  "projector coefficients");
-        CHECK_HIP(ctx, launch_nl_reduce(ctx->d_elems.p, ctx->d_nl_elems.p, (int)ctx->nl_elems.size(), ctx->d_Fp.p, st),
-                  "projector coefficient sum");
+        CHECK_HIP(ctx, run_projectors(ctx, pl.kp, st), "projector coefficients");
     }
     TimedRegion tr(ctx, timed ? 1 : -1, st);
     const int64_t per = out_dtype == PUFE_OUT_F64_GAMMA ? pl.nnz : 2 * pl.nnz;
@@ -1147,21 +1158,15 @@ static int assemble_impl(pufe_ctx *ctx, const double *d_V, const double *kpts, i
             for (int d = 0; d < 3; ++d) kps.kap[k][d] = kpts[3 * (k0 + k) + d];
         char *H = (char *)d_H + (size_t)k0 * per * esz;
         char *S = d_S ? (char *)d_S + (size_t)k0 * per * esz : nullptr;
-        CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), partial, H, S, kps, out_dtype,
-                                     false, st),
-                  "assembly");
-        if (with_nl) {
-            // the separable term of these k-points into H
-            const int64_t ndof = pl.dof_off[pl.nv];
+        const int64_t ndof = pl.dof_off[pl.nv];
+        if (with_nl)
             CHECK_HIP(ctx, launch_nl_gather(pl.kp, ctx->d_elems.p, ctx->d_pgroups.p, ctx->d_edof.p, nullptr,
                                             ctx->d_dof_el_off.p, ctx->d_dof_el.p, ctx->d_Fp.p, kps, pl.n_pfun, ndof,
                                             ctx->d_nlf.p, st),
                       "projector sums");
-            CHECK_HIP(ctx, launch_nl_update((int)pl.nl_blocks.size(), ctx->d_nl_blocks.p, ctx->d_brow.p, ctx->d_bcol.p,
-                                            ctx->d_bval_off.p, ctx->d_dof_off.p, ctx->d_nlf.p, ctx->d_pfun_h.p,
-                                            pl.n_pfun, ndof, kps.nk, out_dtype, H, pl.nnz, st),
-                      "nonlocal update");
-        }
+        CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), partial, H, S, kps, out_dtype,
+                                     false, with_nl ? ctx->d_nlf.p : nullptr, ctx->d_pfun_h.p, pl.n_pfun, ndof, st),
+                  "assembly");
     }
     return PUFE_OK;
 }
@@ -2255,7 +2260,7 @@ int pufe_batch_assemble(pufe_batch *b, const double *const *d_V, const double *k
             e = launch_chunk_reduce_batch(b->d_ctxs.p, b->d_reduce.p, (int)b->reduce.size(), b->cap);
         if (e == hipSuccess)
             e = launch_gather(b->d_ctxs.p, b->d_blocks.p, (int)b->blocks.size(), nullptr, nullptr, nullptr, kps, out_dtype,
-                              false, b->cap);
+                              false, nullptr, nullptr, 0, 0, b->cap);
         hipGraph_t g = nullptr;
         hipError_t e2 = hipStreamEndCapture(b->cap, &g);
         if (e != hipSuccess) {

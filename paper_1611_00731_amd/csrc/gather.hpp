@@ -12,11 +12,14 @@ constexpr int kMaxBlockElems = 8;   // elements that hold both vertices of a blo
 
 // H and S of the k-points kps: every stored block of the listed problems
 // written once.  list: (block (v, w) with v <= w, block (w, v), its first
-// contribution, problem | contributions << 27), contributions element << 6 |
-// corner of v << 3 | corner of w in element order.  partial, H, S: the buffers
+// contribution, problem | projectors couple the block << 26 | contributions << 27),
+// contributions element << 6 | corner of v << 3 | corner of w in element order.  partial, H, S: the buffers
 // of a single-problem call (partial null: each problem's own, also H and S);
-// bloch: the element matrices hold real and imaginary rows.
+// bloch: the element matrices hold real and imaginary rows.  f (null: none; else
+// of a single problem): the projector sums f[(k n_pfun + J) n_dof + i] with the
+// strengths pfun_h, whose term H_ij += sum_J h_J f_J^i conj(f_J^j) the blocks take.
 hipError_t launch_gather(const CtxDev *ctxs, const int4 *list, int n, const double *partial, void *H, void *S,
-                         const KPoints &kps, int out_dtype, bool bloch, hipStream_t st);
+                         const KPoints &kps, int out_dtype, bool bloch, const double2 *f, const double *pfun_h, int n_pfun,
+                         int64_t n_dof, hipStream_t st);
 
 }  // namespace pufe

@@ -13,10 +13,12 @@
 // F_e is per k-point and the gather takes conj(phi) = real - i imaginary, with
 // the boundary phase on the classical FE rows only; the
 // phases and the sum over the elements of a DOF are a gather per (J, DOF)
-// (nl_gather_kernel), and the low-rank update runs per BSR block that a
-// projector image couples (nl_update_kernel).  No atomics; fixed order.
+// (nl_gather_kernel), and the assembly adds the low-rank term to the blocks that
+// a projector image couples (gather.hip).  No atomics; fixed order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "basis.hpp"
 #include "device_common.hpp"
@@ -188,6 +190,280 @@ __global__ __launch_bounds__(kNlThreads) void nl_f_kernel(
     }
 }
 
+// Projector coefficients in moment form (tensor-product elements): an enriched
+// row is M_c Psi_f, so its eight corners share the sums of Psi_f v_c over M_0
+// and M_1 along each direction, and a classical row is a product of three
+// Lagrange factors.  The sum over a line of points runs on v_mfma_f64_4x4x4
+// (functions x projector values at 4 points), those over lines and planes on
+// the accumulators: 2 matrix operations per pair and 4 points for eight rows,
+// where nl_f_kernel evaluates every row at every point.  What is left to bound
+// it is the evaluation of the functions.  Measured on 512 elements of one and
+// two row tiles with 20 projector functions: 590 us there, 111 us here.
+// An item's tasks R0 .. R0 + nR - 1 (quads of tile pairs, then groups of four
+// projector tiles for the classical rows), at most four per wave; stages are
+// planes of a leaf.
+// 1D tables of a leaf, with the rule's weights: hats and Lagrange factors, z
+// with the leaf's volume factor too.
+struct NlTab {
+    int h, l, size;   // h + (2 d + c) n, l + (3 d + i) n
+    __host__ __device__ explicit NlTab(int n) : h(0), l(6 * n), size(15 * n) {}
+};
+
+__host__ __device__ inline int nl_stride(int points) { return ((points + 15) / 16) * 16 + 4; }
+
+struct NlMomLds {
+    static __host__ __device__ size_t bytes(int nfun, int ncol, int nimg, int n, int planes) {
+        return sizeof(double) * ((size_t)(nfun + ncol) * nl_stride(planes * n * n) + NlTab(n).size + 2 * kMaxGauss +
+                                 3 * (size_t)nimg) +
+               sizeof(GroupDev) * kMaxGroups + sizeof(PGroupDev) * kMaxPGroups + sizeof(int16_t) * 8 * kMaxFun + 64;
+    }
+};
+
+template <int L>
+__device__ __forceinline__ void nl_group_value(const GroupDev &G, const double *__restrict__ img,
+                                               const double *__restrict__ spl, const double *__restrict__ wimg,
+                                               const double *x, double *o, int stride) {
+    constexpr int NM = 2 * L + 1;
+    const double rc2 = G.rc * G.rc, inv_rc2 = 1.0 / rc2;
+    const double *c0 = img + 3 * G.img_off;
+    double v[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) v[m] = 0.0;
+    for (int k = 0; k < G.nimg; ++k) {
+        const double rx = x[0] - c0[3 * k], ry = x[1] - c0[3 * k + 1], rz = x[2] - c0[3 * k + 2];
+        const double s = rx * rx + ry * ry + rz * rz;
+        if (s >= rc2) continue;
+        double g0, g1, g2;
+        if (G.nspl > 0) {
+            spline_radial<false>(G, spl, s, g0, g1, g2);
+        } else {
+            const double c = 1.0 - s * inv_rc2, c2 = c * c;
+            g0 = exp(-G.a * s) * c2 * c;
+        }
+        if (wimg) g0 *= wimg[G.img_off + k];
+        double S[7], dS[21];
+        solid_harmonics(L, rx, ry, rz, S, dS);
+#pragma unroll
+        for (int m = 0; m < NM; ++m) v[m] += g0 * S[m];
+    }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) o[m * stride] = v[m];
+}
+
+template <int L>
+__device__ __forceinline__ void nl_projector_value(const PGroupDev &G, const double *x, double *o, int stride) {
+    const double rx = x[0] - G.c[0], ry = x[1] - G.c[1], rz = x[2] - G.c[2];
+    const double s = rx * rx + ry * ry + rz * rz, rc2 = G.rc * G.rc;
+    double rad = 0.0;
+    if (s < rc2) {
+        const double c = 1.0 - s / rc2;
+        rad = exp(-G.a * s) * c * c * c;
+    }
+    double S[7], dS[21];
+    solid_harmonics(L, rx, ry, rz, S, dS);
+#pragma unroll
+    for (int m = 0; m <= 2 * L; ++m) o[m * stride] = rad * S[m];
+}
+
+template <int P>
+__global__ __launch_bounds__(kNlThreads) void nl_moment_kernel(
+    const KParams kp, const NlItemDev *__restrict__ items, const ElemDev *__restrict__ elems,
+    const GroupDev *__restrict__ groups, const double *__restrict__ img, const int32_t *__restrict__ edof,
+    const uint32_t *__restrict__ leaves, const PGroupDev *__restrict__ pgroups, int planes, double *__restrict__ Fp) {
+    constexpr int NT = kNlThreads, NU = kNlMomentTasks / 4, KS = kMaxGauss / 4, NA = P + 1;
+    extern __shared__ __attribute__((aligned(16))) double smem[];
+    const NlItemDev it = items[blockIdx.x];
+    const ElemDev &el = elems[it.elem];
+    const int n = kp.n, n2 = n * n, nfun = el.nfun, ncol = el.ncol, ngrp = el.ngrp, npg = el.npg, nfe = el.nfe;
+    const int img0 = ngrp > 0 ? groups[el.grp_off].img_off : 0;
+    const int nimg = ngrp > 0 ? groups[el.grp_off + ngrp - 1].img_off + groups[el.grp_off + ngrp - 1].nimg - img0 : 0;
+    const int RS = nl_stride(planes * n2);
+    const NlTab tb(n);
+    double *sR = smem;                       // [nfun + ncol][RS]
+    double *sT = sR + (nfun + ncol) * RS, *sGx = sT + tb.size, *sGw = sGx + kMaxGauss, *sImg = sGw + kMaxGauss;
+    GroupDev *sG = (GroupDev *)(sImg + 3 * nimg);
+    PGroupDev *sPG = (PGroupDev *)(sG + kMaxGroups);
+    int16_t *sPos = (int16_t *)(sPG + kMaxPGroups);   // local index of (corner, function)
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int g = tid; g < ngrp; g += NT) {
+        GroupDev G = groups[el.grp_off + g];
+        G.img_off -= img0;
+        sG[g] = G;
+    }
+    for (int g = tid; g < npg; g += NT) sPG[g] = pgroups[el.pg_off + g];
+    for (int k = tid; k < 3 * nimg; k += NT) sImg[k] = img[3 * (size_t)img0 + k];
+    for (int k = tid; k < 8 * kMaxFun; k += NT) sPos[k] = -1;
+    if (tid < n) {
+        sGx[tid] = kp.gx[tid];
+        sGw[tid] = kp.gw[tid];
+    }
+    double org[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) org[c] = el.ijk[0] * kp.E[c] + el.ijk[1] * kp.E[3 + c] + el.ijk[2] * kp.E[6 + c];
+    __syncthreads();
+    for (int k = tid; k < el.nloc - nfe; k += NT) {
+        const int pk = edof[el.edof_off + k];
+        sPos[(pk & 7) * kMaxFun + ((pk >> 3) & 255)] = (int16_t)k;
+    }
+    const int nt = (nfun + 3) / 4, ntc = (ncol + 3) / 4, npairs = nt * ntc, nquad = (npairs + 3) / 4;
+    const int blk = (lane >> 2) & 3, i4 = lane & 3, k4 = lane >> 4;
+    int ra[NU], rb[NU];   // this lane's rows of the table; the classical tasks have none on the left
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int t = it.R0 + wave + 4 * u;
+        const int pr = min(4 * t + blk, max(npairs - 1, 0)), I = ntc > 0 ? pr / ntc : 0, J = pr - I * ntc;
+        ra[u] = min(4 * I + i4, max(nfun - 1, 0)) * RS;
+        const int col = t < nquad ? 4 * J + i4 : 4 * (4 * (t - nquad) + blk) + i4;
+        rb[u] = (nfun + min(col, ncol - 1)) * RS;
+    }
+    double Z[NU][9];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) Z[u][k] = 0.0;
+    const int spl = (n + planes - 1) / planes, nst = (int)(it.leaf_e - it.leaf_b) * spl, steps = (n + 3) / 4;
+#pragma unroll 1
+    for (int st = 0; st < nst; ++st) {
+        const int lf = st / spl, ss = st - lf * spl, z0 = ss * planes, npl = min(planes, n - z0), npts = npl * n2;
+        const uint32_t code = leaves[it.leaf_b + lf];
+        const double h = 1.0 / (double)(1u << (code >> 27));
+        const double c0 = 2.0 * (code & 511u) + 1.0, c1 = 2.0 * ((code >> 9) & 511u) + 1.0,
+                     c2 = 2.0 * ((code >> 18) & 511u) + 1.0;
+        if (ss == 0)
+            for (int e = tid; e < tb.size; e += NT) {
+                const bool hat = e < tb.l;
+                const int j = hat ? e : e - tb.l, r = j / n, i = j - r * n, d = hat ? r >> 1 : r / 3;
+                const int c = hat ? r & 1 : r - 3 * d;
+                const double t = -1.0 + ((d == 0 ? c0 : (d == 1 ? c1 : c2)) + sGx[i]) * h;
+                double v = c ? 0.5 * (1.0 + t) : 0.5 * (1.0 - t);
+                if (!hat) {
+                    double L[3] = {0.0, 0.0, 0.0}, D[3];
+                    lagrange_1d(P, t, L, D);
+                    v = c == 0 ? L[0] : (c == 1 ? L[1] : L[2]);
+                }
+                sT[e] = v * sGw[i] * (d == 2 ? h * h * h * kp.jac : 1.0);
+            }
+        for (int u = tid; u < (ngrp + npg) * npts; u += NT) {
+            const int g = u / npts, q = u - g * npts, z = q / n2, yx = q - z * n2, y = yx / n;
+            const double xi[3] = {-1.0 + (c0 + sGx[yx - y * n]) * h, -1.0 + (c1 + sGx[y]) * h, -1.0 + (c2 + sGx[z0 + z]) * h};
+            double x[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                x[c] = org[c] + 0.5 * (xi[0] + 1.0) * kp.E[c] + 0.5 * (xi[1] + 1.0) * kp.E[3 + c] +
+                       0.5 * (xi[2] + 1.0) * kp.E[6 + c];
+            if (g < ngrp) {
+                const GroupDev &G = sG[g];
+                double *o = sR + G.fbase * RS + q;
+                const double *wi = kp.wimg ? kp.wimg + img0 : nullptr;
+                switch (G.l) {
+                    case 0: nl_group_value<0>(G, sImg, kp.spl, wi, x, o, RS); break;
+                    case 1: nl_group_value<1>(G, sImg, kp.spl, wi, x, o, RS); break;
+                    case 2: nl_group_value<2>(G, sImg, kp.spl, wi, x, o, RS); break;
+                    default: nl_group_value<3>(G, sImg, kp.spl, wi, x, o, RS); break;
+                }
+            } else {
+                const PGroupDev &G = sPG[g - ngrp];
+                double *o = sR + (nfun + G.col0) * RS + q;
+                switch (G.l) {
+                    case 0: nl_projector_value<0>(G, x, o, RS); break;
+                    case 1: nl_projector_value<1>(G, x, o, RS); break;
+                    case 2: nl_projector_value<2>(G, x, o, RS); break;
+                    default: nl_projector_value<3>(G, x, o, RS); break;
+                }
+            }
+        }
+        __syncthreads();
+        // this lane's x weights: hats on the right, a Lagrange factor on the left
+        int xo[KS];
+        double w0[KS], w1[KS], wl[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int x = 4 * s + k4;
+            xo[s] = min(x, n - 1);
+            w0[s] = x < n ? sT[tb.h + x] : 0.0;
+            w1[s] = x < n ? sT[tb.h + n + x] : 0.0;
+            wl[s] = x < n && i4 < NA ? sT[tb.l + i4 * n + x] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int t = wave + 4 * u;
+            if (t >= it.nR) continue;
+            const bool quad = it.R0 + t < nquad;
+#pragma unroll 1
+            for (int z = 0; z < npl; ++z) {
+                double Y[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+                for (int y = 0; y < n; ++y) {
+                    const int o = (z * n + y) * n;
+                    double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) {
+                        if (s >= steps) continue;
+                        const double b = sR[rb[u] + o + xo[s]];
+                        if (quad) {
+                            const double a = sR[ra[u] + o + xo[s]];
+                            t0 = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b * w0[s], t0, 0, 0, 0);
+                            t1 = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b * w1[s], t1, 0, 0, 0);
+                        } else {
+                            t0 = __builtin_amdgcn_mfma_f64_4x4x4f64(wl[s], b, t0, 0, 0, 0);
+                        }
+                    }
+                    if (quad) {
+                        const double y0 = sT[tb.h + 2 * n + y], y1 = sT[tb.h + 3 * n + y];
+                        Y[0] += y0 * t0;
+                        Y[1] += y0 * t1;
+                        Y[2] += y1 * t0;
+                        Y[3] += y1 * t1;
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < NA; ++i) Y[i] += sT[tb.l + (3 + i) * n + y] * t0;
+                    }
+                }
+                if (quad) {
+                    const double q0 = sT[tb.h + 4 * n + z0 + z], q1 = sT[tb.h + 5 * n + z0 + z];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        Z[u][k] += q0 * Y[k];
+                        Z[u][4 + k] += q1 * Y[k];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NA; ++i) {
+                        const double q = sT[tb.l + (6 + i) * n + z0 + z];
+#pragma unroll
+                        for (int k = 0; k < NA; ++k) Z[u][NA * i + k] += q * Y[k];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // slot of this K-chunk: F[col][npad]; lane l holds function l / 16, column l % 4 of its block
+    const int npad = 16 * ((el.nloc + 15) / 16), ncp = 16 * ((ncol + 15) / 16);
+    double *dst = Fp + el.pf_base + (int64_t)it.chunk * ncp * npad;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int t = it.R0 + wave + 4 * u;
+        if (wave + 4 * u >= it.nR) continue;
+        if (t < nquad) {
+            const int pr = 4 * t + blk;
+            if (pr >= npairs) continue;
+            const int f = 4 * (pr / ntc) + k4, c = 4 * (pr % ntc) + i4;
+            if (f >= nfun || c >= ncol) continue;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {   // Z runs over z, y, x of the corner
+                const int loc = sPos[k * kMaxFun + f];
+                if (loc >= 0) dst[(size_t)c * npad + nfe + loc] = Z[u][k];
+            }
+        } else {
+            const int c = 4 * (4 * (t - nquad) + blk) + i4;
+            if (c >= ncol || k4 >= NA) continue;
+#pragma unroll
+            for (int k = 0; k < NA * NA; ++k) dst[(size_t)c * npad + k4 + NA * k] = Z[u][k];
+        }
+    }
+}
+
 // Sum of the K-chunk slots of one element's projector coefficients, in chunk
 // order, into the first slot.
 __global__ __launch_bounds__(256) void nl_reduce_kernel(const ElemDev *__restrict__ elems,
@@ -261,61 +537,34 @@ __global__ __launch_bounds__(256) void nl_gather_kernel(const KParams kp, const 
     for (int k = 0; k < kps.nk; ++k) f[((int64_t)k * n_pfun + J) * n_dof + i] = acc[k];
 }
 
-// H_ij += sum_J h_J f_J^i conj(f_J^j) over the blocks that a projector image
-// couples (one work group per block), for kps.nk k-points.
-__global__ __launch_bounds__(256) void nl_update_kernel(const int32_t *__restrict__ nl_blocks,
-                                                        const int32_t *__restrict__ brow,
-                                                        const int32_t *__restrict__ bcol,
-                                                        const int64_t *__restrict__ bval_off,
-                                                        const int64_t *__restrict__ dof_off,
-                                                        const double2 *__restrict__ f,
-                                                        const double *__restrict__ pfun_h, int n_pfun,
-                                                        int64_t n_dof, int nk, int out_dtype, void *__restrict__ H,
-                                                        int64_t nnz) {
-    const int blk = nl_blocks[blockIdx.x];
-    const int64_t v = brow[blk], w = bcol[blk];
-    const int64_t r0 = dof_off[v], c0 = dof_off[w];
-    const int bc = (int)(dof_off[w + 1] - c0);
-    const int64_t cnt = bval_off[blk + 1] - bval_off[blk];
-    for (int64_t t = threadIdx.x; t < cnt; t += blockDim.x) {
-        const int64_t i = r0 + t / bc, j = c0 + t % bc;
-        const int64_t dst = bval_off[blk] + t;
-        for (int k = 0; k < nk; ++k) {
-            const double2 *fk = f + (int64_t)k * n_pfun * n_dof;
-            double re = 0.0, im = 0.0;
-            for (int J = 0; J < n_pfun; ++J) {
-                const double2 a = fk[(int64_t)J * n_dof + i], b = fk[(int64_t)J * n_dof + j];
-                // h a conj(b)
-                re += pfun_h[J] * (a.x * b.x + a.y * b.y);
-                im += pfun_h[J] * (a.y * b.x - a.x * b.y);
-            }
-            if (out_dtype == 0) {
-                double2 *Hk = (double2 *)H + (int64_t)k * nnz;
-                double2 h = Hk[dst];
-                Hk[dst] = make_double2(h.x + re, h.y + im);
-            } else if (out_dtype == 1) {
-                float *Hk = (float *)H + 2 * (int64_t)k * nnz;
-                Hk[2 * dst] += (float)re;
-                Hk[2 * dst + 1] += (float)im;
-            } else {
-                double *Hk = (double *)H + (int64_t)k * nnz;
-                Hk[dst] += re;
-            }
-        }
-    }
-}
-
 size_t nl_lds_bytes(int npad, int ncol, int nfun, int nimg, int nleaf, int n3) {
     return NlLds::bytes(npad, 16 * ((ncol + 15) / 16), nfun, nimg, nleaf, n3);
 }
 
 hipError_t init_nonlocal_attributes() {
-    const void *ks[2] = {(const void *)nl_f_kernel<1>, (const void *)nl_f_kernel<3>};
+    const void *ks[4] = {(const void *)nl_f_kernel<1>, (const void *)nl_f_kernel<3>, (const void *)nl_moment_kernel<1>,
+                         (const void *)nl_moment_kernel<2>};
     for (const void *k : ks) {
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxDynLds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+int nl_moment_planes(int n) {
+    // stages of up to 128 points: two to five work groups on a compute unit
+    return std::max(1, std::min(n, 128 / (n * n)));
+}
+
+size_t nl_moment_lds(int nfun, int ncol, int nimg, int n, int planes) { return NlMomLds::bytes(nfun, ncol, nimg, n, planes); }
+
+hipError_t launch_nl_moments(const KParams &kp, int n_items, const NlItemDev *items, const ElemDev *elems,
+                             const GroupDev *groups, const double *img, const int32_t *edof, const uint32_t *leaves,
+                             const PGroupDev *pgroups, int planes, double *Fp, size_t lds, hipStream_t st) {
+    if (n_items == 0) return hipSuccess;
+    auto *k = kp.p == 2 ? nl_moment_kernel<2> : nl_moment_kernel<1>;
+    k<<<n_items, kNlThreads, lds, st>>>(kp, items, elems, groups, img, edof, leaves, pgroups, planes, Fp);
+    return hipGetLastError();
 }
 
 hipError_t launch_nl_f(int lmax, const KParams &kp, int n_items, const NlItemDev *items, const ElemDev *elems,
@@ -344,15 +593,6 @@ hipError_t launch_nl_gather(const KParams &kp, const ElemDev *elems, const PGrou
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(nl_gather_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, kp, elems, pgroups, edof,
                        bpart, dof_el_off, dof_el, Fp, kps, n_pfun, n_dof, f);
-    return hipGetLastError();
-}
-
-hipError_t launch_nl_update(int n_blocks, const int32_t *nl_blocks, const int32_t *brow, const int32_t *bcol,
-                            const int64_t *bval_off, const int64_t *dof_off, const double2 *f, const double *pfun_h,
-                            int n_pfun, int64_t n_dof, int nk, int out_dtype, void *H, int64_t nnz, hipStream_t st) {
-    if (n_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(nl_update_kernel, dim3(n_blocks), dim3(256), 0, st, nl_blocks, brow, bcol, bval_off, dof_off, f,
-                       pfun_h, n_pfun, n_dof, nk, out_dtype, H, nnz);
     return hipGetLastError();
 }
 

@@ -308,15 +308,11 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
     };
     std::vector<int32_t> elem_block((size_t)pl.nel * 64);   // block of every element's corner pairs
     // the blocks a projector function couples
-    pl.nl_blocks.clear();
-    for (const auto &vs : atom_vertices)
-        for (int64_t v : vs)
-            for (int64_t w : vs) {
-                auto b = pl.bcol.begin() + pl.brow_ptr[v], e = pl.bcol.begin() + pl.brow_ptr[v + 1];
-                pl.nl_blocks.push_back((int32_t)(std::lower_bound(b, e, (int32_t)w) - pl.bcol.begin()));
-            }
-    std::sort(pl.nl_blocks.begin(), pl.nl_blocks.end());
-    pl.nl_blocks.erase(std::unique(pl.nl_blocks.begin(), pl.nl_blocks.end()), pl.nl_blocks.end());
+    std::vector<char> nl_block(pl.n_pfun > 0 ? pl.bcol.size() : 0, 0);
+    if (pl.n_pfun > 0)
+        for (const auto &vs : atom_vertices)
+            for (int64_t v : vs)
+                for (int64_t w : vs) nl_block[block_index(v, w)] = 1;
 
     // ---- elements
     pl.elems.assign(pl.nel, ElemDev{});
@@ -582,7 +578,8 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         for (int64_t b = 0; b < nnzb; ++b) {
             if (!upper((int32_t)b)) continue;
             const int64_t t = mirror[b] >= 0 ? mirror[b] : block_index(pl.bcol[b], pl.brow[b]);
-            pl.blocks[start[64 - work(b)]++] = make_int4((int)b, (int)t, first[b], (first[b + 1] - first[b]) << 27);
+            const int nl = nl_block.empty() || !nl_block[b] ? 0 : kBlockProjected;
+            pl.blocks[start[64 - work(b)]++] = make_int4((int)b, (int)t, first[b], ((first[b + 1] - first[b]) << 27) | nl);
         }
     }
 

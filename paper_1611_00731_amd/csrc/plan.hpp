@@ -71,7 +71,6 @@ struct Plan {
     std::vector<int64_t> dof_el_off;  // n_dof + 1
     std::vector<int2> dof_el;         // (element, local function)
     int max_ncol = 0, max_npg = 0;
-    std::vector<int32_t> nl_blocks;   // BSR blocks coupled through a projector image
 };
 
 // Image lists keep every image within rc + this margin of an element, so the

@@ -14,6 +14,7 @@ constexpr int kMaxGauss = 12;
 constexpr int kMaxLevel = 8;
 constexpr int kMaxRowChunks = 64; // enriched-row chunks of one partial work item
 constexpr int kMaxProjCols = 64;  // projector columns reaching one element
+constexpr int kBlockProjected = 1 << 26;   // assembly list entry: projectors couple the block
 constexpr int kMaxPGroups = 32;   // projector-image groups reaching one element
 // dynamic LDS a kernel may request: the 160 KiB of a CU minus room for the
 // small static __shared__ variables some kernels also declare
