@@ -188,29 +188,30 @@ __global__ __launch_bounds__(256) void dot_final_kernel(int n, const double *__r
 // the partials of p_i . Ap.  Launch B(i): alpha, x += alpha p_i,
 // r -= alpha Ap and the partials of |r|^2.
 
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+    return v;
+}
+
 // Sum of n partials by a work group of 256, the same in every group.
 __device__ __forceinline__ double sum_partials(const double *__restrict__ part, int n, double *__restrict__ s) {
     double acc = 0.0;
+#pragma unroll 4
     for (int i = threadIdx.x; i < n; i += 256) acc += part[i];
-    s[threadIdx.x] = acc;
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = acc;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) s[threadIdx.x] += s[threadIdx.x + st];
-        __syncthreads();
-    }
-    const double v = s[0];
+    const double v = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
     return v;
 }
 
 __device__ __forceinline__ void put_partial(double v, double *__restrict__ part, double *__restrict__ s) {
-    s[threadIdx.x] = v;
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) s[threadIdx.x] += s[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+    if (threadIdx.x == 0) part[blockIdx.x] = (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 // r = 4 pi (b - nbar m), nbar = (sum of b) / msum, x = 0, partials of |r|^2.
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(256) void cg_start_kernel(int64_t n, const double *
                                                        const double *__restrict__ bpart, int nbpart, double msum,
                                                        double *__restrict__ r, double *__restrict__ x,
                                                        double *__restrict__ part, CgState *__restrict__ st) {
-    __shared__ double s[256];
+    __shared__ double s[4];
     const double nbar = sum_partials(bpart, nbpart, s) / msum;
     double rr = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
@@ -231,9 +232,19 @@ __global__ __launch_bounds__(256) void cg_start_kernel(int64_t n, const double *
     if (blockIdx.x == 0 && threadIdx.x == 0) *st = CgState{{0.0, 0.0}, 0.0, 0.0, 0, 0, 0};
 }
 
-// A(i), one wave per vertex: lane l of a group of nfs^2 holds entry (s, t) of
-// a block, groups of lanes take the row's blocks in turn.  check: only the
-// test of the tolerance (after the last iteration allowed).
+// A(i), W waves per vertex: lane l of a group of nfs^2 holds entry (s, t) of a
+// block, groups of lanes take the row's blocks in turn.  check: only the test of
+// the tolerance (after the last iteration allowed).
+// Bound by latency, the chain of row, columns, r and p, and sums (the blocks of
+// 512 vertices are 7 MB, 1.5 us).  So K r and K p are summed apart, before beta
+// is known, and where the vertices leave the chip short of waves, each takes
+// four: 11.6 us with one wave and one sum, 6.6 us now at 512 vertices of order 2.
+// The solve at 1728 vertices 2.06 ms with one wave, 1.75 with four; at 4096
+// 3.22 and 3.71.  At order 1, where a wave holds 64 blocks at once, 0.50 and
+// 0.44 ms at 180 vertices, 0.46 and 0.51 at 1728.
+static bool cg_wide(int64_t nv, int nfs) { return nv <= (nfs > 1 ? 2048 : 512); }
+
+template <int W>
 __global__ __launch_bounds__(256) void cg_spmv_kernel(int64_t nv, int nfs, int it, double tol, int check,
                                                       const int64_t *__restrict__ brow_ptr,
                                                       const int32_t *__restrict__ bcol, const double *__restrict__ K,
@@ -241,9 +252,25 @@ __global__ __launch_bounds__(256) void cg_spmv_kernel(int64_t nv, int nfs, int i
                                                       double *__restrict__ p1, double *__restrict__ Ap,
                                                       const double *__restrict__ rpart, int nrpart,
                                                       double *__restrict__ part, CgState *__restrict__ st) {
-    __shared__ double s[256];
+    constexpr int V = 4 / W, TV = 64 * W, TR = TV / 8;   // vertices of a group; threads of a vertex, of a row
+    __shared__ double s[256], sw[4];
+    const int per = nfs * nfs, G = 64 / per, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sub = threadIdx.x / TV;
+    const int64_t v = (int64_t)blockIdx.x * V + sub;
+    const int64_t k0 = v < nv ? brow_ptr[v] : 0, k1 = v < nv ? brow_ptr[v + 1] : 0;
     if (st->done || st->broken) return;
-    const double rr = sum_partials(rpart, nrpart, s);
+    const int g = lane / per, e = lane - g * per, row = e / nfs, col = e - row * nfs;
+    double kr = 0.0, kp = 0.0;
+    if (g < G) {
+#pragma unroll 8
+        for (int64_t k = k0 + (wave % W) * G + g; k < k1; k += W * G) {
+            const int64_t j = (int64_t)bcol[k] * nfs + col;
+            const double a = K[k * per + e];
+            kr += a * r[j];
+            if (it > 0) kp += a * p0[j];   // p0 is not read in the first iteration
+        }
+    }
+    const double rr = sum_partials(rpart, nrpart, sw);
     const double old = st->rr[(it + 1) & 1], r0 = it == 0 ? sqrt(rr) : st->r0, rel = it == 0 ? 0.0 : sqrt(rr) / r0;
     const bool stop = it == 0 ? !(r0 > 0.0) : rel <= tol;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -257,32 +284,27 @@ __global__ __launch_bounds__(256) void cg_spmv_kernel(int64_t nv, int nfs, int i
     }
     if (stop || check) return;
     const double beta = it == 0 ? 0.0 : rr / old;
-    const int per = nfs * nfs, G = 64 / per, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t v = (int64_t)blockIdx.x * 4 + wave;
-    const int g = lane / per, e = lane - g * per, row = e / nfs, col = e - row * nfs;
-    // p_i at index j; p0 is not read in the first iteration
-    auto dir = [&](int64_t j) { return beta == 0.0 ? r[j] : r[j] + beta * p0[j]; };
-    double acc = 0.0;
-    if (v < nv && g < G) {
-        const int64_t k1 = brow_ptr[v + 1];
-#pragma unroll 4
-        for (int64_t k = brow_ptr[v] + g; k < k1; k += G) acc += K[k * per + e] * dir((int64_t)bcol[k] * nfs + col);
-    }
-    s[threadIdx.x] = acc;
+    s[threadIdx.x] = kr + beta * kp;
     __syncthreads();
+    // row t of the vertex: TR threads over its waves, lane groups and columns
+    const int t = threadIdx.x % TV, yr = t / TR, l = t % TR, terms = W * G * nfs;
+    double y = 0.0;
+    if (yr < nfs)
+        for (int j = l; j < terms; j += TR) {
+            const int u = j / nfs, c = j - u * nfs, w = u / G, h = u - w * G;
+            y += s[sub * TV + 64 * w + h * per + yr * nfs + c];
+        }
+#pragma unroll
+    for (int m = TR / 2; m > 0; m >>= 1) y += __shfl_xor(y, m, 64);
     double pAp = 0.0;
-    if (v < nv && lane < nfs) {
-        double y = 0.0;
-        for (int h = 0; h < G; ++h)
-            for (int t = 0; t < nfs; ++t) y += s[64 * wave + h * per + lane * nfs + t];
-        const int64_t i = v * nfs + lane;
-        const double pi = dir(i);
+    if (v < nv && yr < nfs && l == 0) {
+        const int64_t i = v * nfs + yr;
+        const double pi = it == 0 ? r[i] : r[i] + beta * p0[i];
         p1[i] = pi;
         Ap[i] = y;
         pAp = pi * y;
     }
-    __syncthreads();
-    put_partial(pAp, part, s);
+    put_partial(pAp, part, sw);
 }
 
 // B(i)
@@ -290,7 +312,7 @@ __global__ __launch_bounds__(256) void cg_update_kernel(int64_t n, int it, const
                                                         const double *__restrict__ Ap, double *__restrict__ x,
                                                         double *__restrict__ r, const double *__restrict__ apart,
                                                         int napart, double *__restrict__ part, CgState *__restrict__ st) {
-    __shared__ double s[256];
+    __shared__ double s[4];
     // `broken` of an earlier launch only: a group of this one that finds
     // p.Ap <= 0 before another has started leads it to the same decision
     if (st->done || st->broken) return;
@@ -316,7 +338,7 @@ __global__ __launch_bounds__(256) void cg_update_kernel(int64_t n, int it, const
 // x -= (sum of m x) / msum, also into out (may be null)
 __global__ __launch_bounds__(256) void cg_mean_kernel(int64_t n, const double *__restrict__ mpart, int nmpart, double msum,
                                                       double *__restrict__ x, double *__restrict__ out) {
-    __shared__ double s[256];
+    __shared__ double s[4];
     const double c = -sum_partials(mpart, nmpart, s) / msum;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         const double v = x[i] + c;
@@ -404,7 +426,7 @@ hipError_t launch_dot_partials(int64_t n, const double *a, const double *b, doub
 
 int dot_partial_slots() { return kDotBlocks; }
 
-int64_t cg_partial_slots(int64_t nv) { return (nv + 3) / 4 + kDotBlocks; }
+int64_t cg_partial_slots(int64_t nv) { return nv + kDotBlocks; }
 
 hipError_t launch_cg_start(const CgSolve &c, const double *b, const double *m, const double *bpart, double msum,
                            hipStream_t st) {
@@ -413,10 +435,12 @@ hipError_t launch_cg_start(const CgSolve &c, const double *b, const double *m, c
 }
 
 hipError_t launch_cg_iteration(const CgSolve &c, int it, double tol, bool check, hipStream_t st) {
-    const int nb = (int)((c.nv + 3) / 4);
+    const bool wide = cg_wide(c.nv, c.nfs);
+    const int nb = (int)(wide ? c.nv : (c.nv + 3) / 4);
     double *apart = c.part + kDotBlocks, *p0 = it & 1 ? c.p0 : c.p1, *p1 = it & 1 ? c.p1 : c.p0;
-    cg_spmv_kernel<<<nb, 256, 0, st>>>(c.nv, c.nfs, it, tol, check, c.brow_ptr, c.bcol, c.K, c.r, p0, p1, c.Ap, c.part,
-                                       kDotBlocks, apart, c.state);
+    auto *spmv = wide ? cg_spmv_kernel<4> : cg_spmv_kernel<1>;
+    spmv<<<nb, 256, 0, st>>>(c.nv, c.nfs, it, tol, check, c.brow_ptr, c.bcol, c.K, c.r, p0, p1, c.Ap, c.part,
+                             kDotBlocks, apart, c.state);
     if (!check)
         cg_update_kernel<<<kDotBlocks, 256, 0, st>>>(c.nv * c.nfs, it, p1, c.Ap, c.x, c.r, apart, nb, c.part, c.state);
     return hipGetLastError();
