@@ -145,7 +145,7 @@ typedef struct {
     int64_t n_leaves; /* octree leaves (0 before pufe_setup) */
     int32_t max_nloc; /* largest number of functions on one element (rows of its contraction: with the
                          Bloch-periodic enrichment, real and imaginary parts counted apart) */
-    int32_t n_colors; /* element colours of the atomic-free scatter */
+    int32_t n_colors; /* classes of elements that share no vertex */
     int32_t n_atoms;
     int32_t n_fe_slots;
 } pufe_sizes;
@@ -200,7 +200,7 @@ int pufe_set_projectors(pufe_ctx *ctx, int n, const pufe_projector *proj);
  * complex and depend on the k-point, so each assembly contracts every element
  * once per k-point: each enriched function contributes a real row (images
  * weighted by cos 2 pi kappa.n) and an imaginary row (sin), the real MFMA
- * contraction gives the Gram matrix of both, and the scatter forms the
+ * contraction gives the Gram matrix of both, and the assembly forms the
  * complex element matrix conj(phi_a) phi_b from it.  The layout, the
  * quadrature rule (built from the periodic functions in the error-driven
  * mode) and the output types are those of the periodic form; the split
@@ -261,8 +261,8 @@ int pufe_get_leaves(pufe_ctx *ctx, int32_t *level, int32_t *ijk, int64_t *elem_l
 /* Assemble H and S for n_k k-points (eq. disceig3d).  d_V[n_qp] is the local
  * potential at the quadrature points; kpts[n_k*3] host, reduced.  d_H and
  * d_S hold n_k consecutive value arrays of nnz entries each, of type
- * out_dtype; d_S may be NULL (S does not depend on V).  The scatter is
- * atomic-free (element colouring) and deterministic.  Errors:
+ * out_dtype; d_S may be NULL (S does not depend on V).  Every entry is
+ * gathered from its elements and written once: deterministic, no atomics.  Errors:
  * PUFE_ERR_STATE before setup, PUFE_ERR_INVALID_ARG for a bad precision or
  * dtype, or F64_GAMMA with a non-zero k-point. */
 int pufe_assemble(pufe_ctx *ctx, const double *d_V, const double *kpts, int n_k, int precision,
@@ -271,10 +271,11 @@ int pufe_assemble(pufe_ctx *ctx, const double *d_V, const double *kpts, int n_k,
 /* Allocation-free form of pufe_assemble, for callers that cannot allocate
  * device memory during the call (code under HIP graph capture, tight serving
  * loops, harnesses that forbid it): the same arguments, kernels and results
- * as pufe_assemble, but the phase table and the K-chunk partial tiles live in
- * a fixed workspace of PUFE_NOALLOC_WORKSPACE_BYTES that the library's code
- * object brings with it (each GPU holds its own copy until the process ends;
- * its address on a device is looked up by pufe_setup).  The call allocates
+ * as pufe_assemble, but the partial tiles live in a fixed workspace of
+ * PUFE_NOALLOC_WORKSPACE_BYTES that the library's code object brings with it
+ * (each GPU holds its own copy until the process ends; its address on a device
+ * is looked up by pufe_setup), the sums in moment form behind them or, where
+ * they do not fit there, in a buffer that pufe_setup allocates.  The call allocates
  * and frees nothing and records no timing events.  Every call on one GPU
  * shares that GPU's workspace: calls that overlap on one GPU (on different
  * streams or host threads) race and give wrong results.  A problem whose
@@ -301,7 +302,9 @@ int pufe_element_matrices(pufe_ctx *ctx, int64_t elem, const double *d_V, int pr
  * precision: PUFE_PREC_FP64, or PUFE_PREC_BF16X3 / PUFE_PREC_BF16X6 for the
  * split-precision form, in which the dense product U = Pt [grad phi; phi]
  * runs on BF16 MFMAs from two or three bf16 limbs per operand with FP32 sums
- * (the rest of the adjoint stays FP64).  Elements of more than 80 local
+ * (the rest of the adjoint stays FP64).  In FP64 with tensor-product elements on
+ * orthorhombic cells, P and Q go onto the moments of the assembly and one pass
+ * over the points serves both.  Otherwise elements of more than 80 local
  * functions (or whose block of Pt, rows and enrichment Hessians do not fit in
  * LDS together) run a second FP64 kernel that streams the element's block of
  * Pt through LDS in 64 x 64 blocks; with such elements the split-precision
@@ -381,8 +384,9 @@ int pufe_tune(pufe_ctx *ctx, int precision, const char *cache_path);
  * (those pufe_tune chose, else the defaults); in FP64 the problems of one
  * stage length whose combined stage fits two work groups per CU share one
  * launch and the rest another, so up to two launches per stage length, plus
- * one for the items of elements of more than 80 functions.  Then one
- * atomic-free scatter launch per element colour covers all problems.  The
+ * one for the items of elements of more than 80 functions; the sums in moment
+ * form take a launch per work group width and points per line.  Then one
+ * launch gathers H and S of all problems.  The
  * sequence is captured once into a HIP graph and replayed;
  * a call with different pointers, k-points, precision or dtype recaptures.
  * d_V, d_H, d_S are host arrays of n device pointers (d_S may be NULL).  The
@@ -402,12 +406,13 @@ const char *pufe_batch_last_error_message(const pufe_batch *b);
 int pufe_bsr_to_dense(pufe_ctx *ctx, const void *d_bsr, int dtype, double *d_dense, void *stream);
 
 /* Kernel timing for measurement.  When enabled, every contraction and every
- * scatter phase enqueued by pufe_assemble is bracketed by HIP events on the
+ * gather of H and S enqueued by pufe_assemble is bracketed by HIP events on the
  * caller's stream.  pufe_kernel_times waits for the recorded events and
  * returns the summed milliseconds and launch counts of
- *   [0] the element contraction kernel, [1] the zero-fill + coloured scatter
- *       (with the nonlocal gather and update when projectors are set),
- *   [2] the adjoint kernel(s), [3] the sum of the K-chunk partial tiles,
+ *   [0] the element contraction kernels, [1] the gather of H and S (with the
+ *       projector sums when projectors are set),
+ *   [2] the adjoint kernel(s), [3] the sum of the K-chunks and the
+ *       element matrices from the moments,
  *   [4] the projector-coefficient kernels of the nonlocal term,
  * clearing them when reset != 0.  out_ms[5] and counts[5] are host arrays. */
 int pufe_enable_timing(pufe_ctx *ctx, int on);

@@ -111,7 +111,9 @@ struct pufe_ctx {
     DevBuf<int32_t> d_mom_tasks;
     DevBuf<int4> d_mom_reduce, d_mom_expand;
     DevBuf<double> d_mom;
-    DevBuf<CtxDev> d_self;          // this problem's tables, for the kernels that take a list of problems
+    DevBuf<CtxDev> d_self;          // this problem's tables, for the kernels that take a list of problems; [1] with
+                                    // the allocation-free entry's moment slots
+    DevBuf<double> d_mom_na;        // these slots, where its workspace has no room for them
     DevBuf<uint32_t> d_leaves;
     DevBuf<int64_t> d_leaf_count, d_leaf_off, d_bval_off, d_dof_off;
     DevBuf<ItemDev> d_items, d_items_split, d_items_wide;
@@ -217,6 +219,11 @@ static CtxDev tables_of(const pufe_ctx *c) {
     d.nnz = c->plan.nnz;
     return d;
 }
+
+// Workspace of the allocation-free entry: the partial tiles, behind the room
+// that its size limit counts for a phase table.
+static constexpr size_t kNoallocTiles = (sizeof(double2) * kMaxKPerLaunch * 27 + 255) / 256 * 256;
+static size_t noalloc_bytes(const pufe_ctx *c) { return kNoallocTiles + (size_t)c->part_slots * 512 * sizeof(double); }
 
 #define CHECK_HIP(ctx, x, where)                          \
     do {                                                  \
@@ -942,7 +949,7 @@ int pufe_query(pufe_ctx *ctx, pufe_sizes *out) {
     out->n_qp = ctx->n_qp;
     out->n_leaves = ctx->n_leaves;
     out->max_nloc = pl.max_nloc;
-    out->n_colors = (int32_t)pl.color_off.size() - 1;
+    out->n_colors = pl.n_colors;
     out->n_atoms = (int32_t)ctx->prob.species.size();
     out->n_fe_slots = pl.nfs;
     return PUFE_OK;
@@ -1005,6 +1012,7 @@ static bool general_variant(const Plan &pl) { return !pl.spl.empty() || pl.kp.p 
 // for the periodic form).
 static int run_contraction(pufe_ctx *ctx, const double *d_V, int precision, hipStream_t st, double *partial,
                            bool timed = true, const double *wimg = nullptr) {
+    const CtxDev *self = ctx->d_self.p + (partial == ctx->d_partial.p ? 0 : 1);
     const bool saved = ctx->timing;
     ctx->timing = saved && timed;
     struct Restore {
@@ -1038,10 +1046,10 @@ static int run_contraction(pufe_ctx *ctx, const double *d_V, int precision, hipS
                                            ctx->d_elems.p, ctx->d_groups.p, ctx->d_img.p, ctx->d_edof.p,
                                            ctx->d_leaves.p, d_V, partial, ctx->lds, st),
                   "contraction");
-        CHECK_HIP(ctx, launch_classical_moments(ctx->d_self.p, ctx->d_mom_items[2].p, (int)ctx->mom_items[2].size(), d_V, st),
+        CHECK_HIP(ctx, launch_classical_moments(self, ctx->d_mom_items[2].p, (int)ctx->mom_items[2].size(), d_V, st),
                   "contraction (classical moments)");
         for (int w = 1; w >= 0; --w)
-            CHECK_HIP(ctx, launch_moments(w ? 8 : 4, pl.kp.n, pl.max_l, general_variant(pl), pl.kp.skew != 0, ctx->d_self.p, ctx->d_mom_items[w].p,
+            CHECK_HIP(ctx, launch_moments(w ? 8 : 4, pl.kp.n, pl.max_l, general_variant(pl), pl.kp.skew != 0, self, ctx->d_mom_items[w].p,
                                           (int)ctx->mom_items[w].size(), ctx->d_mom_tasks.p, d_V, wimg, ctx->mom_lds[w], st),
                       "contraction (moments)");
     }
@@ -1049,9 +1057,9 @@ static int run_contraction(pufe_ctx *ctx, const double *d_V, int precision, hipS
     if (precision == PUFE_PREC_FP64) {
         CHECK_HIP(ctx, launch_chunk_reduce(ctx->d_elems.p, ctx->d_reduce_f64.p, (int)ctx->reduce_f64.size(), partial, st),
                   "K-chunk reduction");
-        CHECK_HIP(ctx, launch_moment_reduce(ctx->d_self.p, ctx->d_mom_reduce.p, (int)ctx->mom_reduce.size(), st),
+        CHECK_HIP(ctx, launch_moment_reduce(self, ctx->d_mom_reduce.p, (int)ctx->mom_reduce.size(), st),
                   "K-chunk reduction (moments)");
-        CHECK_HIP(ctx, launch_moment_expand(ctx->d_self.p, ctx->d_mom_expand.p, (int)ctx->mom_expand.size(), partial, st),
+        CHECK_HIP(ctx, launch_moment_expand(self, ctx->d_mom_expand.p, (int)ctx->mom_expand.size(), partial, st),
                   "element matrices from moments");
         return PUFE_OK;
     }
@@ -1191,10 +1199,7 @@ int pufe_assemble_noalloc(pufe_ctx *ctx, const double *d_V, const double *kpts, 
         return fail(ctx, PUFE_ERR_UNSUPPORTED,
                     "pufe_assemble_noalloc: the Bloch-periodic enrichment keeps its image weights in context buffers; "
                     "use pufe_assemble");
-    // workspace: the partial tiles, behind the room the size limit counts for
-    // a phase table
-    const size_t ztab_bytes = (sizeof(double2) * kMaxKPerLaunch * 27 + 255) / 256 * 256;
-    const size_t need = ztab_bytes + (size_t)ctx->part_slots * 512 * sizeof(double);
+    const size_t need = noalloc_bytes(ctx);
     if (need > kScratchBytes)
         return fail(ctx, PUFE_ERR_UNSUPPORTED,
                     "pufe_assemble_noalloc: this problem's partial tiles need " + std::to_string(need) +
@@ -1205,7 +1210,7 @@ int pufe_assemble_noalloc(pufe_ctx *ctx, const double *d_V, const double *kpts, 
     double *ws = nullptr;
     CHECK_HIP(ctx, scratch_address(ctx->device, &ws), "workspace address");
     return assemble_impl(ctx, d_V, kpts, n_k, precision, out_dtype, d_H, d_S, st,
-                         ws + ztab_bytes / sizeof(double), false);
+                         ws + kNoallocTiles / sizeof(double), false);
 }
 
 int pufe_element_matrices(pufe_ctx *ctx, int64_t elem, const double *d_V, int precision, double *d_He,
@@ -1285,7 +1290,7 @@ static int build_poisson(pufe_ctx *ctx, hipStream_t st) {
     {
         DevBuf<double> zeroV, Hfull;
         CHECK_HIP(ctx, zeroV.alloc((size_t)std::max<int64_t>(ctx->n_qp, 1)), "alloc zero potential");
-        CHECK_HIP(ctx, launch_fill_zero(zeroV.p, ctx->n_qp, false, st), "zero potential");
+        CHECK_HIP(ctx, launch_fill_zero(zeroV.p, ctx->n_qp, st), "zero potential");
         CHECK_HIP(ctx, Hfull.alloc((size_t)pl.nnz), "alloc kinetic matrix");
         const double gamma[3] = {0.0, 0.0, 0.0};
         int rc = assemble_impl(ctx, zeroV.p, gamma, 1, PUFE_PREC_FP64, PUFE_OUT_F64_GAMMA, Hfull.p, nullptr, st,
@@ -1621,7 +1626,7 @@ int pufe_assemble_backward(pufe_ctx *ctx, const double *d_V, const double kpt[3]
                                                       ctx->d_adj_lam.p, d_V, d_P ? d_dLdV : nullptr, ctx->d_adj_f.p, mg,
                                                       ctx->adj_lds[w], st), "adjoint");
         }
-        if (!d_P && d_dLdV) CHECK_HIP(ctx, launch_fill_zero(d_dLdV, ctx->n_qp, false, st), "zero dLdV");
+        if (!d_P && d_dLdV) CHECK_HIP(ctx, launch_fill_zero(d_dLdV, ctx->n_qp, st), "zero dLdV");
         if (d_dLdR)
             CHECK_HIP(ctx, launch_force_reduce((int)ctx->prob.species.size(), ctx->d_adj_ptr.p, ctx->d_adj_slots.p,
                                                d_P || d_Q ? ctx->d_adj_f.p : nullptr, nullptr, d_dLdR, st),
@@ -1640,7 +1645,7 @@ int pufe_assemble_backward(pufe_ctx *ctx, const double *d_V, const double kpt[3]
                                             ctx->d_pt_off.p, ctx->d_Pt.p, d_dLdV, ctx->d_fP.p + wide_slots, mg,
                                             ctx->bw_lds_wide, st), "adjoint (P, wide elements)");
     } else if (d_dLdV) {
-        CHECK_HIP(ctx, launch_fill_zero(d_dLdV, ctx->n_qp, false, st), "zero dLdV");
+        CHECK_HIP(ctx, launch_fill_zero(d_dLdV, ctx->n_qp, st), "zero dLdV");
     }
     if (d_Q) {
         CHECK_HIP(ctx, launch_gather_adjoint(pl.kp, pl.nel, pl.max_nloc, ctx->d_elems.p, ctx->d_edof.p, ctx->d_pt_off.p,
@@ -1702,7 +1707,7 @@ int pufe_bsr_to_dense(pufe_ctx *ctx, const void *d_bsr, int dtype, double *d_den
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     const Plan &pl = ctx->plan;
     int64_t n = pl.dof_off[pl.nv];
-    CHECK_HIP(ctx, launch_fill_zero(d_dense, 2 * n * n, false, st), "zero dense");
+    CHECK_HIP(ctx, launch_fill_zero(d_dense, 2 * n * n, st), "zero dense");
     CHECK_HIP(ctx, launch_bsr_to_dense((int64_t)pl.bcol.size(), ctx->d_brow.p, ctx->d_bcol.p, ctx->d_bval_off.p,
                                        ctx->d_dof_off.p, d_bsr, dtype == PUFE_OUT_C128 ? 0 : 1, n, d_dense, st),
               "bsr to dense");
@@ -1742,8 +1747,21 @@ static int upload_moments(pufe_ctx *ctx, hipStream_t st) {
     CHECK_HIP(ctx, ctx->d_mom_expand.upload_list(ctx->mom_expand, st), "upload expansion list");
     if (ctx->mom_doubles > 0) CHECK_HIP(ctx, ctx->d_mom.alloc((size_t)ctx->mom_doubles), "alloc moments");
     else ctx->d_mom.release();
-    std::vector<CtxDev> self(1);
-    self[0] = tables_of(ctx);
+    std::vector<CtxDev> self(2, tables_of(ctx));
+    // the allocation-free entry may overlap pufe_assemble on another stream: its
+    // moments lie behind its partial tiles or in slots of their own
+    const size_t tiles = noalloc_bytes(ctx);
+    ctx->d_mom_na.release();
+    if (ctx->mom_doubles > 0 && tiles <= kScratchBytes) {
+        if (tiles + (size_t)ctx->mom_doubles * sizeof(double) <= kScratchBytes) {
+            double *ws = nullptr;
+            CHECK_HIP(ctx, scratch_address(ctx->device, &ws), "workspace address");
+            self[1].mom = ws + tiles / sizeof(double);
+        } else {
+            CHECK_HIP(ctx, ctx->d_mom_na.alloc((size_t)ctx->mom_doubles), "alloc moments");
+            self[1].mom = ctx->d_mom_na.p;
+        }
+    }
     CHECK_HIP(ctx, ctx->d_self.upload(self, st), "upload tables");
     return PUFE_OK;
 }

@@ -735,12 +735,6 @@ __global__ void fill_zero_kernel(double *__restrict__ p, int64_t n) {
     for (; i < n; i += stride) p[i] = 0.0;
 }
 
-__global__ void fill_zero_f32_kernel(float *__restrict__ p, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = 0.0f;
-}
-
 // Element matrices of one element (full, mirrored), from its partials.
 __global__ void elem_matrices_kernel(const ElemDev *__restrict__ elems, int64_t e,
                                      const double *__restrict__ partial, double *__restrict__ He,
@@ -974,14 +968,11 @@ hipError_t launch_chunk_reduce_batch(const CtxDev *ctxs, const int4 *list, int n
     return hipGetLastError();
 }
 
-hipError_t launch_fill_zero(void *p, int64_t n, bool f32, hipStream_t st) {
+hipError_t launch_fill_zero(void *p, int64_t n, hipStream_t st) {
     if (n == 0) return hipSuccess;
     int64_t blocks = (n + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    if (f32)
-        hipLaunchKernelGGL(fill_zero_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (float *)p, n);
-    else
-        hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (double *)p, n);
+    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (double *)p, n);
     return hipGetLastError();
 }
 

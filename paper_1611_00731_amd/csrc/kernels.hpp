@@ -9,7 +9,7 @@
 namespace pufe {
 
 constexpr int kContractQ = 16;      // quadrature points per LDS stage of the contraction
-constexpr int kMaxKPerLaunch = 16;  // k-points handled by one scatter launch
+constexpr int kMaxKPerLaunch = 16;  // k-points handled by one assembly launch
 constexpr int kSplitQ = 32;         // quadrature points per LDS stage of the split-bf16 contraction
 // Fixed device workspace of the allocation-free assembly (per GPU, held for
 // the life of the process): the K-chunk partial tiles, behind room for a phase
@@ -64,7 +64,7 @@ hipError_t launch_split_persistent(int nlimb, int lmax, bool gen, const CtxDev *
                                    int grid, size_t lds, hipStream_t st);
 hipError_t launch_chunk_reduce(const ElemDev *elems, const int2 *list, int n, double *partial, hipStream_t st);
 hipError_t launch_chunk_reduce_batch(const CtxDev *ctxs, const int4 *list, int n, hipStream_t st);
-hipError_t launch_fill_zero(void *p, int64_t n, bool f32, hipStream_t st);
+hipError_t launch_fill_zero(void *p, int64_t n, hipStream_t st);
 hipError_t launch_elem_matrices(const ElemDev *elems, int64_t e, const double *partial, double *He, double *Se,
                                 int ld, hipStream_t st);
 hipError_t launch_bsr_to_dense(int64_t nnzb, const int32_t *brow, const int32_t *bcol, const int64_t *bval_off,

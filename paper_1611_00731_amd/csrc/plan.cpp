@@ -335,7 +335,7 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
             pl.spl_off[k] = (int32_t)pl.spl.size();
             radial_spline(pr.radial[k], pr.enr[k].rc, pl.spl);
         }
-    std::vector<std::vector<int32_t>> by_color(27);
+    uint32_t colors = 0;   // parity classes of the elements in use
     for (int64_t e = 0; e < pl.nel; ++e) {
         ElemDev &el = pl.elems[e];
         int i[3] = {(int)(e % n1), (int)((e / n1) % n2), (int)(e / ((int64_t)n1 * n2))};
@@ -495,12 +495,11 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         pl.max_nloc = std::max(pl.max_nloc, el.nloc);
         pl.max_nfun = std::max(pl.max_nfun, nfun);
         pl.max_ngrp = std::max(pl.max_ngrp, el.ngrp);
-        // colour: elements of one colour share no vertex, so their scatters
-        // touch disjoint blocks (odd n_d puts the last layer in colour 2)
+        // colour: elements of one colour share no vertex (odd n_d puts the last
+        // layer in colour 2)
         int col[3];
         for (int d = 0; d < 3; ++d) col[d] = (mesh[d] % 2 == 1 && i[d] == mesh[d] - 1) ? 2 : (i[d] % 2);
-        el.color = col[0] + 3 * col[1] + 9 * col[2];
-        by_color[el.color].push_back((int32_t)e);
+        colors |= 1u << (col[0] + 3 * col[1] + 9 * col[2]);
     }
     pl.img_cur = pl.img;
     // (element, local function) pairs of every DOF, element order
@@ -538,13 +537,7 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
             pl.dof_el_off[g + 1] = (int64_t)pl.dof_el.size();
         }
     }
-    pl.color_elems.clear();
-    pl.color_off.assign(1, 0);
-    for (int c = 0; c < 27; ++c) {
-        if (by_color[c].empty()) continue;
-        pl.color_elems.insert(pl.color_elems.end(), by_color[c].begin(), by_color[c].end());
-        pl.color_off.push_back((int32_t)pl.color_elems.size());
-    }
+    pl.n_colors = __builtin_popcount(colors);
     // ---- assembly lists: contributions of every block (v, w), v <= w, largest
     // blocks first
     {

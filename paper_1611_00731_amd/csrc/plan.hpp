@@ -49,8 +49,7 @@ struct Plan {
     bool bloch = false;
     std::vector<int32_t> img_nk;    // per image entry: lattice shift n (3), then 0 (cos weight) or 1 (sin)
     std::vector<int32_t> bpart;     // per enriched entry: its partner's entry index (-1: an imaginary part)
-    std::vector<int32_t> color_elems;
-    std::vector<int32_t> color_off; // n_colors + 1
+    int32_t n_colors = 0;           // classes of elements that share no vertex
     // assembly: the (element, corner, corner) triples of every block with
     // v <= w, element by element, and one entry per such block (see gather.hpp)
     std::vector<int32_t> contr;

@@ -26,7 +26,6 @@ struct ElemDev {
     int32_t nloc, nfe, nfun, ngrp;
     int32_t grp_off, edof_off;
     int32_t ijk[3];
-    int32_t color;
     int32_t shifts;      // lattice shift bits of corner c at bits 3c..3c+2 (bit d = direction d)
     int32_t nchunk;      // K-chunks of the contraction
     int64_t leaf_off, leaf_end;
