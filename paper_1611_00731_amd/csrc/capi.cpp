@@ -502,7 +502,10 @@ static void plan_moments(pufe_ctx *c) {
         total += cost[e] + m.ff * pl.kp.n3 * (double)(el.leaf_end - el.leaf_off);
     }
     // the moment form takes two to four launches more; below about 60 us of work
-    // saved on the whole chip (1024 SIMDs) a problem stays with the direct kernels
+    // saved on the whole chip (1024 SIMDs) a problem stays with the direct kernels.
+    // Measured per assembly, direct and in moment form: below the line 127 and 221
+    // us (a few dozen elements on a sheared mesh), above it 1.0 and 0.63 ms (512
+    // elements, 1.52 M points)
     if (saved < 60e-6 * 2.4e9 * 1024.0) {
         for (ElemDev &el : pl.elems) el.mchunk = el.fchunk = 0;
         return;
