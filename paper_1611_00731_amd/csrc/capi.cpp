@@ -1361,7 +1361,7 @@ int pufe_hartree(pufe_ctx *ctx, const double *d_n, double *d_vh, double *d_v, do
         ++it;
         CHECK_HIP(ctx, hipMemcpyAsync(&state, ctx->d_cg_state.p, sizeof state, hipMemcpyDeviceToHost, st), "CG state");
         CHECK_HIP(ctx, hipStreamSynchronize(st), "CG state");
-        if (state.done || state.broken) break;
+        if (state.done || state.ended) break;
     }
     const int it = state.it;
     const double rel = state.rel;

@@ -179,14 +179,17 @@ __global__ __launch_bounds__(256) void dot_final_kernel(int n, const double *__r
 //
 // K x = r on the classical FE space, every scalar on the device: an iteration
 // is two launches, each of which sums the block partials of the one before it
-// in a fixed order, and the host only looks at `done` once per batch of
+// in a fixed order, and the host only looks at the outcome once per batch of
 // iterations.  (Read back to the host, the three scalars of an iteration cost
 // more than its arithmetic: 5.2 ms for 59 iterations on 4096 unknowns.)
 //
 // Launch A(i): rr = |r_i|^2; stop if it meets the tolerance, else beta,
 // p_i = r_i + beta p_{i-1} (kept in the buffer of parity i), Ap = K p_i and
 // the partials of p_i . Ap.  Launch B(i): alpha, x += alpha p_i,
-// r -= alpha Ap and the partials of |r|^2.
+// r -= alpha Ap and the partials of |r|^2.  What a launch reads to decide whether
+// the solve goes on is written by launches of the other kind only: `ended` by B
+// for A, `done` by A for B.  The waves of a work group, and the groups of a
+// launch, cannot then disagree, whenever they start.
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -258,7 +261,10 @@ __global__ __launch_bounds__(256) void cg_spmv_kernel(int64_t nv, int nfs, int i
     const int sub = threadIdx.x / TV;
     const int64_t v = (int64_t)blockIdx.x * V + sub;
     const int64_t k0 = v < nv ? brow_ptr[v] : 0, k1 = v < nv ? brow_ptr[v + 1] : 0;
-    if (st->done || st->broken) return;
+    if (st->ended) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->done = 1;
+        return;
+    }
     const int g = lane / per, e = lane - g * per, row = e / nfs, col = e - row * nfs;
     double kr = 0.0, kp = 0.0;
     if (g < G) {
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(256) void cg_spmv_kernel(int64_t nv, int nfs, int i
     const bool stop = it == 0 ? !(r0 > 0.0) : rel <= tol;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st->rr[it & 1] = rr;
-        st->r0 = r0;
+        if (it == 0) st->r0 = r0;
         st->rel = rel;
         if (stop || check) {
             st->it = it;
@@ -313,14 +319,15 @@ __global__ __launch_bounds__(256) void cg_update_kernel(int64_t n, int it, const
                                                         double *__restrict__ r, const double *__restrict__ apart,
                                                         int napart, double *__restrict__ part, CgState *__restrict__ st) {
     __shared__ double s[4];
-    // `broken` of an earlier launch only: a group of this one that finds
-    // p.Ap <= 0 before another has started leads it to the same decision
-    if (st->done || st->broken) return;
+    if (st->done) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->ended = 1;
+        return;
+    }
     const double pAp = sum_partials(apart, napart, s);
     if (!(pAp > 0.0)) {
-        if (threadIdx.x == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
             st->it = it;
-            st->broken = 1;
+            st->ended = 1;
         }
         return;
     }

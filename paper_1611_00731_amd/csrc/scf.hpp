@@ -27,11 +27,12 @@ int dot_partial_slots();
 
 // Conjugate gradients on the classical FE space with their scalars on the
 // device: |r|^2 of the last two iterations, the first residual's norm, the
-// relative residual, iterations done, and whether the solve has ended by the
-// tolerance (or the iteration limit) or on p . Ap <= 0.
+// relative residual, iterations done, and whether the solve is over: `done` is
+// written by the products (the tolerance or the iteration limit is met, or
+// `ended` was set), `ended` by the updates (p . Ap <= 0, or `done` was set).
 struct CgState {
     double rr[2], r0, rel;
-    int32_t it, done, broken;
+    int32_t it, done, ended;
 };
 struct CgSolve {
     int64_t nv;
