@@ -114,8 +114,10 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
         shift = dn(0) + 3 * dn(1) + 9 * dn(2);
     }
     // a block that meets no cell boundary has phase one (and, with the
-    // Bloch-periodic enrichment, the boundary phase on classical rows only)
-    const bool wraps = __any(lane < ncon && (BLOCH ? (sa3 | sb3) != 0 : shift != 13));
+    // Bloch-periodic enrichment, the boundary phase on classical rows only).  Real
+    // output of the periodic form has none at all: kappa is an integer, of any size,
+    // and the cosine of a rounded 2 pi kappa is not one
+    const bool wraps = (BLOCH || DT != 2) && __any(lane < ncon && (BLOCH ? (sa3 | sb3) != 0 : shift != 13));
     if (__syncthreads_or(live && wraps)) {
         for (int i = threadIdx.x; i < kps.nk * 27; i += 256) {
             const int k = i / 27, t = i - 27 * k;
