@@ -12,8 +12,13 @@
 // and a centre's force is -sum (dL/dPsi_f d_k Psi_f + dL/d d_d Psi_f d_dk Psi_f).
 // Along a line of points the polynomials in z and y are evaluated on the
 // coefficients (as on the accumulators of the forward sums), and the sum over
-// g and the powers of x run on v_mfma_f64_4x4x4: row operand the coefficients,
-// column operand x^k times the functions at 4 points.  Per point and ordered
+// g and the polynomials in x run on v_mfma_f64_4x4x4: row operand the coefficients,
+// column operand the polynomial times the functions at 4 points.  The polynomials of
+// each direction are the products of its two hats, m_0 m_0 (1, t, t^2) with t =
+// m_1 / m_0, and m_0 (1, t): the powers of t scale the operand, m_0 the results.  The
+// powers of x itself add up to a product of hats with cancellation near the face
+// where it vanishes: with them dL/dV of one vertex was off by up to 1.2e-12 of itself
+// there, by 1e-14 now as through the functions' own products.  Per point and ordered
 // pair that is 31 multiply-adds on the matrix cores, where the products of Ps
 // with the element's own functions take 256; P and Q share one pass.
 // Bound by issue and latency between the matrix instructions (two waves a SIMD,
@@ -51,14 +56,15 @@ constexpr int kAdjPair = 108 * 64;   // doubles of a quad: LE, LA (27 each), LB_
 __host__ __device__ constexpr int adj_steps(int p) { return ((p + 2) * (p + 2) + 3) / 4; }
 __host__ __device__ inline int adj_mixed_doubles(int p) { return 5 * adj_steps(p) * (p + 2) * 64; }
 
-// 1D tables of a leaf, unweighted: x [n]; y, z polynomials [n][5]; mixed
-// [n][p + 2] and classical [n][2 p + 1] Lagrange values for x, y, z; weights
-// [3][n] (z with the leaf's volume factor).
+// 1D tables of a leaf, unweighted: x [n][2] (m_0, m_1 / m_0 of the two hats); y, z
+// [n][5] (m_0 m_0, m_0 m_1, m_1 m_1, m_0, m_1); mixed [n][p + 2] and classical
+// [n][2 p + 1] Lagrange values for x, y, z; weights [3][n] (z with the leaf's volume
+// factor).
 struct AdjTab {
     int yt, zt, fx, fy, fz, gx, gy, gz, w, size;
     __host__ __device__ AdjTab(int n, int p) {
         const int nf = p + 2, ng = 2 * p + 1;
-        yt = n;
+        yt = 2 * n;
         zt = yt + 5 * n;
         fx = zt + 5 * n;
         fy = fx + nf * n;
@@ -249,7 +255,7 @@ __device__ __forceinline__ void adj_pairs(const double *__restrict__ lam, const 
             for (int x = lane & 3; x < ((n + 3) & ~3); x += 4) {
                 const int xo = min(x, n - 1), q = q0 + xo;
                 const bool in = x < n && yr < v.nyl;
-                const double xi = v.T[xo], w = in ? v.W[q] : 0.0;
+                const double mx = v.T[2 * xo], t = v.T[2 * xo + 1], w = in ? v.W[q] : 0.0;
                 const double *pg = v.P + og + 10 * q, *pf = v.P + of + 10 * q;
                 const dbl2 g0 = *(const dbl2 *)pg, g1 = *(const dbl2 *)(pg + 2);
                 double p = g0[0], dx = g0[1], dy = g1[0], dz = g1[1];
@@ -263,15 +269,16 @@ __device__ __forceinline__ void adj_pairs(const double *__restrict__ lam, const 
                         gz = mfma4(e[k], dz, gz);
                         u = mfma4(a[k], p, u);
                         if (k < 2) {
-                            p *= xi;
-                            dx *= xi;
-                            dy *= xi;
-                            dz *= xi;
+                            p *= t;
+                            dx *= t;
+                            dy *= t;
+                            dz *= t;
                         }
                     }
-                    adj_force_val(pf, u + v.V[q] * y, w, fr);
-                    adj_force_grad(pf, gx, gy, gz, w, fr);
-                    const double dv = adj_sum_functions(pf[0] * y, rep);
+                    const double h = mx * mx, wh = w * h;
+                    adj_force_val(pf, u + v.V[q] * y, wh, fr);
+                    adj_force_grad(pf, gx, gy, gz, wh, fr);
+                    const double dv = h * adj_sum_functions(pf[0] * y, rep);
                     if (lane < 4 * rep && in) sDV[q] = dv;
                 } else if (ROLE == ADJ_B) {
                     double gx = 0.0, gy = 0.0, gz = 0.0;
@@ -280,23 +287,23 @@ __device__ __forceinline__ void adj_pairs(const double *__restrict__ lam, const 
                         gy = mfma4(a[k], p, gy);
                         gz = mfma4(b[k], p, gz);
                         if (k < 2) gx = mfma4(e[k], p, gx);
-                        if (k < 2) p *= xi;
+                        if (k < 2) p *= t;
                     }
-                    adj_force_grad(pf, gx, gy, gz, w, fr);
+                    adj_force_grad(pf, gx, mx * gy, mx * gz, w * mx, fr);
                 } else {
-                    double u = 0.0, u2 = 0.0;
+                    double u = 0.0, u1 = 0.0, u2 = 0.0;
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
                         u = mfma4(a[k], dy, u);
                         u2 = mfma4(b[k], dz, u2);
                         if (k < 2) {
-                            u = mfma4(e[k], dx, u);
-                            dx *= xi;
-                            dy *= xi;
-                            dz *= xi;
+                            u1 = mfma4(e[k], dx, u1);
+                            dx *= t;
+                            dy *= t;
+                            dz *= t;
                         }
                     }
-                    adj_force_val(pf, u + u2, w, fr);
+                    adj_force_val(pf, u1 + mx * (u + u2), w * mx, fr);
                 }
             }
         }
@@ -402,12 +409,12 @@ __device__ __forceinline__ AdjTask adj_task(int un, int qb, int gf) {
 
 // LDS map: the table [4 nt rows], 2 V, weights, dL/dV of every quad and group, 1D tables,
 // classical coefficients of a plane, force sums of every task, Gauss
-// rule, cell constants, image centres, groups.
+// rule, cell constants, image centres, groups (each has one function at least).
 static size_t adj_lds_bytes(int nt, int nimg, int n, int p, int points, int planes) {
     const int ng = 2 * p + 1, sums = mom_quads_b(nt) + (nt + 3) / 4;
     return sizeof(double) * ((size_t)4 * nt * adj_stride(points) + (size_t)(2 + sums) * points + AdjTab(n, p).size +
                              (size_t)planes * ng * ng + (size_t)adj_tasks(nt) * 48 + 2 * kMaxGauss + 12 + 3 * (size_t)nimg) +
-           sizeof(GroupDev) * kMaxGroups + 64;
+           sizeof(GroupDev) * std::min(kMaxGroups, 4 * nt) + 64;
 }
 
 AdjStage adj_stage(int nt, int nimg, int n, int p) {
@@ -512,13 +519,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 for (int e = tid; e < mt.size; e += NT) {
                     int j = e;
                     double v;
-                    if (j < n) {
-                        v = -1.0 + (c[0] + sGx[j]) * h;
-                    } else if (j < mt.fx) {
-                        j -= n;
-                        const int d = j < 5 * n ? 1 : 2, i = (j - 5 * n * (d - 1)) / 5, k = j % 5;
-                        const double x = -1.0 + ((d == 1 ? c[1] : c[2]) + sGx[i]) * h, m0 = 0.5 * (1.0 - x), m1 = 0.5 * (1.0 + x);
-                        v = k == 0 ? m0 * m0 : (k == 1 ? m0 * m1 : (k == 2 ? m1 * m1 : (k == 3 ? m0 : m1)));
+                    if (j < mt.fx) {
+                        const int d = j < mt.yt ? 0 : (j < mt.zt ? 1 : 2), m = d == 0 ? 2 : 5;
+                        j -= d == 0 ? 0 : (d == 1 ? mt.yt : mt.zt);
+                        const int i = j / m, k = j - i * m;
+                        const double x = -1.0 + ((d == 0 ? c[0] : (d == 1 ? c[1] : c[2])) + sGx[i]) * h;
+                        const double m0 = 0.5 * (1.0 - x), m1 = 0.5 * (1.0 + x);
+                        if (d == 0) v = k == 0 ? m0 : m1 / m0;
+                        else v = k == 0 ? m0 * m0 : (k == 1 ? m0 * m1 : (k == 2 ? m1 * m1 : (k == 3 ? m0 : m1)));
                     } else if (j < mt.w) {
                         const bool mixed = j < mt.gx;
                         j -= mixed ? mt.fx : mt.gx;
@@ -670,8 +678,6 @@ __device__ __forceinline__ void fold_pairs(const KParams &kp, const ElemDev &el,
         for (int m = 0; m < 108; ++m) o[m * 64] = 0.0;
         return;
     }
-    const double prod[3][3] = {{0.25, -0.5, 0.25}, {0.25, 0.0, -0.25}, {0.25, 0.5, 0.25}};
-    const double lin[2][2] = {{0.5, -0.5}, {0.5, 0.5}};
     double E[3][3][3], A[3][3][3], X[2][3][3], Y[3][2][3], Z[3][3][2];
 #pragma unroll
     for (int k = 0; k < 3; ++k)
@@ -705,19 +711,19 @@ __device__ __forceinline__ void fold_pairs(const KParams &kp, const ElemDev &el,
             const int64_t at = ok ? (int64_t)(nfe + ka) * npad + nfe + kb : 0;
             const double pv = ok && Ps ? Ps[at] : 0.0, qv = ok && Qs ? 2.0 * Qs[at] : 0.0;
             const double hx[2] = {cx ? 0.5 : -0.5, dx ? 0.5 : -0.5}, hy[2] = {cy ? 0.5 : -0.5, dy ? 0.5 : -0.5};
-            const double yy = kp.G[4] * hy[0] * hy[1] * pv;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double al = prod[cx + dx][k];
-                e9[k][iy] += al * pv;
-                a9[k][iy] += al * qv;
-                a9[k][0] += al * yy;
-                a9[k][1] += 2.0 * al * yy;
-                a9[k][2] += al * yy;
-                y6[k][cy] += hy[1] * kp.sd[1] * al * pv;
-                if (k < 2) x6[k][iy] += hx[1] * kp.sd[0] * lin[cx][k] * pv;
-            }
-            a9[0][iy] += kp.G[0] * hx[0] * hx[1] * pv;
+            // one is m_0 m_0 + 2 m_0 m_1 + m_1 m_1 in the direction of the derivatives
+            const double xx = kp.G[0] * hx[0] * hx[1] * pv, yy = kp.G[4] * hy[0] * hy[1] * pv;
+            const int ix = cx + dx;
+            e9[ix][iy] += pv;
+            a9[ix][iy] += qv;
+            a9[0][iy] += xx;
+            a9[1][iy] += 2.0 * xx;
+            a9[2][iy] += xx;
+            a9[ix][0] += yy;
+            a9[ix][1] += 2.0 * yy;
+            a9[ix][2] += yy;
+            x6[cx][iy] += hx[1] * kp.sd[0] * pv;
+            y6[ix][cy] += hy[1] * kp.sd[1] * pv;
         }
         const double zz = kp.G[8] * hz[0] * hz[1];
 #pragma unroll
