@@ -849,11 +849,13 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     CHECK_HIP(ctx, ctx->d_items.upload_list(ctx->items, st), "upload work items");
     CHECK_HIP(ctx, ctx->d_items_wide.upload_list(ctx->items_wide, st), "upload work items");
     CHECK_HIP(ctx, ctx->d_items_split.upload_list(ctx->items_split, st), "upload work items");
-    // tables of the self-consistent field pieces belong to the previous plan
+    // tables of the self-consistent field pieces and of the adjoint belong to the
+    // previous plan (and its rule: a caller's, if pufe_set_rule gave one)
     ctx->d_dof_el_off.release();
     ctx->d_dof_el.release();
     ctx->d_fe_be.release();
     ctx->have_poisson = false;
+    ctx->have_bw = ctx->have_bw_direct = false;
     {
         int rc = upload_nonlocal(ctx, st);
         if (rc != PUFE_OK) return rc;
