@@ -217,6 +217,16 @@ int pufe_set_projectors(pufe_ctx *ctx, int n, const pufe_projector *proj);
  * PUFE_ERR_UNSUPPORTED (too many functions on an element). */
 int pufe_set_enrichment_phase(pufe_ctx *ctx, int form);
 
+/* The FP64 assembly and adjoint of tensor-product elements work through moments
+ * of the enrichment functions where that is less work; their sums (and the
+ * adjoint's coefficients) take device memory beyond that of the direct kernels.
+ * bytes: the most that the assembly's sums, and likewise the adjoint's buffers,
+ * may take; negative (the default): half of what is free when they are made.
+ * Where it does not suffice, or cannot be had, the direct kernels run, to the
+ * same accuracy.  Errors: PUFE_ERR_STATE after pufe_setup or before
+ * pufe_set_problem. */
+int pufe_set_moment_limit(pufe_ctx *ctx, int64_t bytes);
+
 /* Build the adaptive rule on the device (section "Adaptive quadrature"),
  * upload the element tables and plan the contraction work.  Synchronous.
  * The rule is built once per geometry and reused by every assembly. */
@@ -253,6 +263,12 @@ int pufe_get_layout(pufe_ctx *ctx, int64_t *dof_offset, int64_t *brow_ptr, int32
  * V at these points for pufe_assemble. */
 int pufe_get_quadrature(pufe_ctx *ctx, double *d_xyz, double *d_w, int64_t *d_elem_qp_offset,
                         void *stream);
+
+/* Which form the FP64 kernels of the current plan take: elem_moment[n_elem] = 1
+ * for the elements assembled through moments, *adjoint_moment = 1 if the FP64
+ * adjoint runs through them (0 also before its first call, which plans it).
+ * Either pointer may be NULL. */
+int pufe_get_forms(pufe_ctx *ctx, int32_t *elem_moment, int32_t *adjoint_moment);
 
 /* Octree leaves (host arrays): level[n_leaves], ijk[n_leaves*3] integer cell
  * coordinates at that level, elem_leaf_offset[n_elem+1].  Synchronous. */

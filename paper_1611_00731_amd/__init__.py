@@ -30,7 +30,7 @@ EXPORTS = ["pufe_error_string", "pufe_last_error_message", "pufe_create", "pufe_
            "pufe_assemble_backward", "pufe_bsr_to_dense", "pufe_enable_timing",
            "pufe_kernel_times", "pufe_set_positions", "pufe_batch_create", "pufe_batch_assemble",
            "pufe_batch_destroy", "pufe_batch_last_error_message", "pufe_tune", "pufe_assemble_noalloc", "pufe_set_rule", "pufe_set_projectors",
-           "pufe_set_enrichment_phase", "pufe_fe_load", "pufe_fe_eval", "pufe_hartree", "pufe_lda_xc"]
+           "pufe_set_enrichment_phase", "pufe_set_moment_limit", "pufe_get_forms", "pufe_fe_load", "pufe_fe_eval", "pufe_hartree", "pufe_lda_xc"]
 
 
 class PufeError(RuntimeError):
@@ -88,6 +88,8 @@ def _load():
         "pufe_set_rule": ([vp, C.c_int64, i32p, i32p, i64p, vp], C.c_int),
         "pufe_set_projectors": ([vp, C.c_int, C.POINTER(pufe_projector)], C.c_int),
         "pufe_set_enrichment_phase": ([vp, C.c_int], C.c_int),
+        "pufe_set_moment_limit": ([vp, C.c_int64], C.c_int),
+        "pufe_get_forms": ([vp, i32p, i32p], C.c_int),
         "pufe_fe_load": ([vp, vp, vp, vp], C.c_int),
         "pufe_fe_eval": ([vp, vp, vp, vp], C.c_int),
         "pufe_hartree": ([vp, vp, vp, vp, C.c_double, C.c_int, C.POINTER(C.c_int), dp, vp], C.c_int),
@@ -182,6 +184,17 @@ def pufe_set_projectors(ctx, projectors):
 def pufe_set_enrichment_phase(ctx, form):
     """form: "periodic" (f(R) = 1) or "bloch" (f(R) = exp(i k.R)) of eq. Psi."""
     _check(ctx, lib.pufe_set_enrichment_phase(ctx, ENR_PHASE[form]))
+
+
+def pufe_set_moment_limit(ctx, n_bytes):
+    _check(ctx, lib.pufe_set_moment_limit(ctx, int(n_bytes)))
+
+
+def pufe_get_forms(ctx):
+    """(elements whose FP64 assembly works through moments, whether the FP64 adjoint does)."""
+    elem, adj = np.zeros(pufe_query(ctx)["n_elem"], np.int32), C.c_int32()
+    _check(ctx, lib.pufe_get_forms(ctx, elem.ctypes.data_as(C.POINTER(C.c_int32)), C.byref(adj)))
+    return elem != 0, adj.value != 0
 
 
 def pufe_setup(ctx, stream=None):

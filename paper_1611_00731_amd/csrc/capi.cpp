@@ -114,11 +114,18 @@ struct pufe_ctx {
     DevBuf<CtxDev> d_self;          // this problem's tables, for the kernels that take a list of problems; [1] with
                                     // the allocation-free entry's moment slots
     DevBuf<double> d_mom_na;        // these slots, where its workspace has no room for them
+    // the moment forms' device memory: the caller's limit (negative: none), and
+    // whether the forward plan has given the form up for lack of it
+    int64_t mom_limit = -1;
+    bool mom_off = false;
+    double planned_items = 0.0;     // what plan_items last planned for
+    int planned_block = 0;
     DevBuf<uint32_t> d_leaves;
     DevBuf<int64_t> d_leaf_count, d_leaf_off, d_bval_off, d_dof_off;
     DevBuf<ItemDev> d_items, d_items_split, d_items_wide;
     // adjoint
-    bool have_bw = false, have_bw_direct = false;   // the adjoint's plan; its direct kernels' items
+    // the adjoint's blocks, its choice of form, its direct kernels' items
+    bool have_bw = false, have_adj = false, have_bw_direct = false;
     std::vector<ItemDev> bw_items, bw_items_wide;   // elements of <= 80 functions, and the rest
     size_t bw_lds = 0, bw_lds_wide = 0;
     // FP64 adjoint in moment form: items by 4 and 8 waves, or none
@@ -302,7 +309,7 @@ int pufe_set_problem(pufe_ctx *ctx, const double lattice[9], const int mesh[3], 
     ctx->plan = std::move(pl);
     ctx->have_problem = true;
     ctx->have_setup = false;
-    ctx->have_bw = ctx->have_bw_direct = false;
+    ctx->have_bw = ctx->have_adj = ctx->have_bw_direct = false;
     ctx->n_leaves = ctx->n_qp = 0;
     ++ctx->plan_gen;
     return PUFE_OK;
@@ -458,6 +465,14 @@ static void plan_moments(pufe_ctx *c) {
     c->mom_reduce.clear();
     c->mom_expand.clear();
     c->mom_doubles = 0;
+    if (c->mom_off) {
+        for (ElemDev &el : pl.elems) {
+            el.mchunk = el.fchunk = 0;
+            el.mom_base = el.ff_base = 0;
+            el.nt = (el.nfun + 3) / 4;
+        }
+        return;
+    }
     int nimg = 0;
     for (const ElemDev &el : pl.elems)
         if (el.ngrp > 0) {
@@ -580,6 +595,20 @@ static void plan_moments(pufe_ctx *c) {
 
 static int upload_moments(pufe_ctx *ctx, hipStream_t st);
 
+// Whether a moment form may take `doubles` of device memory: within the caller's
+// limit, and at most half of what is free, so that a problem whose tables fit with
+// the direct kernels keeps room for its caller's matrices.
+static bool moments_fit(const pufe_ctx *c, int64_t doubles) {
+    const uint64_t bytes = (uint64_t)doubles * sizeof(double);
+    if (c->mom_limit >= 0) return bytes <= (uint64_t)c->mom_limit;
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return bytes <= avail / 2;
+}
+
 // Work items (row block x column block of 16x16 tiles x K-chunk), largest
 // MFMA work first.  sel: 0 every element (the split kernels); the elements on
 // the direct FP64 kernels: 1 those of at most kWholeMaxTiles tiles, 2 the
@@ -632,7 +661,10 @@ static std::vector<ItemDev> make_items(const pufe_ctx *c, int block_tiles, int *
     return sorted;
 }
 
-static void plan_items(pufe_ctx *c, double target_items, int block_tiles) {
+static void plan_items(pufe_ctx *c, double target_items, int block_tiles, bool moments = true) {
+    c->mom_off = !moments;
+    c->planned_items = target_items;
+    c->planned_block = block_tiles;
     plan_moments(c);
     plan_chunks(c, target_items);
     const int nfun = std::max(c->plan.max_nfun, 1);
@@ -748,6 +780,16 @@ static int upload_nonlocal(pufe_ctx *ctx, hipStream_t st) {
     return PUFE_OK;
 }
 
+static int place_moments(pufe_ctx *ctx, hipStream_t st);
+
+int pufe_set_moment_limit(pufe_ctx *ctx, int64_t bytes) {
+    if (!ctx) return PUFE_ERR_INVALID_ARG;
+    if (!ctx->have_problem) return fail(ctx, PUFE_ERR_STATE, "pufe_set_problem must come first");
+    if (ctx->have_setup) return fail(ctx, PUFE_ERR_STATE, "the moment forms' limit is set before pufe_setup");
+    ctx->mom_limit = bytes < 0 ? -1 : bytes;
+    return PUFE_OK;
+}
+
 int pufe_setup(pufe_ctx *ctx, void *stream) {
     if (!ctx) return PUFE_ERR_INVALID_ARG;
     if (!ctx->have_problem) return fail(ctx, PUFE_ERR_STATE, "pufe_set_problem must come first");
@@ -855,7 +897,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     ctx->d_dof_el.release();
     ctx->d_fe_be.release();
     ctx->have_poisson = false;
-    ctx->have_bw = ctx->have_bw_direct = false;
+    ctx->have_bw = ctx->have_adj = ctx->have_bw_direct = false;
     {
         int rc = upload_nonlocal(ctx, st);
         if (rc != PUFE_OK) return rc;
@@ -870,7 +912,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     CHECK_HIP(ctx, ctx->d_dof_off.upload(pl.dof_off, st), "upload layout");
     CHECK_HIP(ctx, ctx->d_partial.alloc((size_t)ctx->part_slots * 512), "alloc partial tiles");
     {
-        int rc = upload_moments(ctx, st);
+        int rc = place_moments(ctx, st);
         if (rc != PUFE_OK) return rc;
     }
     {
@@ -982,6 +1024,15 @@ int pufe_get_quadrature(pufe_ctx *ctx, double *d_xyz, double *d_w, int64_t *d_el
     if (d_elem_qp_offset)
         CHECK_HIP(ctx, launch_elem_qp_offset(ctx->plan.kp, ctx->plan.nel, ctx->d_leaf_off.p, d_elem_qp_offset, st),
                   "quadrature offsets");
+    return PUFE_OK;
+}
+
+int pufe_get_forms(pufe_ctx *ctx, int32_t *elem_moment, int32_t *adjoint_moment) {
+    if (!ctx) return PUFE_ERR_INVALID_ARG;
+    if (!ctx->have_setup) return fail(ctx, PUFE_ERR_STATE, "pufe_setup must come first");
+    if (elem_moment)
+        for (int64_t e = 0; e < ctx->plan.nel; ++e) elem_moment[e] = ctx->plan.elems[e].mchunk > 0;
+    if (adjoint_moment) *adjoint_moment = ctx->have_adj && !ctx->adj_fold.empty();
     return PUFE_OK;
 }
 
@@ -1462,12 +1513,16 @@ static int plan_backward(pufe_ctx *c, bool split, hipStream_t st) {
     if (!c->have_bw) {
         CHECK_HIP(c, c->d_pt_off.upload(pt_off, st), "upload adjoint offsets");
         CHECK_HIP(c, c->d_Pt.alloc((size_t)pt_off[pl.nel]), "alloc adjoint blocks");
-        const int rc = plan_adjoint_moments(c, pt_off[pl.nel], st);
-        if (rc != PUFE_OK) return rc;
         c->have_bw = true;
     }
     // with the moment form, the direct kernels serve the split precisions only
+    if (!split && !c->have_adj) {
+        const int rc = plan_adjoint_moments(c, pt_off[pl.nel], st);
+        if (rc != PUFE_OK) return rc;
+        c->have_adj = true;
+    }
     if (!split && !c->adj_fold.empty()) return PUFE_OK;
+    if (c->have_bw_direct) return PUFE_OK;
     std::vector<std::vector<int64_t>> slots(c->prob.species.size());
     const int64_t nn = (int64_t)c->bw_items.size(), ntot = nn + (int64_t)c->bw_items_wide.size();
     for (int64_t idx = 0; idx < ntot; ++idx) {
@@ -1490,15 +1545,27 @@ static int plan_backward(pufe_ctx *c, bool split, hipStream_t st) {
     return PUFE_OK;
 }
 
-// Moment form of the FP64 adjoint: all elements or none.
+// Moment form of the FP64 adjoint: all elements or none, also where its memory does
+// not fit (the direct kernels then serve FP64 too).
 static int plan_adjoint_moments(pufe_ctx *c, int64_t pt_doubles, hipStream_t st) {
     Plan &pl = c->plan;
     const int n = pl.kp.n, p = pl.kp.p, mg = std::max(pl.max_ngrp, 1);
-    for (int w = 0; w < 2; ++w) {
-        c->adj_items[w].clear();
-        c->adj_lds[w] = 0;
-    }
-    c->adj_fold.clear();
+    auto drop = [&] {
+        for (int w = 0; w < 2; ++w) {
+            c->adj_items[w].clear();
+            c->adj_lds[w] = 0;
+            c->d_adj_items[w].release();
+        }
+        c->adj_fold.clear();
+        c->d_adj_fold.release();
+        c->d_adj_base.release();
+        c->d_adj_ptr.release();
+        c->d_adj_slots.release();
+        c->d_adj_lam.release();
+        c->d_adj_Qt.release();
+        c->d_adj_f.release();
+    };
+    drop();
     // the serendipity functions are no tensor products; on sheared cells the
     // sums take the metric's mixed terms too
     if (p > 2 || pl.kp.skew) return PUFE_OK;
@@ -1578,14 +1645,23 @@ static int plan_adjoint_moments(pufe_ctx *c, int64_t pt_doubles, hipStream_t st)
         aslots.insert(aslots.end(), slots[A].begin(), slots[A].end());
         aptr[A + 1] = (int64_t)aslots.size();
     }
-    for (int w = 0; w < 2; ++w) CHECK_HIP(c, c->d_adj_items[w].upload_list(c->adj_items[w], st), "upload adjoint items");
-    CHECK_HIP(c, c->d_adj_fold.upload(c->adj_fold, st), "upload adjoint list");
-    CHECK_HIP(c, c->d_adj_base.upload(base, st), "upload adjoint offsets");
-    CHECK_HIP(c, c->d_adj_ptr.upload(aptr, st), "upload atom lists");
-    CHECK_HIP(c, c->d_adj_slots.upload(aslots, st), "upload atom lists");
-    CHECK_HIP(c, c->d_adj_lam.alloc((size_t)base[pl.nel]), "alloc adjoint coefficients");
-    CHECK_HIP(c, c->d_adj_Qt.alloc((size_t)pt_doubles), "alloc adjoint blocks");
-    CHECK_HIP(c, c->d_adj_f.alloc((size_t)slot * mg * 3), "alloc partial forces");
+    const int64_t forces = (int64_t)slot * mg * 3;
+    hipError_t e = moments_fit(c, base[pl.nel] + pt_doubles + forces) ? hipSuccess : hipErrorOutOfMemory;
+    if (e == hipSuccess) e = c->d_adj_lam.alloc((size_t)base[pl.nel]);
+    if (e == hipSuccess) e = c->d_adj_Qt.alloc((size_t)pt_doubles);
+    if (e == hipSuccess) e = c->d_adj_f.alloc((size_t)forces);
+    for (int w = 0; w < 2; ++w)
+        if (e == hipSuccess) e = c->d_adj_items[w].upload_list(c->adj_items[w], st);
+    if (e == hipSuccess) e = c->d_adj_fold.upload(c->adj_fold, st);
+    if (e == hipSuccess) e = c->d_adj_base.upload(base, st);
+    if (e == hipSuccess) e = c->d_adj_ptr.upload(aptr, st);
+    if (e == hipSuccess) e = c->d_adj_slots.upload(aslots, st);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        drop();
+        return PUFE_OK;
+    }
+    CHECK_HIP(c, e, "adjoint tables");
     return PUFE_OK;
 }
 
@@ -1603,7 +1679,7 @@ int pufe_assemble_backward(pufe_ctx *ctx, const double *d_V, const double kpt[3]
         return fail(ctx, PUFE_ERR_UNSUPPORTED, "the adjoint of the Bloch-periodic enrichment is not supported");
     hipStream_t st = (hipStream_t)stream;
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
-    if (!ctx->have_bw || ((nl != 0 || ctx->adj_fold.empty()) && !ctx->have_bw_direct)) {
+    if (!ctx->have_bw || (nl == 0 && !ctx->have_adj) || ((nl != 0 || ctx->adj_fold.empty()) && !ctx->have_bw_direct)) {
         int rc = plan_backward(ctx, nl != 0, st);
         if (rc != PUFE_OK) return rc;
     }
@@ -1750,25 +1826,45 @@ static int upload_moments(pufe_ctx *ctx, hipStream_t st) {
     CHECK_HIP(ctx, ctx->d_mom_tasks.upload_list(ctx->mom_tasks, st), "upload wave tasks");
     CHECK_HIP(ctx, ctx->d_mom_reduce.upload_list(ctx->mom_reduce, st), "upload chunk reduction list");
     CHECK_HIP(ctx, ctx->d_mom_expand.upload_list(ctx->mom_expand, st), "upload expansion list");
-    if (ctx->mom_doubles > 0) CHECK_HIP(ctx, ctx->d_mom.alloc((size_t)ctx->mom_doubles), "alloc moments");
-    else ctx->d_mom.release();
+    ctx->d_mom.release();
+    ctx->d_mom_na.release();
+    if (ctx->mom_doubles > 0) {
+        if (!moments_fit(ctx, ctx->mom_doubles)) return PUFE_ERR_OOM;
+        CHECK_HIP(ctx, ctx->d_mom.alloc((size_t)ctx->mom_doubles), "alloc moments");
+    }
     std::vector<CtxDev> self(2, tables_of(ctx));
     // the allocation-free entry may overlap pufe_assemble on another stream: its
     // moments lie behind its partial tiles or in slots of their own
     const size_t tiles = noalloc_bytes(ctx);
-    ctx->d_mom_na.release();
     if (ctx->mom_doubles > 0 && tiles <= kScratchBytes) {
         if (tiles + (size_t)ctx->mom_doubles * sizeof(double) <= kScratchBytes) {
             double *ws = nullptr;
             CHECK_HIP(ctx, scratch_address(ctx->device, &ws), "workspace address");
             self[1].mom = ws + tiles / sizeof(double);
         } else {
+            if (!moments_fit(ctx, ctx->mom_doubles)) return PUFE_ERR_OOM;
             CHECK_HIP(ctx, ctx->d_mom_na.alloc((size_t)ctx->mom_doubles), "alloc moments");
             self[1].mom = ctx->d_mom_na.p;
         }
     }
     CHECK_HIP(ctx, ctx->d_self.upload(self, st), "upload tables");
     return PUFE_OK;
+}
+
+// The moment form's tables and slots, after the other tables of the plan; where
+// there is no memory for them, a plan of direct kernels alone (the partial tiles,
+// the split kernels' items and the projectors' stay as they are).
+static int place_moments(pufe_ctx *ctx, hipStream_t st) {
+    int rc = upload_moments(ctx, st);
+    if (rc != PUFE_ERR_OOM || ctx->mom_doubles == 0) return rc;
+    (void)hipGetLastError();
+    plan_items(ctx, ctx->planned_items, ctx->planned_block, false);
+    if (ctx->lds > kMaxDynLds) return fail(ctx, PUFE_ERR_UNSUPPORTED, "contraction stage does not fit in LDS");
+    CHECK_HIP(ctx, ctx->d_elems.upload(ctx->plan.elems, st), "upload elements");
+    CHECK_HIP(ctx, ctx->d_items.upload_list(ctx->items, st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_items_wide.upload_list(ctx->items_wide, st), "upload work items");
+    CHECK_HIP(ctx, ctx->d_reduce_f64.upload_list(ctx->reduce_f64, st), "upload chunk reduction list");
+    return upload_moments(ctx, st);
 }
 
 // Upload the element table, work items and partial buffer of the current plan.
@@ -1782,12 +1878,13 @@ static int upload_items(pufe_ctx *ctx, hipStream_t st) {
     CHECK_HIP(ctx, ctx->d_reduce_f64.upload_list(ctx->reduce_f64, st), "upload chunk reduction list");
     CHECK_HIP(ctx, ctx->d_partial.alloc((size_t)ctx->part_slots * 512), "alloc partial tiles");
     {
-        int rc = upload_moments(ctx, st);
+        int rc = upload_nonlocal(ctx, st);
+        if (rc == PUFE_OK) rc = place_moments(ctx, st);
         if (rc != PUFE_OK) return rc;
     }
-    ctx->have_bw = ctx->have_bw_direct = false;
+    ctx->have_bw = ctx->have_adj = ctx->have_bw_direct = false;
     ctx->have_poisson = false;
-    return upload_nonlocal(ctx, st);
+    return PUFE_OK;
 }
 
 int pufe_tune(pufe_ctx *ctx, int precision, const char *cache_path) {
