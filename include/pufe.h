@@ -388,7 +388,8 @@ int pufe_lda_xc(int64_t n, const double *d_rho, double *d_vxc, double *d_exc, vo
  * points per LDS stage), keep the fastest and record it in the JSON
  * file cache_path (keyed by GPU architecture, precision and problem
  * signature; NULL = no cache).  A cached entry is applied without timing.
- * Synchronous; re-plans the work items of ctx. */
+ * Synchronous; re-plans the work items of ctx.  In FP64, a problem whose elements
+ * all work through moments has no such choice and keeps its plan. */
 int pufe_tune(pufe_ctx *ctx, int precision, const char *cache_path);
 
 /* Batched assembly over several problems (for instance one per lattice

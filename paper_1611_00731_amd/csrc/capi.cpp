@@ -1977,14 +1977,19 @@ int pufe_tune(pufe_ctx *ctx, int precision, const char *cache_path) {
         return PUFE_OK;
     };
     int trc = PUFE_OK;
+    // with every element in moment form all candidates would time the same FP64
+    // launches, and chance would set the K-chunks (the size of the partial tiles,
+    // the order of the projectors' sums): the current choice stays
+    const bool choice = precision != PUFE_PREC_FP64 || !ctx->items.empty() || !ctx->items_wide.empty();
     const int start_block = ctx->tune_block, start_q = ctx->contract_q, start_wide = ctx->wide_tiles;
+    if (!choice) trc = trial(best_items, start_block, start_q, start_wide);
     for (double items : {1024.0, 2048.0, 4096.0, 8192.0, 16384.0})
-        if (trc == PUFE_OK) trc = trial(items, start_block, start_q, start_wide);
-    for (int block = 2; block <= kBlockTiles && trc == PUFE_OK; ++block)
+        if (choice && trc == PUFE_OK) trc = trial(items, start_block, start_q, start_wide);
+    for (int block = 2; choice && block <= kBlockTiles && trc == PUFE_OK; ++block)
         trc = trial(best_items, block, start_q, start_wide);
     for (int qv : {16, 24, 32})
-        if (trc == PUFE_OK) trc = trial(best_items, best_block, qv, start_wide);
-    if (pl.max_nloc > 16 * kWholeMaxTiles)   // elements for the wide kernel
+        if (choice && trc == PUFE_OK) trc = trial(best_items, best_block, qv, start_wide);
+    if (choice && pl.max_nloc > 16 * kWholeMaxTiles)   // elements for the wide kernel
         for (int wide : {kWideTiles, kWideTiles - 1, 0})
             if (trc == PUFE_OK) trc = trial(best_items, best_block, best_q, wide);
     (void)hipEventDestroy(a);
