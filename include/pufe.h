@@ -170,7 +170,7 @@ int pufe_destroy(pufe_ctx *ctx);
  * pointers, non-positive volume, fe_order outside 1..3, l outside 0..3,
  * a <= 0, rc <= 0, n_d < 2),
  * PUFE_ERR_UNSUPPORTED (GEOM refinement of a non-orthorhombic cell, more
- * functions on one element than the kernels hold). */
+ * functions on one element than the kernels hold, 2^32 blocks or more). */
 int pufe_set_problem(pufe_ctx *ctx, const double lattice[9], const int mesh[3], int fe_order,
                      int n_atoms, const double *pos, const int *species, int n_enr,
                      const pufe_enrichment *enr, const pufe_quad *quad);

@@ -93,7 +93,8 @@ struct pufe_ctx {
     DevBuf<GroupDev> d_groups;
     DevBuf<double> d_img, d_pos, d_partial;
     DevBuf<double> d_spl;           // coefficients of the tabulated radials
-    DevBuf<int32_t> d_edof, d_leaf_elem, d_contr, d_brow, d_bcol;
+    DevBuf<int32_t> d_edof, d_leaf_elem, d_brow, d_bcol;
+    DevBuf<int64_t> d_contr;
     DevBuf<int4> d_blocks;
     std::vector<int2> reduce;       // (element, tile pair) of every element with several K-chunks
     std::vector<int2> reduce_f64;   // those of the elements on the direct FP64 kernels

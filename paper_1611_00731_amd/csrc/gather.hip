@@ -95,17 +95,17 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
     const bool live = at < n;
     const int4 e = list[live ? at : n - 1];
     const CtxDev &cx = ctxs[e.w & (kBlockProjected - 1)];
-    const int ncon = e.w >> 27, nfs = cx.kp.nfs, nfe = cx.kp.nfe, p = cx.kp.p;
+    const int ncon = block_count(e), nfs = cx.kp.nfs, nfe = cx.kp.nfe, p = cx.kp.p;
     // lane j holds contribution j: element tiles, corners, lattice shift and
     // the corners' enriched entries
     int64_t base = 0;
     int cc = 0, ca0 = 0, cb0 = 0, shift = 13, sa3 = 0, sb3 = 0;
     if (lane < ncon) {
-        const int con = cx.contr[e.z + lane];
-        const ElemDev &el = cx.elems[con >> 6];
-        const int ca = (con >> 3) & 7, cb = con & 7;
+        const int64_t con = cx.contr[block_first(e) + lane];
+        const ElemDev &el = cx.elems[contr_elem(con)];
+        cc = contr_corners(con);
+        const int ca = cc >> 3, cb = cc & 7;
         base = el.part_base * 512;
-        cc = con & 63;
         ca0 = el.cs[ca] | ((el.cs[ca + 1] - el.cs[ca]) << 16);
         cb0 = el.cs[cb] | ((el.cs[cb + 1] - el.cs[cb]) << 16);
         sa3 = (el.shifts >> (3 * ca)) & 7;
@@ -131,11 +131,12 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
     if (!live) return;
     const double *part = partial1 ? partial1 : cx.partial;
     Out *H = (Out *)(H1 ? H1 : cx.H), *S = (Out *)(H1 ? S1 : cx.S);
-    const int64_t off = cx.bval_off[e.x], offT = cx.bval_off[e.y], nnz = cx.nnz;
-    const int64_t v = cx.brow[e.x], w = cx.bcol[e.x];
+    const int64_t blk = block_index(e), blkT = block_mirror(e);
+    const int64_t off = cx.bval_off[blk], offT = cx.bval_off[blkT], nnz = cx.nnz;
+    const int64_t v = cx.brow[blk], w = cx.bcol[blk];
     const int bv = (int)(cx.dof_off[v + 1] - cx.dof_off[v]), bw = (int)(cx.dof_off[w + 1] - cx.dof_off[w]);
-    const bool mirror = e.x != e.y;
-    const bool proj = NL && (e.w & kBlockProjected) != 0;
+    const bool mirror = blk != blkT;
+    const bool proj = NL && block_projected(e);
     const int dofs = bv + bw, nst = proj && n_pfun * dofs <= kGatherStage ? n_pfun * dofs : 0;
     double2 *sF = sFs[NL ? threadIdx.x >> 6 : 0];
     const int64_t v0 = cx.dof_off[v], w0 = cx.dof_off[w];

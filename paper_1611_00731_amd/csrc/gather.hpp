@@ -11,9 +11,8 @@ namespace pufe {
 constexpr int kMaxBlockElems = 8;   // elements that hold both vertices of a block
 
 // H and S of the k-points kps: every stored block of the listed problems
-// written once.  list: (block (v, w) with v <= w, block (w, v), its first
-// contribution, problem | projectors couple the block << 26 | contributions << 27),
-// contributions element << 6 | corner of v << 3 | corner of w in element order.  partial, H, S: the buffers
+// written once.  list: entries of block_pack with the problem added to w, blocks
+// (v, w) with v <= w; contributions of contr_pack in element order.  partial, H, S: the buffers
 // of a single-problem call (partial null: each problem's own, also H and S);
 // bloch: the element matrices hold real and imaginary rows.  f (null: none; else
 // of a single problem): the projector sums f[(k n_pfun + J) n_dof + i] with the

@@ -306,7 +306,7 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         auto b = pl.bcol.begin() + pl.brow_ptr[v], e = pl.bcol.begin() + pl.brow_ptr[v + 1];
         return std::lower_bound(b, e, (int32_t)w) - pl.bcol.begin();
     };
-    std::vector<int32_t> elem_block((size_t)pl.nel * 64);   // block of every element's corner pairs
+    std::vector<uint32_t> elem_block((size_t)pl.nel * 64);   // block of every element's corner pairs
     // the blocks a projector function couples
     std::vector<char> nl_block(pl.n_pfun > 0 ? pl.bcol.size() : 0, 0);
     if (pl.n_pfun > 0)
@@ -355,7 +355,7 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
             el.bw[ca] = (int32_t)(pl.dof_off[cv[ca] + 1] - pl.dof_off[cv[ca]]);
             for (int cb = 0; cb < 8; ++cb) {
                 const int64_t b = block_index(cv[ca], cv[cb]);
-                elem_block[64 * e + ca * 8 + cb] = (int32_t)b;
+                elem_block[64 * e + ca * 8 + cb] = (uint32_t)b;
                 el.blk[ca * 8 + cb] = pl.bval_off[b];
             }
         }
@@ -542,18 +542,19 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
     // blocks first
     {
         const int64_t nnzb = (int64_t)pl.bcol.size();
-        if (pl.nel >= (int64_t)1 << 25 || nnzb >= (int64_t)1 << 31) { err = "too many elements"; return PUFE_ERR_UNSUPPORTED; }
-        std::vector<int32_t> first(nnzb + 1, 0), mirror(nnzb, -1);
-        auto upper = [&](int32_t b) { return pl.brow[b] <= pl.bcol[b]; };
+        if (nnzb >= (int64_t)1 << 32) { err = "2^32 blocks and more are not supported"; return PUFE_ERR_UNSUPPORTED; }
+        std::vector<int64_t> first(nnzb + 1, 0);   // at most 36 contributions per element: below 2^32
+        std::vector<int64_t> mirror(nnzb, -1);
+        auto upper = [&](int64_t b) { return pl.brow[b] <= pl.bcol[b]; };
         for (size_t k = 0; k < elem_block.size(); ++k)
-            if (upper(elem_block[k])) ++first[elem_block[k] + 1];
+            if (upper(elem_block[k])) ++first[(int64_t)elem_block[k] + 1];
         for (int64_t k = 0; k < nnzb; ++k) first[k + 1] += first[k];
         pl.contr.assign(first[nnzb], 0);
-        std::vector<int32_t> at(first.begin(), first.end() - 1);
+        std::vector<int64_t> at(first.begin(), first.end() - 1);
         for (size_t k = 0; k < elem_block.size(); ++k) {
-            const int32_t b = elem_block[k];
+            const int64_t b = elem_block[k];
             if (!upper(b)) continue;
-            pl.contr[at[b]++] = (int32_t)k;   // element << 6 | corner of v << 3 | corner of w
+            pl.contr[at[b]++] = contr_pack((int64_t)(k >> 6), (int)(k >> 3) & 7, (int)k & 7);
             mirror[b] = elem_block[(k & ~(size_t)63) | (k & 7) << 3 | ((k >> 3) & 7)];
         }
         // by the power of two of their work (at most 8 contributions, none for
@@ -565,14 +566,14 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         };
         int64_t start[66] = {};
         for (int64_t b = 0; b < nnzb; ++b)
-            if (upper((int32_t)b)) ++start[65 - work(b)];
+            if (upper(b)) ++start[65 - work(b)];
         for (int l = 1; l < 66; ++l) start[l] += start[l - 1];
         pl.blocks.assign(start[65], make_int4(0, 0, 0, 0));
         for (int64_t b = 0; b < nnzb; ++b) {
-            if (!upper((int32_t)b)) continue;
+            if (!upper(b)) continue;
             const int64_t t = mirror[b] >= 0 ? mirror[b] : block_index(pl.bcol[b], pl.brow[b]);
-            const int nl = nl_block.empty() || !nl_block[b] ? 0 : kBlockProjected;
-            pl.blocks[start[64 - work(b)]++] = make_int4((int)b, (int)t, first[b], ((first[b + 1] - first[b]) << 27) | nl);
+            pl.blocks[start[64 - work(b)]++] =
+                block_pack(b, t, first[b], (int)(first[b + 1] - first[b]), !nl_block.empty() && nl_block[b]);
         }
     }
 

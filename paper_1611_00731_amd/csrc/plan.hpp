@@ -52,7 +52,7 @@ struct Plan {
     int32_t n_colors = 0;           // classes of elements that share no vertex
     // assembly: the (element, corner, corner) triples of every block with
     // v <= w, element by element, and one entry per such block (see gather.hpp)
-    std::vector<int32_t> contr;
+    std::vector<int64_t> contr;
     std::vector<int4> blocks;
     int max_nloc = 0, max_nfun = 0, max_ngrp = 0;
     int max_l = 0;                  // largest angular momentum of any descriptor

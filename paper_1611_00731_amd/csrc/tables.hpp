@@ -83,6 +83,27 @@ static inline __host__ __device__ int32_t edof_pack(int corner, int f, int slot)
     return corner | (f << 3) | (slot << 11);
 }
 
+// Contribution of an element to a block of the assembly: its corners cv and cw are
+// the block's vertices.  Assembly list entry of a block: the blocks (v, w) and
+// (w, v) and its first contribution (32 bits unsigned each), and in w the problem,
+// whether projectors couple the block, and the number of contributions (at most 8).
+static inline __host__ __device__ int64_t contr_pack(int64_t elem, int cv, int cw) { return elem << 6 | cv << 3 | cw; }
+static inline __host__ __device__ int64_t contr_elem(int64_t c) { return c >> 6; }
+static inline __host__ __device__ int contr_corners(int64_t c) { return (int)(c & 63); }
+static inline __host__ __device__ int4 block_pack(int64_t b, int64_t mirror, int64_t first, int n, bool projected) {
+    int4 e;
+    e.x = (int)(uint32_t)b;
+    e.y = (int)(uint32_t)mirror;
+    e.z = (int)(uint32_t)first;
+    e.w = n << 27 | (projected ? kBlockProjected : 0);
+    return e;
+}
+static inline __host__ __device__ int64_t block_index(const int4 &e) { return (int64_t)(uint32_t)e.x; }
+static inline __host__ __device__ int64_t block_mirror(const int4 &e) { return (int64_t)(uint32_t)e.y; }
+static inline __host__ __device__ int64_t block_first(const int4 &e) { return (int64_t)(uint32_t)e.z; }
+static inline __host__ __device__ bool block_projected(const int4 &e) { return (e.w & kBlockProjected) != 0; }
+static inline __host__ __device__ int block_count(const int4 &e) { return e.w >> 27; }
+
 // A contraction work item: one element, one row block and one column block of
 // 16x16 tiles, one range of octree leaves (a K-chunk).
 struct ItemDev {
@@ -152,7 +173,8 @@ struct CtxDev {
     double *partial;
     double *mom;         // moment slots
     // block layout and the elements of every block (assembly)
-    const int32_t *contr, *brow, *bcol;
+    const int64_t *contr;
+    const int32_t *brow, *bcol;
     const int64_t *bval_off, *dof_off;
     void *H, *S;
     int64_t nnz;
