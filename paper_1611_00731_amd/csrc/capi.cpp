@@ -14,6 +14,7 @@
 #include "adjoint.hpp"
 #include "backward.hpp"
 #include "bloch.hpp"
+#include "forms.hpp"
 #include "gather.hpp"
 #include "kernels.hpp"
 #include "moments.hpp"
@@ -466,14 +467,12 @@ static void plan_moments(pufe_ctx *c) {
     c->mom_reduce.clear();
     c->mom_expand.clear();
     c->mom_doubles = 0;
-    if (c->mom_off) {
-        for (ElemDev &el : pl.elems) {
-            el.mchunk = el.fchunk = 0;
-            el.mom_base = el.ff_base = 0;
-            el.nt = (el.nfun + 3) / 4;
-        }
-        return;
+    for (ElemDev &el : pl.elems) {
+        el.mchunk = el.fchunk = 0;
+        el.mom_base = el.ff_base = 0;
+        el.nt = (el.nfun + 3) / 4;
     }
+    if (c->mom_off || p > 2) return;   // the serendipity functions stay with the direct kernels
     int nimg = 0;
     for (const ElemDev &el : pl.elems)
         if (el.ngrp > 0) {
@@ -486,53 +485,80 @@ static void plan_moments(pufe_ctx *c) {
         MomStage st{0, 0, 0};
     };
     std::vector<Kind> kinds(kMaxFun / 4 + 1);
-    std::vector<double> cost(pl.nel, 0.0);
-    double total = 0.0, fe_cost = 0.0, saved = 0.0;
+    FormModel model;
+    model.el.resize(pl.nel);
+    model.n3 = pl.kp.n3;
+    model.nfun = pl.max_nfun;
+    model.nimg = pl.max_img;
+    const bool general = !pl.spl.empty() || pl.bloch;
+    model.moment[0] *= pl.kp.skew ? 1.30 : (general ? 1.08 : 1.0);
+    model.moment[1] *= pl.kp.skew ? 1.73 : (general ? 1.08 : 1.0);
+    std::vector<char> able(pl.nel, 0), none(pl.nel, 0);
+    double work = 0.0;
     for (int64_t e = 0; e < pl.nel; ++e) {
-        ElemDev &el = pl.elems[e];
-        el.mchunk = 0;
-        el.mom_base = 0;
-        el.nt = (el.nfun + 3) / 4;
-        if (p > 2) continue;   // the serendipity functions are no tensor products
-        Kind &kd = kinds[el.nt];
+        const ElemDev &el = pl.elems[e];
         const MomCost m = mom_cost_of(pl, el);
-        if (el.nt > 0) {
-            if (kd.tab < 0) {
-                kd.st = mom_stage(el.nt, nimg, n, p, mom_waves(el.nt));
-                kd.tab = (int)c->mom_tasks.size();
-                kd.items = mom_wave_tasks(el.nt, mom_waves(el.nt), m, c->mom_tasks);
-            }
-            if (kd.st.planes == 0) continue;
+        Kind &kd = kinds[el.nt];
+        if (el.nt > 0 && kd.tab < 0) {
+            kd.st = mom_stage(el.nt, nimg, n, p, mom_waves(el.nt));
+            kd.tab = (int)c->mom_tasks.size();
+            kd.items = mom_wave_tasks(el.nt, mom_waves(el.nt), m, c->mom_tasks);
         }
-        const double per_point = mom_cost_total(m, el.nt, kd.items);
-        // the direct kernels: five 16x16x4 MFMAs of 64 cycles per tile pair
-        // and 4 points, the rows' VALU work about once more on top.  Measured
-        // over issue-bound time: about 2.0 there, 1.7 here
-        const int T = (el.nloc + 15) / 16;
-        const double direct = 2.0 * (T * (T + 1) / 2 * 80.0 + 3.0 * el.nloc + m.fill), moment = 1.7 * (per_point + m.ff);
-        if (moment > direct) continue;
-        saved += (direct - moment) * pl.kp.n3 * (double)(el.leaf_end - el.leaf_off);
-        el.mchunk = 1;
-        fe_cost = m.ff;
-        cost[e] = per_point * pl.kp.n3 * (double)(el.leaf_end - el.leaf_off);
-        total += cost[e] + m.ff * pl.kp.n3 * (double)(el.leaf_end - el.leaf_off);
+        able[e] = el.nt == 0 || kd.st.planes > 0;
+        FormElem &f = model.el[e];
+        f.leaves = (double)(el.leaf_end - el.leaf_off);
+        f.pts = f.leaves * pl.kp.n3;
+        f.fill = m.fill;
+        f.per_point = el.nt > 0 ? mom_cost_total(m, el.nt, kd.items) : 0.0;
+        f.ff = m.ff;
+        f.nloc = el.nloc;
+        f.nt = el.nt;
+        f.nfun = el.nfun;
+        f.tiles = (el.nloc + 15) / 16;
+        f.pairs = 0.5 * f.tiles * (f.tiles + 1.0);
+        f.items = kd.items;
+        f.stages = kd.st.planes > 0 ? (n + kd.st.planes - 1) / kd.st.planes : 0;
+        f.buffers = kd.st.buffers;
+        work += f.pairs * f.pts;
     }
-    // the moment form takes two to four launches more; below about 60 us of work
-    // saved on the whole chip (1024 SIMDs) a problem stays with the direct kernels.
-    // Measured per assembly, direct and in moment form: below the line 127 and 221
-    // us (a few dozen elements on a sheared mesh), above it 1.0 and 0.63 ms (512
-    // elements, 1.52 M points)
-    if (saved < 60e-6 * 2.4e9 * 1024.0) {
-        for (ElemDev &el : pl.elems) el.mchunk = el.fchunk = 0;
+    for (FormElem &f : model.el)   // the default K-chunks of the direct kernels, whatever the tuner has chosen
+        f.chunks = std::max(1.0, std::min(f.leaves, std::round(f.pairs * f.pts * 4096.0 / std::max(work, 4096.0))));
+    // every element that can, those whose own work is less that way, or none:
+    // the fastest by the model, the direct kernels unless another is faster by 6 %
+    // (measured over the 360 problems: no choice but four costs more than 2 % over
+    // the direct kernels, the worst 13 %; without that margin eleven and 32 %)
+    std::vector<char> some(pl.nel, 0);
+    const double d = model.dur(able);
+    for (int64_t e = 0; e < pl.nel; ++e) some[e] = able[e] && model.cheaper(model.el[e], d);
+    const std::vector<char> *best = &none;
+    double t = 0.94 * model.time(none);
+    for (const std::vector<char> *m : {&able, &some}) {
+        if (std::find(m->begin(), m->end(), (char)1) == m->end()) continue;
+        const double tm = model.time(*m);
+        if (tm < t) {
+            t = tm;
+            best = m;
+        }
+    }
+    if (best == &none) {
+        c->mom_tasks.clear();
         return;
+    }
+    std::vector<double> cost(pl.nel, 0.0);
+    double total = 0.0, fe_cost = 0.0;
+    for (int64_t e = 0; e < pl.nel; ++e) {
+        if (!(*best)[e]) continue;
+        const FormElem &f = model.el[e];
+        pl.elems[e].mchunk = 1;
+        fe_cost = f.ff;
+        cost[e] = f.per_point * f.pts;
+        total += cost[e] + f.ff * f.pts;
     }
     // chunks: about four rounds of work groups over the chip, none shorter
     // than 40,000 cycles (the start of a work group and its moments' stores)
     const double dur = std::max(total / (1024.0 * 4.0), 40000.0);
     for (int64_t e = 0; e < pl.nel; ++e) {
         ElemDev &el = pl.elems[e];
-        el.fchunk = 0;
-        el.ff_base = 0;
         if (el.mchunk == 0) continue;
         const Kind &kd = kinds[el.nt];
         const int w = mom_waves(el.nt) == 4 ? 0 : 1, slots = mom_slots(el.nt), nw = w ? 8 : 4;

@@ -21,7 +21,7 @@ WORKSPACE = 64 * MIB
 CASES = {
     # mesh, order, Gauss points, re; a bound of the sums' bytes from above or below
     "workspace": ((6, 6, 6), 2, 10, 1.6, 32 * MIB, True),
-    "own buffer": ((10, 10, 10), 2, 6, 2.4, WORKSPACE, False),
+    "own buffer": ((10, 10, 10), 2, 10, 2.4, WORKSPACE, False),
 }
 
 

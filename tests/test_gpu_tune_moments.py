@@ -18,7 +18,7 @@ import paper_1611_00731_amd as P  # noqa: E402
 
 
 def tuned(limit, cache, precision="fp64"):
-    prob = W.small("lih", mesh=(6, 6, 6), fe_order=2, levels=1, n=8, a=7.0, rc=2.6, re=1.6)
+    prob = W.small("one", mesh=(8, 8, 8), fe_order=2, levels=2, n=7, a=6.0, rc=2.5, re=1.4)
     p = P.Problem(prob)
     P.pufe_set_moment_limit(p.ctx, limit)
     p.setup()
