@@ -1214,7 +1214,7 @@ static int assemble_bloch(pufe_ctx *ctx, const double *d_V, const double *kpts, 
                                                 ctx->d_dof_el_off.p, ctx->d_dof_el.p, ctx->d_Fp.p, one, pl.n_pfun,
                                                 ndof, ctx->d_nlf.p, st),
                           "projector sums");
-            CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), ctx->d_partial.p, H, S, one,
+            CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, pl.gather, ctx->d_partial.p, H, S, one,
                                          out_dtype, true, with_nl ? ctx->d_nlf.p : nullptr, ctx->d_pfun_h.p, pl.n_pfun,
                                          ndof, st),
                       "assembly");
@@ -1255,7 +1255,7 @@ static int assemble_impl(pufe_ctx *ctx, const double *d_V, const double *kpts, i
                                             ctx->d_dof_el_off.p, ctx->d_dof_el.p, ctx->d_Fp.p, kps, pl.n_pfun, ndof,
                                             ctx->d_nlf.p, st),
                       "projector sums");
-        CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, (int)pl.blocks.size(), partial, H, S, kps, out_dtype,
+        CHECK_HIP(ctx, launch_gather(ctx->d_self.p, ctx->d_blocks.p, pl.gather, partial, H, S, kps, out_dtype,
                                      false, with_nl ? ctx->d_nlf.p : nullptr, ctx->d_pfun_h.p, pl.n_pfun, ndof, st),
                   "assembly");
     }
@@ -2067,6 +2067,7 @@ struct pufe_batch {
     int device = 0;
     std::vector<ItemDev> items, items_split;
     std::vector<int4> blocks;               // assembly list of all problems (gather.hpp)
+    GatherSizes gather;
     // FP64 items in up to kBatchClasses classes, each a persistent launch of
     // its own (items [item_off[c], item_off[c + 1])): per stage length, the
     // problems whose combined stage fits two work groups per CU, then the rest
@@ -2214,10 +2215,6 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
         b->max_l = std::max(b->max_l, c->plan.max_l);
         b->gen = b->gen || general_variant(c->plan);
         if (!c->items_wide.empty()) b->lds_wide = std::max(b->lds_wide, c->lds_wide);
-        for (int4 r : c->plan.blocks) {
-            r.w |= i;
-            b->blocks.push_back(r);
-        }
         for (const int2 &r : c->reduce) b->reduce.push_back(make_int4(i, r.x, r.y, 0));
         for (const int2 &r : c->reduce_f64) b->reduce_f64.push_back(make_int4(i, r.x, r.y, 0));
         for (int4 r : c->mom_reduce) {
@@ -2228,6 +2225,21 @@ int pufe_batch_create(pufe_batch **out, pufe_ctx *const *ctxs, int n) {
             r.w = i;
             b->mom_expand.push_back(r);
         }
+    }
+    // assembly list: the small blocks of the problems that list them apart go last
+    for (int part = 0; part < 2; ++part)
+        for (int i = 0; i < n; ++i) {
+            const Plan &pl = ctxs[i]->plan;
+            const size_t cut = pl.blocks.size() - pl.gather.small;
+            for (size_t k = part ? cut : 0; k < (part ? pl.blocks.size() : cut); ++k) {
+                b->blocks.push_back(pl.blocks[k]);
+                b->blocks.back().w |= i;
+            }
+        }
+    b->gather.blocks = (int)b->blocks.size();
+    for (int i = 0; i < n; ++i) {
+        b->gather.small += ctxs[i]->plan.gather.small;
+        b->gather.max_entries = std::max(b->gather.max_entries, ctxs[i]->plan.gather.max_entries);
     }
     // moment items of all problems, longest first, over the joined wave tasks
     for (int i = 0; i < n; ++i) b->skew = b->skew || ctxs[i]->plan.kp.skew != 0;
@@ -2411,7 +2423,7 @@ int pufe_batch_assemble(pufe_batch *b, const double *const *d_V, const double *k
         if (e == hipSuccess && precision != PUFE_PREC_FP64)
             e = launch_chunk_reduce_batch(b->d_ctxs.p, b->d_reduce.p, (int)b->reduce.size(), b->cap);
         if (e == hipSuccess)
-            e = launch_gather(b->d_ctxs.p, b->d_blocks.p, (int)b->blocks.size(), nullptr, nullptr, nullptr, kps, out_dtype,
+            e = launch_gather(b->d_ctxs.p, b->d_blocks.p, b->gather, nullptr, nullptr, nullptr, kps, out_dtype,
                               false, nullptr, nullptr, 0, 0, b->cap);
         hipGraph_t g = nullptr;
         hipError_t e2 = hipStreamEndCapture(b->cap, &g);

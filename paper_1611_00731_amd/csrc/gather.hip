@@ -4,6 +4,8 @@
 //   H[g_a][g_b] = sum over elements of conj(p_a) p_b H_e[a][b],
 // and written once.  One wave per pair of blocks (v, w), (w, v): the matrices
 // are Hermitian, so the second block is the conjugate transpose of the first.
+// Where there are few blocks, several waves share the entries of each; where there
+// are very many small ones, a wave takes eight blocks.
 //
 // Bound by writing H and S.  Scattering element by element instead needs the
 // outputs zeroed, two reads and two writes of each entry per element that
@@ -16,6 +18,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gather.hpp"
@@ -83,15 +86,22 @@ constexpr int kGatherStage = 576;
 // after 130 us of this kernel, 248 us together now.  A wave stages its block's
 // rows of f in LDS, k-point by k-point; what does not fit is read through the
 // caches.
-template <int DT, bool BLOCH, bool NL>
+// GL lanes work on a block: a wave, or eight of its lanes.
+template <int DT, bool BLOCH, bool NL, int GL>
 __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ ctxs, const int4 *__restrict__ list, int n,
                                                      const double *__restrict__ partial1, void *H1, void *S1,
                                                      const KPoints kps, const double2 *__restrict__ f,
                                                      const double *__restrict__ pfun_h, int n_pfun, int64_t n_dof) {
     typedef typename OutType<DT>::type Out;
-    __shared__ double2 sFs[NL ? 4 : 1][NL ? kGatherStage : 1];
+    constexpr bool WAVE = GL == 64;
+    __shared__ double2 sFs[NL && WAVE ? 4 : 1][NL && WAVE ? kGatherStage : 1];
     __shared__ double2 sZ[kMaxKPerLaunch * 27];   // exp(2 pi i kappa . dn), dn = (t % 3, t / 3 % 3, t / 9) - 1
-    const int lane = threadIdx.x & 63, at = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    // contributions of the blocks of eight lanes: the lanes of a block leave its loop
+    // at different times, so they read each other's through LDS
+    __shared__ int64_t sBase[WAVE ? 1 : 256];
+    __shared__ int sCon[WAVE ? 1 : 256][3];
+    const int lane = threadIdx.x & (GL - 1);
+    const int at = WAVE ? __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)) : blockIdx.x * 32 + threadIdx.x / 8;
     const bool live = at < n;
     const int4 e = list[live ? at : n - 1];
     const CtxDev &cx = ctxs[e.w & (kBlockProjected - 1)];
@@ -117,7 +127,14 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
     // Bloch-periodic enrichment, the boundary phase on classical rows only).  Real
     // output of the periodic form has none at all: kappa is an integer, of any size,
     // and the cosine of a rounded 2 pi kappa is not one
-    const bool wraps = (BLOCH || DT != 2) && __any(lane < ncon && (BLOCH ? (sa3 | sb3) != 0 : shift != 13));
+    const bool mine = (BLOCH || DT != 2) && lane < ncon && (BLOCH ? (sa3 | sb3) != 0 : shift != 13);
+    const bool wraps = WAVE ? __any(mine) : ((__ballot(mine) >> (threadIdx.x & 56)) & 255u) != 0;
+    if (!WAVE) {
+        sBase[threadIdx.x] = base;
+        sCon[threadIdx.x][0] = cc | (shift << 6) | (sa3 << 11) | (sb3 << 14);
+        sCon[threadIdx.x][1] = ca0;
+        sCon[threadIdx.x][2] = cb0;
+    }
     if (__syncthreads_or(live && wraps)) {
         for (int i = threadIdx.x; i < kps.nk * 27; i += 256) {
             const int k = i / 27, t = i - 27 * k;
@@ -129,6 +146,14 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
         __syncthreads();
     }
     if (!live) return;
+    const int first = threadIdx.x & ~(GL - 1);   // contribution j of the block, in lane j or in LDS
+    auto con_base = [&](int j) { return WAVE ? read_lane64(base, j) : sBase[first + j]; };
+    auto con_corners = [&](int j) { return WAVE ? __builtin_amdgcn_readlane(cc, j) : sCon[first + j][0] & 63; };
+    auto con_a = [&](int j) { return WAVE ? __builtin_amdgcn_readlane(ca0, j) : sCon[first + j][1]; };
+    auto con_b = [&](int j) { return WAVE ? __builtin_amdgcn_readlane(cb0, j) : sCon[first + j][2]; };
+    auto con_shift = [&](int j) { return WAVE ? __builtin_amdgcn_readlane(shift, j) : (sCon[first + j][0] >> 6) & 31; };
+    auto con_sa = [&](int j) { return WAVE ? __builtin_amdgcn_readlane(sa3, j) : (sCon[first + j][0] >> 11) & 7; };
+    auto con_sb = [&](int j) { return WAVE ? __builtin_amdgcn_readlane(sb3, j) : (sCon[first + j][0] >> 14) & 7; };
     const double *part = partial1 ? partial1 : cx.partial;
     Out *H = (Out *)(H1 ? H1 : cx.H), *S = (Out *)(H1 ? S1 : cx.S);
     const int64_t blk = block_index(e), blkT = block_mirror(e);
@@ -137,11 +162,11 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
     const int bv = (int)(cx.dof_off[v + 1] - cx.dof_off[v]), bw = (int)(cx.dof_off[w + 1] - cx.dof_off[w]);
     const bool mirror = blk != blkT;
     const bool proj = NL && block_projected(e);
-    const int dofs = bv + bw, nst = proj && n_pfun * dofs <= kGatherStage ? n_pfun * dofs : 0;
-    double2 *sF = sFs[NL ? threadIdx.x >> 6 : 0];
+    const int dofs = bv + bw, nst = WAVE && proj && n_pfun * dofs <= kGatherStage ? n_pfun * dofs : 0;
+    double2 *sF = sFs[NL && WAVE ? threadIdx.x >> 6 : 0];
     const int64_t v0 = cx.dof_off[v], w0 = cx.dof_off[w];
     for (int kn = 0; kn < (NL ? kps.nk : 1); ++kn) {
-        if (NL && nst > 0) {
+        if (NL && WAVE && nst > 0) {
             const double2 *fk = f + (int64_t)kn * n_pfun * n_dof;
             __builtin_amdgcn_wave_barrier();
             for (int i = lane; i < nst; i += 64) {
@@ -151,7 +176,7 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        for (int i = lane; i < bv * bw; i += 64) {
+        for (int i = lane + GL * blockIdx.y; i < bv * bw; i += GL * gridDim.y) {
             const int sa = i / bw, sb = i - sa * bw;
             const int64_t o = off + i, oT = offT + (int64_t)sb * bv + sa;
             auto put = [&](int k, double hr, double hi, double sr, double si) {
@@ -181,11 +206,10 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
             };
             // one element's value: hr + i hi, sr + i si before the phase
             auto value = [&](int j, double *h, double *s) -> bool {
-                const int c = __builtin_amdgcn_readlane(cc, j), ua = __builtin_amdgcn_readlane(ca0, j),
-                          ub = __builtin_amdgcn_readlane(cb0, j);
+                const int c = con_corners(j), ua = con_a(j), ub = con_b(j);
                 const int a = local_of(p, nfs, nfe, c >> 3, sa, ua & 0xffff), b = local_of(p, nfs, nfe, c & 7, sb, ub & 0xffff);
                 if (a < 0 || b < 0) return false;
-                const double *t = part + read_lane64(base, j);
+                const double *t = part + con_base(j);
                 const int64_t ab = entry_of(a, b);
                 h[0] = t[ab];
                 s[0] = t[ab + 256];
@@ -232,9 +256,9 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
                 for (int j = 0; j < ncon; ++j) {
                     double h[2], s[2];
                     if (!value(j, h, s)) continue;
-                    int t = __builtin_amdgcn_readlane(shift, j);
+                    int t = con_shift(j);
                     if (BLOCH) {
-                        const int za = sa < nfs ? __builtin_amdgcn_readlane(sa3, j) : 0, zb = sb < nfs ? __builtin_amdgcn_readlane(sb3, j) : 0;
+                        const int za = sa < nfs ? con_sa(j) : 0, zb = sb < nfs ? con_sb(j) : 0;
                         auto dn = [&](int d) { return ((zb >> d) & 1) - ((za >> d) & 1) + 1; };
                         t = dn(0) + 3 * dn(1) + 9 * dn(2);
                     }
@@ -262,19 +286,26 @@ __global__ __launch_bounds__(256) void gather_kernel(const CtxDev *__restrict__ 
     }
 }
 
-hipError_t launch_gather(const CtxDev *ctxs, const int4 *list, int n, const double *partial, void *H, void *S,
+hipError_t launch_gather(const CtxDev *ctxs, const int4 *list, const GatherSizes &sz, const double *partial, void *H, void *S,
                          const KPoints &kps, int out_dtype, bool bloch, const double2 *f, const double *pfun_h, int n_pfun,
                          int64_t n_dof, hipStream_t st) {
-    if (n == 0) return hipSuccess;
-    auto go = [&](auto *k) {
-        k<<<(n + 3) / 4, 256, 0, st>>>(ctxs, list, n, partial, H, S, kps, f, pfun_h, n_pfun, n_dof);
+    const int n = sz.blocks - sz.small;
+    // waves per block: until about 8192 are in flight (32 a CU), each with entries
+    // (48 elements of 283 functions: 115 us with a wave per block, 22 with several;
+    // element by element in eight launches 82)
+    const int parts = n > 0 ? std::max(1, std::min((sz.max_entries + 63) / 64, 8192 / n)) : 1;
+    auto go = [&](auto *k, auto *ks) {
+        if (n > 0)
+            k<<<dim3((n + 3) / 4, parts), 256, 0, st>>>(ctxs, list, n, partial, H, S, kps, f, pfun_h, n_pfun, n_dof);
+        if (sz.small > 0)
+            ks<<<(sz.small + 31) / 32, 256, 0, st>>>(ctxs, list + n, sz.small, partial, H, S, kps, f, pfun_h, n_pfun, n_dof);
         return hipGetLastError();
     };
     auto type = [&](auto bl, auto nl) {
         constexpr bool B = decltype(bl)::value, N = decltype(nl)::value;
-        if (out_dtype == 0) return go(gather_kernel<0, B, N>);
-        if (out_dtype == 1) return go(gather_kernel<1, B, N>);
-        return go(gather_kernel<2, B, N>);
+        if (out_dtype == 0) return go(gather_kernel<0, B, N, 64>, gather_kernel<0, B, N, 8>);
+        if (out_dtype == 1) return go(gather_kernel<1, B, N, 64>, gather_kernel<1, B, N, 8>);
+        return go(gather_kernel<2, B, N, 64>, gather_kernel<2, B, N, 8>);
     };
     if (bloch) return f ? type(std::true_type(), std::true_type()) : type(std::true_type(), std::false_type());
     return f ? type(std::false_type(), std::true_type()) : type(std::false_type(), std::false_type());

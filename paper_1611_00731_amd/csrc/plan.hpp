@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "../../include/pufe.h"
+#include "gather.hpp"
 #include "tables.hpp"
 
 namespace pufe {
@@ -54,6 +55,7 @@ struct Plan {
     // v <= w, element by element, and one entry per such block (see gather.hpp)
     std::vector<int64_t> contr;
     std::vector<int4> blocks;
+    GatherSizes gather;
     int max_nloc = 0, max_nfun = 0, max_ngrp = 0;
     int max_l = 0;                  // largest angular momentum of any descriptor
     int max_img = 0;                // most image centres of one element's groups
