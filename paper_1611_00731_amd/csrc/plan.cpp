@@ -542,17 +542,18 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
     // blocks first
     {
         const int64_t nnzb = (int64_t)pl.bcol.size();
-        if (nnzb >= (int64_t)1 << 32) { err = "2^32 blocks and more are not supported"; return PUFE_ERR_UNSUPPORTED; }
-        std::vector<int64_t> first(nnzb + 1, 0);   // at most 36 contributions per element: below 2^32
-        std::vector<int64_t> mirror(nnzb, -1);
+        if (nnzb >= ((int64_t)1 << 32) - 1) { err = "2^32 blocks and more are not supported"; return PUFE_ERR_UNSUPPORTED; }
+        // contributions (at most 36 per element: below 2^32) and mirror of every block
+        constexpr uint32_t kNone = ~(uint32_t)0;
+        std::vector<uint32_t> first(nnzb + 1, 0), mirror(nnzb, kNone);
         auto upper = [&](int64_t b) { return pl.brow[b] <= pl.bcol[b]; };
         for (size_t k = 0; k < elem_block.size(); ++k)
             if (upper(elem_block[k])) ++first[(int64_t)elem_block[k] + 1];
         for (int64_t k = 0; k < nnzb; ++k) first[k + 1] += first[k];
         pl.contr.assign(first[nnzb], 0);
-        std::vector<int64_t> at(first.begin(), first.end() - 1);
+        std::vector<uint32_t> at(first.begin(), first.end() - 1);
         for (size_t k = 0; k < elem_block.size(); ++k) {
-            const int64_t b = elem_block[k];
+            const uint32_t b = elem_block[k];
             if (!upper(b)) continue;
             pl.contr[at[b]++] = contr_pack((int64_t)(k >> 6), (int)(k >> 3) & 7, (int)k & 7);
             mirror[b] = elem_block[(k & ~(size_t)63) | (k & 7) << 3 | ((k >> 3) & 7)];
@@ -560,25 +561,25 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         // by the power of two of their work (at most 8 contributions, none for
         // blocks that only projectors couple)
         auto area = [&](int64_t b) { return pl.bval_off[b + 1] - pl.bval_off[b]; };
+        std::vector<int8_t> work(nnzb, 0);
         int64_t small = 0, most = 0;
         for (int64_t b = 0; b < nnzb; ++b) {
             if (!upper(b)) continue;
-            small += area(b) <= kSmallBlock;
-            most = std::max(most, area(b));
+            const int64_t n = area(b), x = n * (first[b + 1] - first[b] + 1);
+            work[b] = (int8_t)(63 - __builtin_clzll((uint64_t)x));
+            small += n <= kSmallBlock;
+            most = std::max(most, n);
         }
         // very many small blocks go last, in a launch of their own: a wave takes
         // eight of them (13,824 vertices of one function: gather 229 -> 63 us, 4096: 73 ->
         // 26); fewer do not fill the chip that way
         if (small < kManySmall) small = 0;
-        auto work = [&](int64_t b) {
-            if (small > 0 && area(b) <= kSmallBlock) return -1;
-            int l = 0;
-            for (int64_t x = area(b) * (first[b + 1] - first[b] + 1); x > 1; x >>= 1) ++l;
-            return l;
-        };
         int64_t start[67] = {};
-        for (int64_t b = 0; b < nnzb; ++b)
-            if (upper(b)) ++start[65 - work(b)];
+        for (int64_t b = 0; b < nnzb; ++b) {
+            if (!upper(b)) continue;
+            if (small > 0 && area(b) <= kSmallBlock) work[b] = -1;
+            ++start[65 - work[b]];
+        }
         for (int l = 1; l < 67; ++l) start[l] += start[l - 1];
         pl.blocks.assign(start[66], make_int4(0, 0, 0, 0));
         pl.gather.blocks = (int)pl.blocks.size();
@@ -586,8 +587,8 @@ int build_plan(const Problem &pr, Plan &pl, std::string &err) {
         pl.gather.max_entries = (int)most;
         for (int64_t b = 0; b < nnzb; ++b) {
             if (!upper(b)) continue;
-            const int64_t t = mirror[b] >= 0 ? mirror[b] : block_index(pl.bcol[b], pl.brow[b]);
-            pl.blocks[start[64 - work(b)]++] =
+            const int64_t t = mirror[b] != kNone ? mirror[b] : block_index(pl.bcol[b], pl.brow[b]);
+            pl.blocks[start[64 - work[b]]++] =
                 block_pack(b, t, first[b], (int)(first[b + 1] - first[b]), !nl_block.empty() && nl_block[b]);
         }
     }
