@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libpufe.so")
 OBJ = os.path.join(HERE, "_build")
 SOURCES = ["capi.cpp", "plan.cpp", "kernels.hip", "moments.hip", "expand.hip", "gather.hip", "adjoint.hip", "backward.hip", "split.hip", "aq_error.hip", "nonlocal.hip",
            "bloch.hip", "scf.hip"]
-HEADERS = ["tables.hpp", "plan.hpp", "kernels.hpp", "moments.hpp", "forms.hpp", "gather.hpp", "basis.hpp", "adjoint.hpp", "backward.hpp", "device_common.hpp", "enrich.hpp",
+HEADERS = ["tables.hpp", "plan.hpp", "kernels.hpp", "moments.hpp", "moment_math.hpp", "forms.hpp", "gather.hpp", "basis.hpp", "adjoint.hpp", "backward.hpp", "device_common.hpp", "enrich.hpp",
            "aq_error.hpp", "stage.hpp", "limbs.hpp", "nonlocal.hpp", "bloch.hpp", "scf.hpp"]
 
 FLAGS = [

@@ -36,6 +36,7 @@
 #include "basis.hpp"
 #include "device_common.hpp"
 #include "enrich.hpp"
+#include "moment_math.hpp"
 #include "moments.hpp"
 #include "stage.hpp"
 #include "tables.hpp"
@@ -43,12 +44,6 @@
 namespace pufe {
 
 namespace {
-
-typedef double dbl2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ double mfma4(double a, double b, double c) {
-    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
-}
 
 constexpr int kAdjPair = 108 * 64;   // doubles of a quad: LE, LA (27 each), LB_x, LB_y, LB_z (18 each)
 
@@ -171,20 +166,6 @@ __device__ __forceinline__ double adj_sum_functions(double v, int rep) {
     if (rep < 4) s += rot(s, std::integral_constant<int, 0x128>());   // row_ror:8
     if (rep < 2) s += rot(s, std::integral_constant<int, 0x124>());   // row_ror:4
     return s;
-}
-
-template <int M>
-__device__ __forceinline__ double lagrange_at(int k, double t) {
-    constexpr double h = 2.0 / (M - 1);
-    constexpr double f[5] = {1.0, 1.0, 2.0, 6.0, 24.0};
-    double v = 1.0, d = 1.0;
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-        v *= j == k ? 1.0 : t - (-1.0 + j * h);
-        const double inv = 1.0 / (f[j] * f[M - 1 - j] * (M == 3 ? h * h : (M == 4 ? h * h * h : h * h * h * h)));
-        d = j == k ? ((M - 1 - j) & 1 ? -inv : inv) : d;
-    }
-    return v * d;
 }
 
 // A stage as the wave tasks see it: nyl lines per plane from (z0, y0), planes
@@ -532,7 +513,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                         j -= mixed ? mt.fx : mt.gx;
                         const int m = mixed ? nf : ng, i = j / m, k = j - i * m, d = i < n ? 0 : (i < 2 * n ? 1 : 2);
                         const double x = -1.0 + ((d == 0 ? c[0] : (d == 1 ? c[1] : c[2])) + sGx[i - d * n]) * h;
-                        v = m == 5 ? lagrange_at<5>(k, x) : (m == 4 ? lagrange_at<4>(k, x) : lagrange_at<3>(k, x));
+                        v = m == 5 ? lagrange_equi<5>(k, x) : (m == 4 ? lagrange_equi<4>(k, x) : lagrange_equi<3>(k, x));
                     } else {
                         j -= mt.w;
                         v = sGw[j % n] * (j >= 2 * n ? vol : 1.0);

@@ -354,7 +354,9 @@ int pufe_set_enrichment_phase(pufe_ctx *ctx, int form) {
 
 // Split each element's contraction into K-chunks (ranges of leaves) of about
 // equal MFMA work; the chunking fixes the layout of the partial tiles and does
-// not depend on how the tile pairs of a chunk are grouped into work items.
+// not depend on how the tile pairs of a chunk are grouped into work items.  It is
+// that of the split precisions for every element; in FP64 an element in moment form
+// writes its first slot only.
 static void plan_chunks(pufe_ctx *c, double target_items) {
     Plan &pl = c->plan;
     const int n3 = pl.kp.n3;

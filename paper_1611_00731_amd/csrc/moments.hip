@@ -46,6 +46,7 @@
 #include "basis.hpp"
 #include "device_common.hpp"
 #include "enrich.hpp"
+#include "moment_math.hpp"
 #include "moments.hpp"
 #include "stage.hpp"
 #include "tables.hpp"
@@ -53,10 +54,6 @@
 namespace pufe {
 
 namespace {
-
-__device__ __forceinline__ double mfma4(double a, double b, double c) {
-    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
-}
 
 // 1D tables of one leaf, doubles: x coordinate [n]; y and z polynomials
 // [n][5] (m0 m0, m0 m1, m1 m1, m0, m1); mixed x, y, z [n][p + 2] times the
@@ -78,7 +75,8 @@ struct MomTab {
 // last operand read of a line may touch (never written, so zero), and its
 // stride in doubles: value and gradient of a point are neighbours, and the
 // stride is odd in 16-byte units, so that the eight rows of a 128-bit read
-// phase meet distinct banks.
+// phase start at distinct banks.  Other accesses still conflict: 2.06e9 cycles a
+// launch of the eight-wave groups on 1728 elements of up to 41 functions.
 __host__ __device__ inline int mom_points(int points) { return points + 3; }
 __host__ __device__ inline int mom_stride(int points) { return 4 * mom_points(points) + 2; }
 
@@ -90,8 +88,6 @@ struct MomLane {
     int oa, ob;      // offsets of the row and column operands at the lane's first point
     int k4;
 };
-
-typedef double dbl2 __attribute__((ext_vector_type(2)));
 
 // Value and gradient of one function at one point.
 struct MomOp {
@@ -458,22 +454,6 @@ __device__ __forceinline__ void mom_group(const GroupDev &G, const double *__res
         for (int m = 0; m < NM; ++m)
 #pragma unroll
             for (int c = 0; c < 4; ++c) o[m * MS + c] = 0.0;
-}
-
-// Value at t of Lagrange polynomial k on M equidistant nodes of [-1, 1].
-template <int M>
-__device__ __forceinline__ double lagrange_equi(int k, double t) {
-    constexpr double h = 2.0 / (M - 1);
-    // prod_{j != k} (k - j) h = (-1)^(M - 1 - k) k! (M - 1 - k)! h^(M - 1)
-    constexpr double f[5] = {1.0, 1.0, 2.0, 6.0, 24.0};
-    double v = 1.0, d = 1.0;
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-        v *= j == k ? 1.0 : t - (-1.0 + j * h);
-        const double inv = 1.0 / (f[j] * f[M - 1 - j] * (M == 3 ? h * h : (M == 4 ? h * h * h : h * h * h * h)));
-        d = j == k ? ((M - 1 - j) & 1 ? -inv : inv) : d;
-    }
-    return v * d;
 }
 
 }  // namespace
