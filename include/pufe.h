@@ -242,7 +242,10 @@ int pufe_setup(pufe_ctx *ctx, void *stream);
  * c = c1 + 2 c2 + 4 c3).  The leaves of each element must cover its reference
  * cube exactly once.  Re-plans the work items (a batch created before must be
  * created anew).  Synchronous.  Errors: PUFE_ERR_STATE before pufe_setup,
- * PUFE_ERR_INVALID_ARG for malformed leaves. */
+ * PUFE_ERR_INVALID_ARG for malformed leaves (the context keeps its rule),
+ * PUFE_ERR_UNSUPPORTED for a rule whose work items do not fit, PUFE_ERR_OOM
+ * (after these the context has no rule: until pufe_set_rule gives one that fits, or
+ * pufe_setup the problem's own, the calls that need it return PUFE_ERR_STATE). */
 int pufe_set_rule(pufe_ctx *ctx, int64_t n_leaves, const int32_t *level, const int32_t *ijk,
                   const int64_t *elem_leaf_offset, void *stream);
 

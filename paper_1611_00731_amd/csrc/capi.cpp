@@ -68,6 +68,9 @@ struct pufe_ctx {
     int device = 0;
     std::string err;
     bool have_problem = false, have_setup = false;
+    // what pufe_setup makes for the problem is there; without have_setup the rule and its
+    // plan are not (a call that replaces them failed midway), pufe_set_rule may give them
+    bool have_tables = false;
     Problem prob;
     Plan plan;
     int64_t n_leaves = 0, n_qp = 0;
@@ -271,7 +274,7 @@ int pufe_create(pufe_ctx **out, int device) {
 
 int pufe_destroy(pufe_ctx *ctx) {
     if (!ctx) return PUFE_ERR_INVALID_ARG;
-    if (ctx->have_setup) (void)hipSetDevice(ctx->device);
+    if (ctx->d_leaf_off.p) (void)hipSetDevice(ctx->device);   // it has device buffers
     delete ctx;
     return PUFE_OK;
 }
@@ -310,7 +313,7 @@ int pufe_set_problem(pufe_ctx *ctx, const double lattice[9], const int mesh[3], 
     ctx->prob = std::move(pr);
     ctx->plan = std::move(pl);
     ctx->have_problem = true;
-    ctx->have_setup = false;
+    ctx->have_setup = ctx->have_tables = false;
     ctx->have_bw = ctx->have_adj = ctx->have_bw_direct = false;
     ctx->n_leaves = ctx->n_qp = 0;
     ++ctx->plan_gen;
@@ -320,7 +323,7 @@ int pufe_set_problem(pufe_ctx *ctx, const double lattice[9], const int mesh[3], 
 int pufe_set_projectors(pufe_ctx *ctx, int n, const pufe_projector *proj) {
     if (!ctx) return PUFE_ERR_INVALID_ARG;
     if (!ctx->have_problem) return fail(ctx, PUFE_ERR_STATE, "pufe_set_problem must come first");
-    if (ctx->have_setup) return fail(ctx, PUFE_ERR_STATE, "projectors are set before pufe_setup");
+    if (ctx->have_tables) return fail(ctx, PUFE_ERR_STATE, "projectors are set before pufe_setup");
     if (n < 0 || (n > 0 && !proj)) return fail(ctx, PUFE_ERR_INVALID_ARG, "null pointer or negative count");
     Problem pr = ctx->prob;
     pr.proj.assign(proj, proj + n);
@@ -337,7 +340,7 @@ int pufe_set_projectors(pufe_ctx *ctx, int n, const pufe_projector *proj) {
 int pufe_set_enrichment_phase(pufe_ctx *ctx, int form) {
     if (!ctx) return PUFE_ERR_INVALID_ARG;
     if (!ctx->have_problem) return fail(ctx, PUFE_ERR_STATE, "pufe_set_problem must come first");
-    if (ctx->have_setup) return fail(ctx, PUFE_ERR_STATE, "the enrichment form is set before pufe_setup");
+    if (ctx->have_tables) return fail(ctx, PUFE_ERR_STATE, "the enrichment form is set before pufe_setup");
     if (form != PUFE_ENR_PERIODIC && form != PUFE_ENR_BLOCH)
         return fail(ctx, PUFE_ERR_INVALID_ARG, "unknown enrichment form");
     Problem pr = ctx->prob;
@@ -814,7 +817,7 @@ static int place_moments(pufe_ctx *ctx, hipStream_t st);
 int pufe_set_moment_limit(pufe_ctx *ctx, int64_t bytes) {
     if (!ctx) return PUFE_ERR_INVALID_ARG;
     if (!ctx->have_problem) return fail(ctx, PUFE_ERR_STATE, "pufe_set_problem must come first");
-    if (ctx->have_setup) return fail(ctx, PUFE_ERR_STATE, "the moment forms' limit is set before pufe_setup");
+    if (ctx->have_tables) return fail(ctx, PUFE_ERR_STATE, "the moment forms' limit is set before pufe_setup");
     ctx->mom_limit = bytes < 0 ? -1 : bytes;
     return PUFE_OK;
 }
@@ -824,6 +827,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     if (!ctx->have_problem) return fail(ctx, PUFE_ERR_STATE, "pufe_set_problem must come first");
     hipStream_t st = (hipStream_t)stream;
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
+    ctx->have_setup = ctx->have_tables = false;   // until all of it has succeeded
     {
         hipError_t ea = init_contract_attributes();
         if (ea == hipSuccess) ea = init_moment_attributes();
@@ -951,7 +955,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
         CHECK_HIP(ctx, scratch_address(ctx->device, &ws), "workspace address");
     }
     CHECK_HIP(ctx, hipStreamSynchronize(st), "sync");
-    ctx->have_setup = true;
+    ctx->have_setup = ctx->have_tables = true;
     ++ctx->plan_gen;
     return PUFE_OK;
 }
@@ -959,7 +963,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
 int pufe_set_rule(pufe_ctx *ctx, int64_t n_leaves, const int32_t *level, const int32_t *ijk,
                   const int64_t *elem_leaf_offset, void *stream) {
     if (!ctx) return PUFE_ERR_INVALID_ARG;
-    if (!ctx->have_setup) return fail(ctx, PUFE_ERR_STATE, "pufe_setup must come first");
+    if (!ctx->have_tables) return fail(ctx, PUFE_ERR_STATE, "pufe_setup must come first");
     Plan &pl = ctx->plan;
     const int64_t nel = pl.nel;
     if (n_leaves < nel || !level || !ijk || !elem_leaf_offset)
@@ -990,6 +994,9 @@ int pufe_set_rule(pufe_ctx *ctx, int64_t n_leaves, const int32_t *level, const i
     hipStream_t st = (hipStream_t)stream;
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     CHECK_HIP(ctx, hipStreamSynchronize(st), "sync");
+    // from here on the tables are the new rule's in part: a failure leaves a context
+    // without a rule, not one whose launches read freed or short lists
+    ctx->have_setup = false;
     CHECK_HIP(ctx, ctx->d_leaves.alloc(n_leaves), "alloc leaves");
     CHECK_HIP(ctx, ctx->d_leaf_elem.alloc(n_leaves), "alloc leaf elements");
     CHECK_HIP(ctx, hipMemcpy(ctx->d_leaves.p, codes.data(), sizeof(uint32_t) * n_leaves, hipMemcpyHostToDevice),
@@ -1007,7 +1014,9 @@ int pufe_set_rule(pufe_ctx *ctx, int64_t n_leaves, const int32_t *level, const i
     }
     plan_items(ctx, ctx->tune_items, ctx->tune_block);
     if (ctx->lds > kMaxDynLds) return fail(ctx, PUFE_ERR_UNSUPPORTED, "contraction stage does not fit in LDS");
-    return upload_items(ctx, nullptr);
+    const int rc = upload_items(ctx, nullptr);
+    ctx->have_setup = rc == PUFE_OK;
+    return rc;
 }
 
 int pufe_query(pufe_ctx *ctx, pufe_sizes *out) {
@@ -1595,8 +1604,8 @@ static int plan_adjoint_moments(pufe_ctx *c, int64_t pt_doubles, hipStream_t st)
         c->d_adj_f.release();
     };
     drop();
-    // the serendipity functions are no tensor products; on sheared cells the
-    // sums take the metric's mixed terms too
+    // the fold knows neither the serendipity functions' polynomials nor, on sheared
+    // cells, the metric's mixed terms: both stay with the direct kernels
     if (p > 2 || pl.kp.skew) return PUFE_OK;
     std::vector<AdjStage> stages(pl.nel);
     std::vector<double> cost(pl.nel);
@@ -1899,6 +1908,8 @@ static int place_moments(pufe_ctx *ctx, hipStream_t st) {
 // Upload the element table, work items and partial buffer of the current plan.
 static int upload_items(pufe_ctx *ctx, hipStream_t st) {
     ++ctx->plan_gen;
+    ctx->have_bw = ctx->have_adj = ctx->have_bw_direct = false;
+    ctx->have_poisson = false;
     CHECK_HIP(ctx, ctx->d_elems.upload(ctx->plan.elems, st), "upload elements");
     CHECK_HIP(ctx, ctx->d_items.upload_list(ctx->items, st), "upload work items");
     CHECK_HIP(ctx, ctx->d_items_wide.upload_list(ctx->items_wide, st), "upload work items");
@@ -1911,8 +1922,6 @@ static int upload_items(pufe_ctx *ctx, hipStream_t st) {
         if (rc == PUFE_OK) rc = place_moments(ctx, st);
         if (rc != PUFE_OK) return rc;
     }
-    ctx->have_bw = ctx->have_adj = ctx->have_bw_direct = false;
-    ctx->have_poisson = false;
     return PUFE_OK;
 }
 
@@ -1954,7 +1963,9 @@ int pufe_tune(pufe_ctx *ctx, int precision, const char *cache_path) {
                 ctx->wide_tiles = wide;
                 ctx->tuned = true;
                 plan_items(ctx, items, block);
-                return upload_items(ctx, nullptr);
+                const int rc = upload_items(ctx, nullptr);
+                ctx->have_setup = rc == PUFE_OK;
+                return rc;
             }
         }
     }
@@ -2025,6 +2036,7 @@ int pufe_tune(pufe_ctx *ctx, int precision, const char *cache_path) {
     (void)hipEventDestroy(b);
     if (trc != PUFE_OK) {
         ctx->timing = saved;
+        ctx->have_setup = false;   // the plan of a trial, in part
         return trc;
     }
     ctx->timing = saved;
@@ -2035,6 +2047,7 @@ int pufe_tune(pufe_ctx *ctx, int precision, const char *cache_path) {
     ctx->tuned = true;
     plan_items(ctx, best_items, best_block);
     int rc = upload_items(ctx, nullptr);
+    ctx->have_setup = rc == PUFE_OK;
     if (rc != PUFE_OK) return rc;
     if (cache_path) {
         // append or insert the entry into a flat JSON object

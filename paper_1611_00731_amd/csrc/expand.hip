@@ -1,8 +1,8 @@
 // Element matrices from the moments of moments.hip: every entry of the upper
 // 16x16 tiles of H_e and S_e is a short sum of moments.  Bound by reading the
 // moments and by launch latency on small problems: the work is a few hundred
-// multiply-adds per entry, once per element instead of once per point.  1.05 ms
-// for 1728 elements of up to 283 functions, 95 us for 512 of up to 67.
+// multiply-adds per entry, once per element instead of once per point.  0.88 ms
+// for 1096 elements of up to 283 functions, 98 us for 512 of up to 67.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
