@@ -24,8 +24,8 @@
 // Bound by issue and latency between the matrix instructions (two waves a SIMD,
 // a dozen LDS reads and as many FP64 operations per 15 of them), not by these.
 // Measured, P and Q together: 512 elements of one or two row tiles, 7036 leaves
-// of 216 points 0.95 ms (8.1 ms through the element's own functions), 216
-// elements of up to eleven, 664 leaves 1.7 ms (17.4 ms).
+// of 216 points 0.97 ms (8.1 ms through the element's own functions), 216
+// elements of up to eleven, 664 leaves 1.50 ms (17.4 ms).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
