@@ -828,6 +828,7 @@ int pufe_setup(pufe_ctx *ctx, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     ctx->have_setup = ctx->have_tables = false;   // until all of it has succeeded
+    ++ctx->plan_gen;   // a batch's graph must not replay over what is replaced, also if this fails
     {
         hipError_t ea = init_contract_attributes();
         if (ea == hipSuccess) ea = init_moment_attributes();
@@ -995,8 +996,10 @@ int pufe_set_rule(pufe_ctx *ctx, int64_t n_leaves, const int32_t *level, const i
     CHECK_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     CHECK_HIP(ctx, hipStreamSynchronize(st), "sync");
     // from here on the tables are the new rule's in part: a failure leaves a context
-    // without a rule, not one whose launches read freed or short lists
+    // without a rule, not one whose launches (a batch's graph either) read freed or
+    // short lists
     ctx->have_setup = false;
+    ++ctx->plan_gen;
     CHECK_HIP(ctx, ctx->d_leaves.alloc(n_leaves), "alloc leaves");
     CHECK_HIP(ctx, ctx->d_leaf_elem.alloc(n_leaves), "alloc leaf elements");
     CHECK_HIP(ctx, hipMemcpy(ctx->d_leaves.p, codes.data(), sizeof(uint32_t) * n_leaves, hipMemcpyHostToDevice),
